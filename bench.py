@@ -134,10 +134,10 @@ def main():
         _, tune_ms = hp.hp_autotune(s, ws, 0, 1 << 20, repeats=2)
         (nw, blk_mode), blk_ms = hp.hp_autotune_blocked(s, ws, 0, 1 << 22, repeats=2)
         tune_ms = {"dense": tune_ms, "blocked": blk_ms}
-    # wide blocks with 8 waves (the default, or --nw 8): the whole map, one
-    # range cut at a multiple of 2^17, takes blocks of 2048 sequences where
-    # N >= 17; --nw 4 --blk-mode 3 keeps blocks of 1024 on 4 waves
-    wide8 = blk_mode == 3 and (args.blk_mode < 0 or nw == 8) and s.N >= 17
+    # the largest wide blocks (the default, or --nw 8): the whole map, one
+    # range cut at a multiple of 2^19, takes blocks of 4096 sequences on 8
+    # waves; --nw 4 --blk-mode 3 keeps blocks of 1024 on 2 waves
+    wide8 = blk_mode == 3 and (args.blk_mode < 0 or nw == 8) and s.N >= 19
     kname = ("k_gemm_wide_w8<%d>" % (s.K_pad // 32) if wide8
              else "k_gemm_wide<%d>" % (s.K_pad // 32) if blk_mode == 3
              else "k_gemm_blk<%d,%d,%d>" % (s.K_pad // 32, nw, blk_mode))
@@ -193,14 +193,17 @@ def main():
     # the method's work: nbp contact products h_i h_j and their sum per pair
     method_ops = 2.0 * s.nbp * pairs
     achieved_tops = method_ops / (enum_ms * 1e-3) / 1e12
-    # MFMA work the blocked form issues: one depth-32 product per pair, plus
-    # the per-block first product (K_pad deep, 32 virtual rows) per
-    # conformation tile, once per block of 256 sequences, or of 1024 or 2048
-    # for wide blocks
+    # MFMA work the blocked form issues, in the time of int8 products: one
+    # depth-32 product per pair (wide blocks: per two, which share an
+    # accumulator), plus the per-block first product (32 virtual rows, K_pad
+    # deep; wide blocks: ceil(K_pad / 64) FP4 steps, each in the time of an int8
+    # product of depth 32) per conformation tile, once per block of 256
+    # sequences, or of 1024 or 4096 for wide blocks
     n_tiles = (n_conf + 31) // 32
-    block_seqs = 2048 if wide8 else 1024 if blk_mode == 3 else 256
-    blk_mfma_ops = (2.0 * 32 * pairs +
-                    2.0 * s.K_pad * 32 * 32 * n_tiles * (total // block_seqs))
+    block_seqs = 4096 if wide8 else 1024 if blk_mode == 3 else 256
+    first_depth = 32 * ((s.K_pad // 32 + 1) // 2) if blk_mode == 3 else s.K_pad
+    blk_mfma_ops = (2.0 * 32 * pairs / (2 if blk_mode == 3 else 1) +
+                    2.0 * first_depth * 32 * 32 * n_tiles * (total // block_seqs))
     evals_per_s = pairs / (ms_step * 1e-3)
     src_hash = kernel_source_hash()
 
@@ -223,7 +226,7 @@ def main():
                         "counts + union-find",
             "lattice": "3x3x3", "N": N, "sequences": total, "n_conf": n_conf,
             "n_class": s.n_class, "K": s.K, "K_pad": s.K_pad, "nbp": s.nbp,
-            "form": "blocked_i8", "waves_per_workgroup": 8 if wide8 else nw,
+            "form": "blocked_i8", "waves_per_workgroup": 8 if wide8 else 2 if blk_mode == 3 else nw,
             "staging_mode": blk_mode, "block_sequences": block_seqs,
         },
         "roofline": {
@@ -245,8 +248,7 @@ def main():
         "full_map_ms_3x3x3": ms_step,
         "kernel_ms": {k: float(np.mean(v)) for k, v in kms.items()},
         "enumerate_evals_per_s": pairs / (enum_ms * 1e-3),
-        # matrix-pipe utilisation: what the blocked kernel issues (depth-32
-        # products for every pair plus the per-block first product)
+        # matrix-pipe utilisation: what the blocked kernel issues
         "blocked_mfma_pipe_frac": blk_mfma_ops / (enum_ms * 1e-3) / 1e12 / PEAK_INT8_TOPS,
         "blocked_mfma_ops_per_pair": blk_mfma_ops / pairs,
         "kernel_source_sha": src_hash,

@@ -226,8 +226,8 @@ hp_status hp_enumerate_symmetric_blocked(const hp_structs *s, const void *d_ws, 
  * / 2.  Reversal maps wide blocks onto wide blocks; with a = the h highest
  * monomers (and m the middle one for odd N), b = the h lowest and b' =
  * reverse(b), the canonical wide blocks are those with a <= b'.  One
- * workgroup of 4 waves scores a wide block, the first product of each
- * conformation tile computed once for all four waves.
+ * workgroup scores a wide block, the first product of each conformation tile
+ * computed once for all its waves.
  *   hp_wide_block_count  number of canonical wide blocks: about 2^N / 2048.
  *   hp_enumerate_symmetric_wide  scores canonical wide blocks [b_lo, b_hi)
  *                        and fills d_out / d_emin (full 2^N-entry maps,
@@ -295,10 +295,11 @@ hp_status hp_sample(const hp_structs *s, const void *d_ws, int form, uint64_t se
  * Batched launch: several enumeration jobs, possibly of different lattices
  * and uneven sizes, from one work list of fixed-size items (256 sequences
  * for HP_FORM_GEMM_I8; for HP_FORM_BLOCKED_I8 one wide block where wide
- * blocks apply and the selected staging mode is -1 or 3 -- of 2048 when the
- * job's range ends are multiples of 2^17, N >= 17 and 8 waves are allowed
- * (mode -1, or nw 8), else of 1024 -- otherwise 4 blocks of 256).  Jobs are grouped by product depth (hp_info.K_pad; blocked: also
- * by wide blocks and unary rows) and each group is one kernel launch,
+ * blocks apply and the selected staging mode is -1 or 3 -- of 4096 or 2048
+ * when the job's range ends are multiples of 2^19 (N >= 19) or 2^17 (N >= 17)
+ * and 8 waves are allowed (mode -1, or nw 8), else of 1024 -- otherwise 4
+ * blocks of 256).  Jobs are grouped by product depth (hp_info.K_pad; blocked:
+ * also by wide blocks and unary rows) and each group is one kernel launch,
  * compiled for that depth, with one workgroup per item; the groups
  * are enqueued back to back on `stream`.  HP_FORM_POPCOUNT runs the jobs as
  * separate hp_enumerate calls.  Each job has the meaning of one hp_enumerate
@@ -369,11 +370,11 @@ hp_status hp_enumerate_batch_static(const hp_job *jobs, int njobs, int form, voi
  * while the current tile's keys are updated; 2: as 0, with the per-sequence
  * operand of the second product read from LDS instead of held in registers;
  * 3: wide blocks, one first product per conformation tile shared by the
- * waves of a workgroup: with nw = 8, where both ends of the range are
- * multiples of 2^17 and N >= 17, 2048 sequences (monomers 0 .. 4 and 6, 8,
- * .., 16 vary) per workgroup of 8 waves, otherwise 1024 sequences sharing
- * every monomer above the low 10 per workgroup of 4 waves; with nw = 4
- * always the latter -- pure pair energies over plain ranges only, elsewhere
+ * waves of a workgroup: with nw = 8, 4096 sequences (monomers 0 .. 4 and 6,
+ * 8, .., 18 vary) where both ends of the range are multiples of 2^19 and N >=
+ * 19, 2048 (0 .. 4 and 6, 8, .., 16) for multiples of 2^17 and N >= 17,
+ * otherwise 1024 sequences sharing every monomer above the low 10; with nw =
+ * 4 always the last -- pure pair energies over plain ranges only, elsewhere
  * mode 3 acts as -1; -1, default: 3 with 8 waves where wide blocks apply,
  * else 2 for K_pad <= 192, else 0).  hp_blocked_selected
  * reports them (either pointer may be NULL).  Results never depend on the

@@ -66,17 +66,14 @@ hp_status plan_batch(const hp_job *jobs, int njobs, int form, size_t ws_bytes, c
         kb_max = std::max(kb_max, int(jobs[i].structs->K_pad / 32));
     }
     // blocked jobs group by depth, by whether they carry unary rows and by
-    // the wide blocks they run as (0 none, 1 of 1024, 2 of 2048): key
+    // the wide blocks they run as (0 none, 1 of 1024, 2 of 2048, 3 of 4096): key
     // 8 depth + 2 wide + unary
-    auto wide_kind = [&](int i) {
-        const hp_job &jb = jobs[i];
-        return blk_batch_wide8(jb.structs, jb.seq_lo, jb.seq_hi) ? 2u
-               : blk_batch_wide(jb.structs)                         ? 1u
-                                                                    : 0u;
+    auto wide = [&](int i) {
+        return unsigned(blk_batch_kind(jobs[i].structs, jobs[i].seq_lo, jobs[i].seq_hi));
     };
     auto depth = [&](int i) {
         const hp_structs *t = jobs[i].structs;
-        return int(blocked ? 8 * t->blk_KB + 2 * wide_kind(i) + (t->blk_coefB != 0 ? 1u : 0u)
+        return int(blocked ? 8 * t->blk_KB + 2 * wide(i) + (t->blk_coefB != 0 ? 1u : 0u)
                            : t->K_pad / 32);
     };
     // stable insertion sort by depth (batches hold a handful of jobs)
@@ -92,10 +89,8 @@ hp_status plan_batch(const hp_job *jobs, int njobs, int form, size_t ws_bytes, c
     for (int r = 0; r < njobs; ++r) {
         const hp_job &jb = jobs[order[r]];
         uint64_t items;
-        if (blocked && wide_kind(order[r]) == 2) {
-            items = ((jb.seq_hi - jb.seq_lo) >> kWide11ChunkBits) << 6;
-        } else if (blocked && blk_batch_wide(jb.structs)) {
-            items = ((jb.seq_hi - 1) >> kWideBits) - (jb.seq_lo >> kWideBits) + 1;
+        if (blocked && wide(order[r])) {
+            items = wide_blocks(int(wide(order[r])), jb.seq_lo, jb.seq_hi);
         } else if (blocked) {
             const uint64_t nblk = ((jb.seq_hi - 1) >> kBlkBits) - (jb.seq_lo >> kBlkBits) + 1;
             const uint64_t per = blk_batch_seqs_per_item() >> kBlkBits;
@@ -212,6 +207,7 @@ EnumJob make_enum_job(const hp_structs *s, const void *d_ws, uint64_t lo, uint64
     j.masks = reinterpret_cast<const uint32_t *>(base + s->ws.masks);
     j.gemm_a = reinterpret_cast<const int8_t *>(base + s->ws.gemm_a);
     j.gemm_b = reinterpret_cast<const int8_t *>(base + s->ws.gemm_b);
+    j.wide_c1 = reinterpret_cast<const int8_t *>(base + s->ws.wide_c1);
     j.wide_s2 = s->wide_ok ? reinterpret_cast<const int8_t *>(base + s->ws.wide_s2) : nullptr;
     j.blk_shift = int32_t(s->blk_shift);
     j.blk_win_tiles = int32_t(s->blk_win_tiles);
@@ -362,6 +358,7 @@ hp_status hp_upload(const hp_structs *s, void *d_ws, size_t ws_bytes, void *stre
         {s->ws.gemm_a, s->gemm_a.data(), s->gemm_a.size()},
         {s->ws.gemm_b, s->gemm_b.data(), s->gemm_b.size()},
         {s->ws.blk_s2, s->blk_s2.data(), s->blk_s2.size()},
+        {s->ws.wide_c1, s->wide_c1.data(), s->wide_c1.size()},
         {s->ws.wide_s2, s->wide_s2.data(), s->wide_s2.size()},
     };
     for (const Part &p : parts) {

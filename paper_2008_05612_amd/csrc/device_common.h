@@ -126,9 +126,11 @@ __device__ __forceinline__ uint64_t sequence_at(const EnumJob &j, uint64_t t, ui
 // folds iff that gap reaches the threshold, or it has no other conformation.
 // Plain and sampled jobs write at t - lo; symmetric jobs write the full-size
 // maps at s and reverse(s) and count a non-palindromic sequence twice.
-__device__ __forceinline__ void finish_sequence(const EnumJob &j, uint64_t t, uint64_t s,
-                                                uint64_t rs, bool valid, int gb, int gs,
-                                                bool count_lane, int fmul)
+// Returns the wave's number of deleterious sequences (the same in every lane);
+// the caller sums them and adds them once (count_deleterious).
+__device__ __forceinline__ unsigned finish_sequence(const EnumJob &j, uint64_t t, uint64_t s,
+                                                    uint64_t rs, bool valid, int gb, int gs,
+                                                    int fmul)
 {
     const int nb = gb >> kKeyConfBits;
     const int ns = gs >> kKeyConfBits;
@@ -164,8 +166,15 @@ __device__ __forceinline__ void finish_sequence(const EnumJob &j, uint64_t t, ui
     }
     const unsigned long long del = __ballot(valid && !uniq);
     const unsigned long long del2 = __ballot(valid && !uniq && twin);
-    if (count_lane && j.nondesign && del)
-        atomicAdd(j.nondesign, (unsigned long long)(__popcll(del) + __popcll(del2)));
+    return unsigned(__popcll(del) + __popcll(del2));
+}
+
+// Adds a wave's deleterious count.  One atomic per wave, not per sequence
+// tile: they all go to one address, where they are served one at a time.
+__device__ __forceinline__ void count_deleterious(const EnumJob &j, unsigned del, bool one_lane)
+{
+    if (one_lane && j.nondesign && del)
+        atomicAdd(j.nondesign, (unsigned long long)del);
 }
 
 // B-operand fragments of one lane for T sequences: bytes of product rows

@@ -294,50 +294,6 @@ __device__ __forceinline__ void stage_two(const v4i &a2, const v4i (&sf)[S2_LDS 
     }
 }
 
-// Stage two of one conformation tile in the wide kernel: as stage_two, with
-// two changes that free registers for a third accumulator (four waves per
-// SIMD still fit): the running top-2 of each lane lives in LDS (g[t * 64],
-// read and written only by the rare key update), and the product of
-// sequence tile t + 2 is issued right after tile t's test, so each test reads
-// a product issued a full test earlier.  Issuing that product after the test
-// rather than before or inside it measured fastest (full 3x3x3 map, 8 waves:
-// 310 ms against 314 ms where the compiler placed it and 318 ms before the
-// test): a wave that reaches an MFMA while the matrix pipe still runs another
-// wave's product waits there, and after its nine test instructions the pipe
-// is more often free.
-__device__ __forceinline__ void stage_two_wide(const v4i &a2, const v4i (&sf)[kBlkTiles], int2 *g,
-                                               int (&thr)[kBlkTiles], int conf_base,
-                                               int win_shift)
-{
-    const v16i zero = {};
-    v16i acc[3];
-    acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf[0], zero, 0, 0, 0);
-    acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf[1], zero, 0, 0, 0);
-#pragma unroll
-    for (int t = 0; t < kBlkTiles; ++t) {
-        if (t + 2 < kBlkTiles)
-            acc[(t + 2) % 3] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf[t + 2], zero, 0, 0, 0);
-        const v16i &a = acc[t % 3];
-        const bool hit = __any(max16(a) >= thr[t]);
-        if (t + 2 < kBlkTiles) {
-            // the test's 9 vector instructions (8 v_max3, 1 compare), then the MFMA
-            __builtin_amdgcn_sched_group_barrier(0x002, 9, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        }
-        if (__builtin_expect(hit, 0)) {
-            int b = 0, sc = 0;
-#pragma unroll
-            for (int r = 0; r < 16; r += 2)
-                top2_add2(b, sc, a[r], a[r + 1]);
-            int2 v = g[t * 64];
-            top2_merge(v.x, v.y, window_to_global(b, conf_base, win_shift),
-                       window_to_global(sc, conf_base, win_shift));
-            g[t * 64] = v;
-            thr[t] = absorb_threshold(v.y, win_shift);
-        }
-    }
-}
-
 // Staging of the C1 tiles:
 //   kBlkLds  : double-buffered LDS, one barrier per tile; stage one of a tile
 //              runs right before its stage two.
@@ -451,6 +407,7 @@ __device__ __forceinline__ void blk_body(const EnumJob &j, uint64_t blk0, v4i *l
         }
     }
 
+    unsigned del = 0;
 #pragma unroll
     for (int t = 0; t < kBlkTiles; ++t) {
         const int ob = __shfl_xor(gb[t], 32);
@@ -461,13 +418,14 @@ __device__ __forceinline__ void blk_body(const EnumJob &j, uint64_t blk0, v4i *l
             // a diagonal block holds each sequence and its reverse itself
             const uint64_t sq = blk_sequence(j, outer, t * 32 + col);
             const uint64_t rs = diag ? sq : __builtin_bitreverse64(sq) >> (64 - j.N);
-            finish_sequence(j, sq, sq, rs, half == 0 && blk < j.hi, gb[t], gs[t], lane == 0, 1);
+            del += finish_sequence(j, sq, sq, rs, half == 0 && blk < j.hi, gb[t], gs[t], 1);
         } else {
             const uint64_t idx = outer + uint64_t(t * 32 + col);
-            finish_sequence(j, idx, idx, idx, half == 0 && idx >= j.lo && idx < j.hi, gb[t],
-                            gs[t], lane == 0, 1);
+            del += finish_sequence(j, idx, idx, idx, half == 0 && idx >= j.lo && idx < j.hi,
+                                   gb[t], gs[t], 1);
         }
     }
+    count_deleterious(j, del, lane == 0);
 }
 
 template <int KB, int NW, int MODE, bool CANON, bool UNARY>
@@ -510,131 +468,136 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_blk_batch(BatchHeader *hdr, in
 
 // ---------------------------------------------------------------------------
 // Wide blocks (pure pair energies): one block of sequences sharing every
-// outer monomer per workgroup, wave w scoring the 256 sequences whose
-// varying monomers above the low 8 are the bits of w.  The block term, the
-// weights w_v of the varying monomers and their 16 pair terms fill all but
-// one or three of the 32 virtual rows, so ONE first product per
-// conformation tile serves every wave of the workgroup: each wave computes
-// it for every NW-th tile (one group of NW tiles ahead) and hands the packed
-// result to the others through LDS.  Three geometries (G):
-//   0  plain ranges, 1024 sequences (the low 10 monomers), 4 waves;
+// outer monomer per workgroup.  The block term, the weights w_v of the varying
+// monomers and their 16 pair terms are at most 29 virtual rows, so ONE first
+// product per 32-conformation tile serves every wave of the workgroup: each
+// wave computes it for every NW-th tile (one group of NW tiles ahead) and
+// hands the packed result to the others through LDS.  Four geometries (G):
+//   0  plain ranges, 1024 sequences (the low 10 monomers), 2 waves;
 //   1  reversal-canonical blocks, 1024 sequences (the 10 around the middle),
-//      4 waves;
+//      2 waves;
 //   2  plain ranges cut at multiples of 2^17, 2048 sequences (monomers 0 .. 4
 //      and the even ones 6 .. 16: equal parity never touches, so 11 varying
-//      monomers have only 14 pairs), 8 waves, so a first product serves 2048
-//      sequences; the default where it applies.
-// Per 32 x 32 tile the matrix pipe runs one depth-32 product plus 1/NW of the
-// first product's K_pad/32, and the first product is packed once per
-// workgroup.
+//      monomers have only 14 pairs), 4 waves;
+//   3  plain ranges cut at multiples of 2^19, 4096 sequences (monomers 0 .. 4
+//      and the even ones 6 .. 18: 16 pairs), 8 waves.
+//
+// The second product is a threshold scan.  Counts of H-H contacts are at
+// most 31 (kScanMaxContacts), so one int32 accumulator holds two sequences:
+// column `col` of sequence tile t carries x = 64 t + col and x + 32, whose
+// operands differ in one varying monomer, with indicator bytes h(x) +
+// 64 h(x + 32), and two constant virtual rows (1 and 64, the last two of the
+// 32) carry V = 32 - T of each, T being the smallest count that can still
+// change that sequence's two best (one more than its second best).  The
+// accumulator is
+//   64 (32 + n(x + 32) - T(x + 32)) + (32 + n(x) - T(x)),
+// both fields within 0 .. 63, and bits 11 and 5 say whether n reaches T.  A
+// lane ORs its 16 accumulators (8 v_or3 per product, for 32 conformations x
+// 64 sequences), and only a tile in which some bit is set is absorbed.  A
+// conformation below T can change neither the lowest energy, nor its
+// conformation when unique, nor whether it is unique, nor the gap to the
+// second-lowest energy, so every output is that of updating every key (which
+// conformation the second key names may differ; it is never reported).
+// Simulated on sampled 3x3x3 blocks, 8 % of a wave's tiles hold a hit.
+//
+// The first product runs in FP4 (0/1 weights times the 0/1 contact matrix,
+// depth 64 per MFMA in the time an int8 product of depth 32 takes, exact in
+// the float accumulator), which halves its matrix time and the bytes of the
+// contact matrix that every workgroup reads.
 // ---------------------------------------------------------------------------
 
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// bits 5 and 11 of an accumulator: the count of either sequence reaches its
+// threshold
+constexpr int kScanHit = (1 << 5) | (1 << 11);
+
 template <int G>
-constexpr int wide_bits() { return G == 2 ? kWide11Bits : kWideBits; }
+constexpr int wide_bits() { return G == 3 ? kWide12Bits : G == 2 ? kWide11Bits : kWideBits; }
 template <int G>
-constexpr int wide_waves() { return G == 2 ? kWide11Waves : 4; }
-// virtual rows: 0 block term, 1 .. nb weights, then 16 pairs, then 2 index rows
+constexpr int wide_waves() { return 1 << (wide_bits<G>() - kWideWaveBits); }
+// virtual rows: 0 block term, 1 .. nb weights, then 16 pairs; 30 and 31 the
+// constants 1 and 64
 template <int G>
 constexpr int wide_row_vv() { return 1 + wide_bits<G>(); }
+// first-product steps of depth 64 for pair depth KB * 32
+template <int KB>
+constexpr int wide_steps() { return (KB + 1) / 2; }
+// waves of the second-product table before those of geometry G
 template <int G>
-constexpr int wide_row_idx() { return wide_row_vv<G>() + 16; }
+constexpr int wide_s2_slot() { return G == 0 ? 0 : G == 1 ? 2 : G == 2 ? 4 : 8; }
 
 // Varying monomer x of a wide block: G 0 the low 10; G 1 the 10 around the
 // middle, h = j.half_bits outer monomers on each side (and, for odd N, the
-// middle monomer h + 5 outer as well); G 2 monomers 0 .. 4, 6, 8, .., 16.
+// middle monomer h + 5 outer as well); G 2, 3 monomers 0 .. 4, 6, 8, ...
 template <int G>
 __device__ __forceinline__ int wide_pos(const EnumJob &j, int x)
 {
     if constexpr (G == 1)
         return j.half_bits + x + (x >= 5 ? (j.N & 1) : 0);
-    else if constexpr (G == 2)
+    else if constexpr (G >= 2)
         return x < 5 ? x : 2 * x - 4;
     else
         return x;
-}
-
-template <int G>
-__device__ __forceinline__ bool wide_varies(const EnumJob &j, int i)
-{
-    if constexpr (G == 0) {
-        return i < kWideBits;
-    } else if constexpr (G == 2) {
-        return i < 5 || (i >= 6 && i <= 16 && !(i & 1));
-    } else {
-        const int h = j.half_bits, odd = j.N & 1;
-        return i >= h && i < h + kWideBits + odd && !(odd && i == h + 5);
-    }
 }
 
 // Pair p (0 .. 15) of the block's varying monomers as x-indices a | b << 4.
 template <int G>
 __device__ __forceinline__ int wide_pair(const EnumJob &j, int p)
 {
-    const uint64_t w = G == 2                     ? (p < 8 ? kW11Pairs0 : kW11Pairs1)
+    const uint64_t w = G == 3                     ? (p < 8 ? kW12Pairs0 : kW12Pairs1)
+                       : G == 2                   ? (p < 8 ? kW11Pairs0 : kW11Pairs1)
                        : (G == 1 && (j.N & 1)) ? (p < 8 ? kMid10OddPairs0 : kMid10OddPairs1)
                                                  : (p < 8 ? kLow10Pairs0 : kLow10Pairs1);
     return int((w >> (8 * (p & 7))) & 0xffu);
 }
 
-// First-product A operand of a wide block, fragment kb of this lane:
-// virtual row m (0 block term, 1 .. nb the weight of varying monomer m - 1,
-// then the 16 varying pairs, then the two index rows) over product rows
-// k = 32 kb + 16 half + q of C1.
+// Eight bits spread to the nibbles of a word as FP4 ones (code 2).
+__device__ __forceinline__ uint32_t fp4_ones(uint32_t b)
+{
+    b = (b | (b << 12)) & 0x000f000fu;
+    b = (b | (b << 6)) & 0x03030303u;
+    b = (b | (b << 3)) & 0x11111111u;
+    return b << 1;
+}
+
+// First-product A operand of a wide block, step `st` of this lane: virtual
+// row m over product rows k = 64 st + 32 half + n, n < 32, row k being the
+// pair (i, i + d) of the k-th odd separation d >= 3 in (d, i) order.  Every
+// row is a symmetric function of two monomer sets, bit (i, j) = X_i Y_j or
+// Y_i X_j: the block term has X = Y = the outer H monomers, a weight X = its
+// monomer and Y = the outer H monomers, a varying pair one monomer each.  So
+// a run of separation d is one word, X & (Y >> d) | Y & (X >> d), and the 32
+// bits of a step are gathered from the runs that overlap it.
 template <int G>
 __device__ __forceinline__ v4i wide_v_fragment(const EnumJob &j, uint64_t outer, int m, int half,
-                                               int kb)
+                                               int st)
 {
-    constexpr int kRowVV = wide_row_vv<G>(), kRowIdx = wide_row_idx<G>();
-    const int N = j.N;
-    const int coef = j.blk_coef;
-    const int wv = m >= 1 && m < kRowVV ? wide_pos<G>(j, m - 1) : -1;
-    int va = -1, vb = -1;
-    if (m >= kRowVV && m < kRowIdx) {
+    constexpr int kRowVV = wide_row_vv<G>();
+    uint64_t X = 0, Y = 0;
+    if (m == 0) {
+        X = Y = outer;
+    } else if (m < kRowVV) {
+        X = uint64_t(1) << wide_pos<G>(j, m - 1);
+        Y = outer;
+    } else if (m < kRowVV + 16) {
         const int pr = wide_pair<G>(j, m - kRowVV);
-        va = wide_pos<G>(j, pr & 15);
-        vb = wide_pos<G>(j, pr >> 4);
+        X = uint64_t(1) << wide_pos<G>(j, pr & 15);
+        Y = uint64_t(1) << wide_pos<G>(j, pr >> 4);
     }
-    // product row k < K is the pair (i, i + d) of the k-th odd separation
-    // d >= 3 in (d, i) order
-    const int kbase = kb * 32 + half * 16;
-    int d = 3, i = kbase;
-    while (d < N && i >= N - d) {
-        i -= N - d;
-        d += 2;
+    const int N = j.N;
+    uint32_t bits = 0;
+    int s = -(64 * st + 32 * half);   // where the run of separation d starts in the step
+    for (int d = 3; d < N; d += 2) {
+        const uint64_t run = (X & (Y >> d)) | (Y & (X >> d));
+        const int len = N - d;
+        if (s < 32 && s + len > 0)
+            bits |= s >= 0 ? uint32_t(run) << s : uint32_t(run >> -s);
+        s += len;
     }
-    uint32_t w[4];
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-        uint32_t word = 0;
-#pragma unroll
-        for (int bb = 0; bb < 4; ++bb) {
-            const int k = kbase + q4 * 4 + bb;
-            int v = 0;
-            if (k == j.K) {
-                v = m == kRowIdx ? 1 : 0;
-            } else if (k == j.K + 1) {
-                v = m == kRowIdx + 1 ? -1 : 0;
-            } else if (d < N) {
-                const int jj = i + d;
-                const bool out_i = !wide_varies<G>(j, i), out_j = !wide_varies<G>(j, jj);
-                const bool h_i = (outer >> i) & 1u, h_j = (outer >> jj) & 1u;
-                if (m == 0)
-                    v = out_i && out_j && h_i && h_j ? -coef : 0;
-                else if (m < kRowVV)
-                    v = (i == wv && out_j && h_j) || (jj == wv && out_i && h_i) ? -coef : 0;
-                else if (m < kRowIdx)
-                    v = i == va && jj == vb ? -coef : 0;
-            }
-            word |= (uint32_t(v) & 0xffu) << (8 * bb);
-            ++i;   // next row: next i, or the next run
-            if (d < N && i + d >= N) {
-                i = 0;
-                d += 2;
-            }
-        }
-        w[q4] = word;
-    }
-    return v4i{int(w[0]), int(w[1]), int(w[2]), int(w[3])};
+    return v4i{int(fp4_ones(bits & 0xffu)), int(fp4_ones((bits >> 8) & 0xffu)),
+               int(fp4_ones((bits >> 16) & 0xffu)), int(fp4_ones(bits >> 24))};
 }
 
 // Canonical wide block index t -> outer bits, as blk_canonical_outer with 10
@@ -662,48 +625,173 @@ __device__ __forceinline__ uint64_t wide_canonical_outer(const EnumJob &j, uint6
     return (uint64_t(a) << (h + kWideBits + odd)) | (uint64_t(m) << (h + 5)) | b;
 }
 
-// Plain-11 block index t -> outer bits: chunk t >> 6 of 2^17 sequences, and
-// within it bits 0 .. 5 of t on the outer monomers 5, 7, .., 15.
-__device__ __forceinline__ uint64_t wide11_outer(uint64_t t)
+// Block index of a chunked geometry (G 2: 2^17 sequences in 64 blocks, G 3:
+// 2^19 in 128) -> outer bits: the chunk, and within it the low bits of t on
+// the outer monomers 5, 7, ...
+template <int G>
+__device__ __forceinline__ uint64_t wide_chunk_outer(uint64_t t)
 {
-    uint64_t o = (t >> 6) << kWide11ChunkBits;
+    constexpr int kOuter = G == 3 ? 7 : 6;
+    uint64_t o = (t >> kOuter) << (2 * kOuter + 5);
 #pragma unroll
-    for (int k = 0; k < 6; ++k)
+    for (int k = 0; k < kOuter; ++k)
         o |= ((t >> k) & 1u) << (5 + 2 * k);
     return o;
 }
 
-// The work of one workgroup: wave w of NW = wide_waves<G>() scores the 256
-// sequences x = 256 w + 32 t + col (t = 0 .. 7) of block `blk` (plain 10:
-// sequence >> 10; canonical: canonical block index; plain 11: chunk << 6 |
-// the outer bits of the chunk).  vlds holds the block's first-product
-// fragments, a2s the packed first products of two groups of NW tiles
-// ([2][NW][64]), gbs every lane's running top-2 keys ([NW][8][64]).
+// Keys of the scan's two best: (n << 17) | (row << 12) | (tile + 1), the
+// conformation 32 tile + row at count n (tiles fit: kScanMaxTiles); 0 is "no
+// conformation".  V = 32 - T of a sequence whose second-best key is gs: T is
+// one more than that key's count, 0 while it is "no conformation".
+__device__ __forceinline__ int scan_bias(int gs)
+{
+    return 32 - int((unsigned(gs) + kMaxConf) >> kKeyConfBits);
+}
+
+// The same key with the conformation's number in its low bits, as
+// finish_sequence reads it.
+__device__ __forceinline__ int scan_global(int k)
+{
+    const int conf = ((k & 0xfff) - 1) * kTileConf + ((k >> 12) & 31);
+    return k ? (k & ~int(kMaxConf)) | (conf + 1) : 0;
+}
+
+// OR of a lane's 16 accumulators (8 v_or3).
+__device__ __forceinline__ int or16(const v16i &a)
+{
+    int o = a[0];
+#pragma unroll
+    for (int r = 1; r < 15; r += 2)
+        o = o | a[r] | a[r + 1];
+    return o | a[15];
+}
+
+// The two largest of a lane's 16 accumulators by one field, unsigned, as
+// (field << 26) | row: shifting the accumulator left by 26 keeps the lower
+// field alone, by 20 the upper one above the lower (whose bits only break
+// ties).  One shift-or per register and, per two registers, v_max3, v_med3
+// and half of a v_max3; the median is written as the instruction, which the
+// compiler does not find beside the maximum of the same values (its inputs are
+// results of vector instructions, not of the matrix product).
+template <int SHIFT>
+__device__ __forceinline__ void scan_best(const v16i &a, unsigned &b, unsigned &s)
+{
+    b = s = 0;
+#pragma unroll
+    for (int q = 0; q < 16; q += 4) {
+        unsigned m[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            // row of register q in this lane: 8 (q / 4) + 4 half + q % 4
+            const unsigned k0 = (unsigned(a[q + 2 * p]) << SHIFT) | unsigned(2 * q + 2 * p);
+            const unsigned k1 = (unsigned(a[q + 2 * p + 1]) << SHIFT) | unsigned(2 * q + 2 * p + 1);
+            asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m[p]) : "v"(b), "v"(k0), "v"(k1));
+            b = max(max(b, k0), k1);
+        }
+        s = max(max(s, m[0]), m[1]);
+    }
+}
+
+// Absorbs the 32 conformations of tile `tile` into the two best of the
+// column's sequences: the scan's product again, the two best rows of each
+// field that has a hit, an exchange between the lane halves after which a
+// lane holds the candidates of its own sequence (half 0 the lower field, half
+// 1 the upper) from both halves' rows, and the merge as keys into *g.  A
+// candidate below T, or of an empty column, merges as a key below the second
+// best and changes nothing.  The two V bytes sit in the last word of the
+// second operand of the half-1 lanes.
+__device__ __forceinline__ void scan_absorb(const v4i &a2, v4i &sf, int hit, int2 *g, int tile,
+                                            int half)
+{
+    const v16i zero = {};
+    const v16i a = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf, zero, 0, 0, 0);
+    int2 v = *g;
+    unsigned b0 = 0, s0 = 0, b1 = 0, s1 = 0;
+    if (__any((hit & 32) != 0))
+        scan_best<26>(a, b0, s0);
+    if (__any((hit & 2048) != 0))
+        scan_best<20>(a, b1, s1);
+    // (x, y) -> ([x of half 0 | y of half 0], [x of half 1 | y of half 1])
+    const auto pb = __builtin_amdgcn_permlane32_swap(b0, b1, false, false);
+    const auto ps = __builtin_amdgcn_permlane32_swap(s0, s1, false, false);
+    const int base = tile + 1 - (scan_bias(v.y) << kKeyConfBits);
+    auto key = [&](unsigned k, int more) {
+        return int(((k >> 26) << kKeyConfBits) + ((k & 31) << 12)) + base + more;
+    };
+    top2_merge(v.x, v.y, key(pb[0], 0), key(ps[0], 0));
+    top2_merge(v.x, v.y, key(pb[1], 4 << 12), key(ps[1], 4 << 12));
+    *g = v;
+    const int nb = scan_bias(v.y);
+    const auto pv = __builtin_amdgcn_permlane32_swap(nb, nb, false, false);
+    const int word = int((pv[0] << 16) | (pv[1] << 24));
+    sf[3] = half ? (sf[3] & 0xffff) | word : sf[3];
+}
+
+// Second product of one conformation tile: the threshold scan of the wave's
+// 512 sequences.  NA accumulators: with three, each OR chain reads a product
+// issued a full chain earlier; the next product is issued after the chain
+// (forced with sched_group_barrier), when the matrix pipe is more often free.
+// Measured alone, an int8 product takes 34 SIMD cycles, and with n vector
+// instructions beside it 12 + 4.2 n where that is more: 44 for the 8 v_or3.
+template <int NA>
+__device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], int2 *g, int tile,
+                                          int half)
+{
+    const v16i zero = {};
+    v16i acc[NA];
+    int hit[kBlkTiles];
+#pragma unroll
+    for (int t = 0; t < NA - 1; ++t)
+        acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf[t], zero, 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < kBlkTiles; ++t) {
+        const int n = t + NA - 1;
+        if (n < kBlkTiles)
+            acc[n % NA] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf[n], zero, 0, 0, 0);
+        hit[t] = or16(acc[t % NA]);
+        if (n < kBlkTiles) {
+            __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+    }
+    const int any = (hit[0] | hit[1] | hit[2]) | (hit[3] | hit[4]) | (hit[5] | hit[6] | hit[7]);
+    if (__builtin_expect(__any((any & kScanHit) != 0), 0)) {
+#pragma unroll
+        for (int t = 0; t < kBlkTiles; ++t)
+            if (__any((hit[t] & kScanHit) != 0))
+                scan_absorb(a2, sf[t], hit[t], g + t * 64, tile, half);
+    }
+}
+
+// The work of one workgroup: wave w of NW = wide_waves<G>() scores the 512
+// sequences x = 512 w + 64 t + lane (t = 0 .. 7) of block `blk` (plain 10:
+// sequence >> 10; canonical: canonical block index; chunked: chunk and the
+// outer bits within it).  vlds holds the block's first-product fragments, a2s
+// the packed first products of two groups of NW tiles ([2][NW][64]), gbs
+// every sequence's two best keys ([NW][8][64]).
 template <int KB, int G>
 __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, v4i *vlds, v4i *a2s,
                                           int2 *gbs)
 {
     constexpr int NW = wide_waves<G>();
+    constexpr int KS = wide_steps<KB>();
+    // deep products leave registers for two accumulators (four waves per SIMD)
+    constexpr int kAcc = KS <= 3 ? 3 : 2;
     bool diag = false;
     const uint64_t outer = G == 1   ? wide_canonical_outer(j, blk, &diag)
-                           : G == 2 ? wide11_outer(blk)
+                           : G >= 2 ? wide_chunk_outer<G>(blk)
                                     : blk << kWideBits;
-    // Contact tiles of the first product are loaded one group ahead into
-    // registers for shallow products; deep ones (K_pad > 160) load right
-    // before use, which keeps four waves per SIMD.
-    constexpr bool kPrefetch = KB <= 5;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int col = lane & 31;
     const int half = lane >> 5;
-    const v4i *__restrict__ B1 = reinterpret_cast<const v4i *>(j.gemm_b);
+    const v4i *__restrict__ C1 = reinterpret_cast<const v4i *>(j.wide_c1);
 
-    // the waves build the block's fragments, one kb at a time
-    for (int kb = wave; kb < KB; kb += NW)
-        vlds[kb * 64 + lane] = wide_v_fragment<G>(j, outer, col, half, kb);
+    // the waves build the block's fragments, one step at a time
+    for (int st = wave; st < KS; st += NW)
+        vlds[st * 64 + lane] = wide_v_fragment<G>(j, outer, lane & 31, half, st);
     v4i sf[kBlkTiles];
     const v4i *__restrict__ S2 = reinterpret_cast<const v4i *>(j.wide_s2) +
-                                 ((G == 0 ? 0 : G == 1 ? 4 : 8) + wave) * (kBlkTiles * 64);
+                                 (wide_s2_slot<G>() + wave) * (kBlkTiles * 64);
 #pragma unroll
     for (int t = 0; t < kBlkTiles; ++t)
         sf[t] = S2[t * 64 + lane];
@@ -713,110 +801,98 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, v4i *v
     // also wait for the contact-tile loads issued one group ahead.
     __builtin_amdgcn_s_waitcnt(0x0f70);
 
-    // this lane's running top-2 (global keys) per sequence tile, in LDS
+    // this lane's two best (global keys) per sequence tile, in LDS
     int2 *const top2 = gbs + wave * (kBlkTiles * 64) + lane;
-    int thr[kBlkTiles];
 #pragma unroll
-    for (int t = 0; t < kBlkTiles; ++t) {
+    for (int t = 0; t < kBlkTiles; ++t)
         top2[t * 64] = int2{0, 0};
-        thr[t] = 0;
-    }
 
     const int n_tiles = j.n_tiles;
-    const int win_tiles = j.blk_win_tiles;
-    const int win_shift = j.blk_shift;
+    const int n_conf = j.n_conf;
 
     // contact tile `tile` of the first product (this lane's fragments); every
     // wave reads only its own tiles, straight from global memory (L2-resident)
-    auto load_c1 = [&](int tile, v4i (&c1)[KB]) {
-        const v4i *__restrict__ src = B1 + size_t(tile) * (KB * 64) + lane;
+    auto load_c1 = [&](int tile, v4i (&c1)[KS]) {
+        const v4i *__restrict__ src = C1 + size_t(tile) * (KS * 64) + lane;
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-            c1[kb] = src[kb * 64];
+        for (int st = 0; st < KS; ++st)
+            c1[st] = src[st * 64];
     };
-    // first product of a tile into this wave's slot of buffer `buf`
-    auto first = [&](const v4i (&c1)[KB], int buf) {
-        v16i d1;
+    // first product of a tile into this wave's slot of buffer `buf`: row
+    // 8 (q / 4) + 4 half + q % 4 of the result is byte q of this lane's second
+    // operand, and the two constant rows are bytes 14 and 15 of half 1
+    // (0 in columns beyond the last conformation, whose accumulators stay 0)
+    auto first = [&](const v4i (&c1)[KS], int tile, int buf) {
+        v16f d1;
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-            const v16i zero = {};
-            d1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(vlds[kb * 64 + lane], c1[kb],
-                                                       kb == 0 ? zero : d1, 0, 0, 0);
+        for (int st = 0; st < KS; ++st) {
+            const v16f zero = {};
+            const v4i v = vlds[st * 64 + lane];
+            const v8i a = {v[0], v[1], v[2], v[3], 0, 0, 0, 0};
+            const v8i b = {c1[st][0], c1[st][1], c1[st][2], c1[st][3], 0, 0, 0, 0};
+            d1 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, st == 0 ? zero : d1, 4, 4,
+                                                                 0, 0, 0, 0);
         }
-        a2s[(buf * NW + wave) * 64 + lane] = pack_d1(d1);
+        const int ones = half && tile * kTileConf + (lane & 31) < n_conf ? 0x40010000 : 0;
+        v4i p;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            uint32_t x = 0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                x = __builtin_amdgcn_cvt_pk_u8_f32(d1[4 * w + b], b, x);
+            p[w] = int(x);
+        }
+        p[3] |= ones;   // rows 30 and 31 of the product are 0
+        a2s[(buf * NW + wave) * 64 + lane] = p;
     };
 
-    v4i c1[KB];
+    v4i c1[KS];
     __syncthreads();   // vlds
     if (wave < n_tiles) {
         load_c1(wave, c1);
-        first(c1, 0);
+        first(c1, wave, 0);
     }
-    if (kPrefetch && NW + wave < n_tiles)
+    if (NW + wave < n_tiles)
         load_c1(NW + wave, c1);
     __syncthreads();
-    int conf_base = 0;
-    int wnext = win_tiles;   // first tile of the next key window
     // The packed first product of the next tile is read from LDS one tile
-    // ahead, so no tile starts by waiting for it.  With 8 waves the group's
-    // barrier sits before its last tile: by then every wave has read all of
-    // this group's buffer and written its first product of the next group,
-    // so the next group's first tile can be read ahead as well.  (With 4 waves
-    // that needs registers beyond four waves per SIMD where the contact tiles
-    // are prefetched, and measured slower where they are not; there the
-    // barrier stays at the group's end and each group's first tile is read at
-    // its start.)
-    constexpr bool kEarlyBarrier = NW == 8;
+    // ahead, so no tile starts by waiting for it.  The group's barrier sits
+    // before its last tile: by then every wave has read all of this group's
+    // buffer and written its first product of the next group, so the next
+    // group's first tile can be read ahead as well.
     v4i a2n = a2s[lane];
     for (int g = 0; g * NW < n_tiles; ++g) {
         const int buf = g & 1;
         const int nt = (g + 1) * NW + wave;   // this wave's tile of the next group
-        if constexpr (!kEarlyBarrier)
-            a2n = a2s[(buf * NW) * 64 + lane];
-#pragma unroll
+#pragma unroll 1
         for (int tt = 0; tt < NW; ++tt) {
             const int tile = g * NW + tt;
             const v4i a2 = a2n;
             if (tt + 1 < NW) {
                 a2n = a2s[(buf * NW + tt + 1) * 64 + lane];
-            } else if constexpr (kEarlyBarrier) {
+            } else {
                 // the next group's first products are visible, and this
                 // group's buffer is free for the group after it
                 __syncthreads();
                 a2n = a2s[((buf ^ 1) * NW) * 64 + lane];
             }
-            if (tile < n_tiles) {
-                if (tile == wnext) {
-                    conf_base += win_tiles * kTileConf;
-                    wnext += win_tiles;
-                }
-                stage_two_wide(a2, sf, top2, thr, conf_base, win_shift);
-            }
+            if (tile < n_tiles)
+                scan_tile<kAcc>(a2, sf, top2, tile, half);
             if (tt == 0 && nt < n_tiles) {
-                if (!kPrefetch)
-                    load_c1(nt, c1);
-                first(c1, buf ^ 1);
-                if (kPrefetch && nt + NW < n_tiles)
+                first(c1, nt, buf ^ 1);
+                if (nt + NW < n_tiles)
                     load_c1(nt + NW, c1);
             }
         }
-        if constexpr (!kEarlyBarrier)
-            __syncthreads();   // as above, at the group's end
     }
 
-    int gb[kBlkTiles], gs[kBlkTiles];
-#pragma unroll
+    unsigned del = 0;
+#pragma unroll 1
     for (int t = 0; t < kBlkTiles; ++t) {
-        const int2 v = top2[t * 64];
-        gb[t] = v.x;
-        gs[t] = v.y;
-    }
-#pragma unroll
-    for (int t = 0; t < kBlkTiles; ++t) {
-        const int ob = __shfl_xor(gb[t], 32);
-        const int os = __shfl_xor(gs[t], 32);
-        top2_merge(gb[t], gs[t], ob, os);
-        const int x = wave * 256 + t * 32 + col;
+        const int2 k = top2[t * 64];
+        const int2 v = {scan_global(k.x), scan_global(k.y)};
+        const int x = wave * 512 + t * 64 + lane;
         if constexpr (G == 1) {
             // off the diagonal the block's reverse is never scored: write both;
             // a diagonal block holds each sequence and its reverse itself
@@ -825,54 +901,68 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, v4i *v
             for (int b = 0; b < kWideBits; ++b)
                 sq |= uint64_t((x >> b) & 1) << wide_pos<1>(j, b);
             const uint64_t rs = diag ? sq : __builtin_bitreverse64(sq) >> (64 - j.N);
-            finish_sequence(j, sq, sq, rs, half == 0 && blk < j.hi, gb[t], gs[t], lane == 0, 1);
-        } else if constexpr (G == 2) {
+            del += finish_sequence(j, sq, sq, rs, blk < j.hi, v.x, v.y, j.A);
+        } else if constexpr (G >= 2) {
             uint64_t sq = outer | uint64_t(x & 31);
 #pragma unroll
-            for (int b = 5; b < kWide11Bits; ++b)
-                sq |= uint64_t((x >> b) & 1) << wide_pos<2>(j, b);
-            finish_sequence(j, sq, sq, sq, half == 0 && sq >= j.lo && sq < j.hi, gb[t], gs[t],
-                            lane == 0, 1);
+            for (int b = 5; b < wide_bits<G>(); ++b)
+                sq |= uint64_t((x >> b) & 1) << wide_pos<G>(j, b);
+            del += finish_sequence(j, sq, sq, sq, sq >= j.lo && sq < j.hi, v.x, v.y, j.A);
         } else {
             const uint64_t idx = outer + uint64_t(x);
-            finish_sequence(j, idx, idx, idx, half == 0 && idx >= j.lo && idx < j.hi, gb[t],
-                            gs[t], lane == 0, 1);
+            del += finish_sequence(j, idx, idx, idx, idx >= j.lo && idx < j.hi, v.x, v.y, j.A);
         }
     }
+    count_deleterious(j, del, lane == 0);
 }
 
 template <int KB, bool CANON>
-__global__ __launch_bounds__(256) void k_gemm_wide(EnumJob j)
+__global__ __launch_bounds__(128, 4) void k_gemm_wide(EnumJob j)
 {
-    // first-product A operand of the block (the same for all four waves), the
-    // packed first products of the current and the next group of 4 tiles and
-    // every lane's running top-2 keys
-    __shared__ v4i vlds[KB * 64];
-    __shared__ v4i a2s[2 * 4 * 64];
-    __shared__ int2 gbs[4 * kBlkTiles * 64];
+    // first-product A operand of the block (the same for every wave), the
+    // packed first products of the current and the next group of tiles and
+    // every sequence's two best keys
+    constexpr int NW = wide_waves<0>();
+    __shared__ v4i vlds[wide_steps<KB>() * 64];
+    __shared__ v4i a2s[2 * NW * 64];
+    __shared__ int2 gbs[NW * kBlkTiles * 64];
     wide_body<KB, CANON ? 1 : 0>(j, (CANON ? j.lo : j.lo >> kWideBits) + blockIdx.x, vlds, a2s,
                                  gbs);
 }
 
-// Plain ranges cut at multiples of 2^17: blocks of 2048 sequences, 8 waves
-// (two workgroups per CU: 53 KB of LDS each at K_pad 160).
+// Plain ranges cut at multiples of 2^17: blocks of 2048 sequences, 4 waves.
 template <int KB>
-__global__ __launch_bounds__(512) void k_gemm_wide_w8(EnumJob j)
+__global__ __launch_bounds__(256, 4) void k_gemm_wide_w4(EnumJob j)
 {
-    __shared__ v4i vlds[KB * 64];
-    __shared__ v4i a2s[2 * kWide11Waves * 64];
-    __shared__ int2 gbs[kWide11Waves * kBlkTiles * 64];
+    constexpr int NW = wide_waves<2>();
+    __shared__ v4i vlds[wide_steps<KB>() * 64];
+    __shared__ v4i a2s[2 * NW * 64];
+    __shared__ int2 gbs[NW * kBlkTiles * 64];
     wide_body<KB, 2>(j, ((j.lo >> kWide11ChunkBits) << 6) + blockIdx.x, vlds, a2s, gbs);
 }
 
-// Batched wide blocks for jobs of one product depth: workgroup b scores the
-// wide block of item item_lo + b, in the job whose item range holds it.
+// Plain ranges cut at multiples of 2^19: blocks of 4096 sequences, 8 waves.
 template <int KB>
-__global__ __launch_bounds__(256) void k_gemm_wide_batch(BatchHeader *hdr, int item_lo)
+__global__ __launch_bounds__(512, 4) void k_gemm_wide_w8(EnumJob j)
 {
-    __shared__ v4i vlds[KB * 64];
-    __shared__ v4i a2s[2 * 4 * 64];
-    __shared__ int2 gbs[4 * kBlkTiles * 64];
+    constexpr int NW = wide_waves<3>();
+    __shared__ v4i vlds[wide_steps<KB>() * 64];
+    __shared__ v4i a2s[2 * NW * 64];
+    __shared__ int2 gbs[NW * kBlkTiles * 64];
+    wide_body<KB, 3>(j, ((j.lo >> kWide12ChunkBits) << 7) + blockIdx.x, vlds, a2s, gbs);
+}
+
+// Batched wide blocks for jobs of one product depth and geometry G (0, 2 or
+// 3): workgroup b scores the wide block of item item_lo + b, in the job whose
+// item range holds it.
+template <int KB, int G>
+__global__ __launch_bounds__(64 * wide_waves<G>(), 4) void k_gemm_wide_batch(BatchHeader *hdr,
+                                                                             int item_lo)
+{
+    constexpr int NW = wide_waves<G>();
+    __shared__ v4i vlds[wide_steps<KB>() * 64];
+    __shared__ v4i a2s[2 * NW * 64];
+    __shared__ int2 gbs[NW * kBlkTiles * 64];
     const EnumJob *jobs = reinterpret_cast<const EnumJob *>(hdr + 1);
     const int njobs = hdr->njobs;
     const int64_t *start = reinterpret_cast<const int64_t *>(jobs + njobs);
@@ -887,74 +977,46 @@ __global__ __launch_bounds__(256) void k_gemm_wide_batch(BatchHeader *hdr, int i
     }
     lo = __builtin_amdgcn_readfirstlane(lo);
     const EnumJob &j = jobs[lo];
-    wide_body<KB, 0>(j, (j.lo >> kWideBits) + uint64_t(it - start[lo]), vlds, a2s, gbs);
+    const uint64_t blk0 = G == 3   ? (j.lo >> kWide12ChunkBits) << 7
+                          : G == 2 ? (j.lo >> kWide11ChunkBits) << 6
+                                   : j.lo >> kWideBits;
+    wide_body<KB, G>(j, blk0 + uint64_t(it - start[lo]), vlds, a2s, gbs);
 }
 
-// The same with blocks of 2048 sequences on 8 waves, for jobs whose range
-// ends are multiples of 2^17: item b of a job is its block b of the chunked
-// 2048-sequence geometry.
-template <int KB>
-__global__ __launch_bounds__(512) void k_gemm_wide_batch_w8(BatchHeader *hdr, int item_lo)
+template <int KB, int G>
+hipError_t launch_wide_batch_g(BatchHeader *hdr, int item_lo, unsigned grid, hipStream_t st)
 {
-    __shared__ v4i vlds[KB * 64];
-    __shared__ v4i a2s[2 * kWide11Waves * 64];
-    __shared__ int2 gbs[kWide11Waves * kBlkTiles * 64];
-    const EnumJob *jobs = reinterpret_cast<const EnumJob *>(hdr + 1);
-    const int njobs = hdr->njobs;
-    const int64_t *start = reinterpret_cast<const int64_t *>(jobs + njobs);
-    const int it = item_lo + int(blockIdx.x);
-    int lo = 0, hi = njobs - 1;   // job with start[job] <= it < start[job+1]
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) / 2;
-        if (start[mid] <= it)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    lo = __builtin_amdgcn_readfirstlane(lo);
-    const EnumJob &j = jobs[lo];
-    wide_body<KB, 2>(j, ((j.lo >> kWide11ChunkBits) << 6) + uint64_t(it - start[lo]), vlds, a2s,
-                     gbs);
+    hipLaunchKernelGGL((k_gemm_wide_batch<KB, G>), dim3(grid), dim3(64 * wide_waves<G>()), 0, st,
+                       hdr, item_lo);
+    return hipGetLastError();
 }
 
-// wide: 1 blocks of 1024 on 4 waves, 2 blocks of 2048 on 8 waves
+// wide: 1 blocks of 1024, 2 blocks of 2048, 3 blocks of 4096
 template <int KB>
 hipError_t launch_wide_batch(BatchHeader *hdr, int item_lo, unsigned grid, int wide,
                              hipStream_t st)
 {
-    if (wide == 2)
-        hipLaunchKernelGGL((k_gemm_wide_batch_w8<KB>), dim3(grid), dim3(512), 0, st, hdr,
-                           item_lo);
-    else
-        hipLaunchKernelGGL((k_gemm_wide_batch<KB>), dim3(grid), dim3(256), 0, st, hdr, item_lo);
-    return hipGetLastError();
-}
-
-// With 8 waves allowed, plain ranges take blocks of 2048 when both ends are
-// multiples of 2^17 and monomer 16 exists; otherwise blocks of 1024 (4
-// waves).  The 2048 geometry issues half the first products and re-reads the
-// contact matrix half as often, and two workgroups per CU keep the SIMDs
-// busy while one meets at its group barrier (16 waves in one workgroup per
-// CU, tried, left them idle there).
-inline bool wide11_applies(const EnumJob &j)
-{
-    const uint64_t m = (uint64_t(1) << kWide11ChunkBits) - 1;
-    return j.N >= kWide11ChunkBits && j.hi > j.lo && (j.lo & m) == 0 && (j.hi & m) == 0;
+    return wide == 3   ? launch_wide_batch_g<KB, 3>(hdr, item_lo, grid, st)
+           : wide == 2 ? launch_wide_batch_g<KB, 2>(hdr, item_lo, grid, st)
+                       : launch_wide_batch_g<KB, 0>(hdr, item_lo, grid, st);
 }
 
 template <int KB>
-hipError_t launch_wide(const EnumJob &j, bool waves8, hipStream_t st)
+hipError_t launch_wide(const EnumJob &j, bool chunked, hipStream_t st)
 {
     if (j.mode == kSeqCanonical) {
-        hipLaunchKernelGGL((k_gemm_wide<KB, true>), dim3(unsigned(j.hi - j.lo)), dim3(256), 0, st,
-                           j);
-    } else if (waves8 && wide11_applies(j)) {
-        const uint64_t n = ((j.hi - j.lo) >> kWide11ChunkBits) << 6;
-        hipLaunchKernelGGL((k_gemm_wide_w8<KB>), dim3(unsigned(n)), dim3(512), 0, st, j);
-    } else {
-        const uint64_t n = ((j.hi - 1) >> kWideBits) - (j.lo >> kWideBits) + 1;
-        hipLaunchKernelGGL((k_gemm_wide<KB, false>), dim3(unsigned(n)), dim3(256), 0, st, j);
+        hipLaunchKernelGGL((k_gemm_wide<KB, true>), dim3(unsigned(j.hi - j.lo)),
+                           dim3(64 * wide_waves<1>()), 0, st, j);
+        return hipGetLastError();
     }
+    const int kind = wide_kind(j.N, j.lo, j.hi, chunked);
+    const dim3 grid(unsigned(wide_blocks(kind, j.lo, j.hi)));
+    if (kind == 3)
+        hipLaunchKernelGGL((k_gemm_wide_w8<KB>), grid, dim3(64 * wide_waves<3>()), 0, st, j);
+    else if (kind == 2)
+        hipLaunchKernelGGL((k_gemm_wide_w4<KB>), grid, dim3(64 * wide_waves<2>()), 0, st, j);
+    else
+        hipLaunchKernelGGL((k_gemm_wide<KB, false>), grid, dim3(64 * wide_waves<0>()), 0, st, j);
     return hipGetLastError();
 }
 

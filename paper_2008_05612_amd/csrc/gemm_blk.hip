@@ -57,18 +57,27 @@ constexpr int kDepths = int(sizeof(kBlocked) / sizeof(kBlocked[0])) - 1;
 
 uint64_t blk_batch_seqs_per_item() { return uint64_t(1) << kWideBits; }
 
-bool blk_batch_wide(const hp_structs *s)
+int wide_kind(int N, uint64_t lo, uint64_t hi, bool chunked)
 {
-    const int mode = blocked_selected_mode();
-    return s->wide_ok && (mode < 0 || mode == kBlkStageWide);
+    auto cut = [&](int bits) {
+        return N >= bits && ((lo | hi) & ((uint64_t(1) << bits) - 1)) == 0;
+    };
+    return !chunked ? 1 : cut(kWide12ChunkBits) ? 3 : cut(kWide11ChunkBits) ? 2 : 1;
 }
 
-bool blk_batch_wide8(const hp_structs *s, uint64_t lo, uint64_t hi)
+uint64_t wide_blocks(int kind, uint64_t lo, uint64_t hi)
 {
-    const uint64_t m = (uint64_t(1) << kWide11ChunkBits) - 1;
+    return kind == 3   ? (hi - lo) >> kWide12Bits
+           : kind == 2 ? (hi - lo) >> kWide11Bits
+                       : ((hi - 1) >> kWideBits) - (lo >> kWideBits) + 1;
+}
+
+int blk_batch_kind(const hp_structs *s, uint64_t lo, uint64_t hi)
+{
     const int mode = blocked_selected_mode();
-    return blk_batch_wide(s) && (mode < 0 || blocked_selected_nw() == 8) &&
-           s->N >= kWide11ChunkBits && hi > lo && (lo & m) == 0 && (hi & m) == 0;
+    if (!s->wide_ok || !(mode < 0 || mode == kBlkStageWide))
+        return 0;
+    return wide_kind(s->N, lo, hi, mode < 0 || blocked_selected_nw() == 8);
 }
 
 hipError_t launch_gemm_blk_batch(void *d_batch_ws, int kb, bool unary, int wide, int item_lo,
@@ -91,8 +100,8 @@ hipError_t launch_gemm_blocked(const EnumJob &j, int nw, int mode, hipStream_t s
     // the second operand in LDS for shallow products
     const bool wide_ok = j.wide_s2 && j.mode == kSeqPlain && j.blk_ngroups == 0 &&
                          j.blk_coefB == 0;
-    // wide blocks: 8 waves (blocks of 2048 where the range allows) by default
-    // or when 8 waves are selected; 4 waves (blocks of 1024) when 4 are
+    // wide blocks: the largest that the range allows by default or when 8
+    // waves are selected; blocks of 1024 when 4 are
     const bool wide8 = mode < 0 || nw == 8;
     if (mode == kBlkStageWide && !wide_ok)
         mode = -1;

@@ -255,6 +255,7 @@ __device__ __forceinline__ void gemm_body(const EnumJob &j, uint64_t seq0_wg, v4
         }
     }
 
+    unsigned del = 0;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         const int ob = __shfl_xor(gb[t], 32);
@@ -263,8 +264,9 @@ __device__ __forceinline__ void gemm_body(const EnumJob &j, uint64_t seq0_wg, v4
         const uint64_t idx = seq0 + t * 32 + col;
         uint64_t rs;
         const uint64_t sq = sequence_at(j, idx, &rs);
-        finish_sequence(j, idx, sq, rs, half == 0 && idx < j.hi, gb[t], gs[t], lane == 0, 1);
+        del += finish_sequence(j, idx, sq, rs, half == 0 && idx < j.hi, gb[t], gs[t], 1);
     }
+    count_deleterious(j, del, lane == 0);
 }
 
 template <int KB, int T, int NW, int MODE>

@@ -35,8 +35,9 @@ struct WsLayout {
     size_t gemm_a = 0;   // int8_t[n_tiles][K_pad/32][64 lanes][16]
     size_t gemm_b = 0;   // blocked form: int8_t[n_tiles][K_pad/32][64 lanes][16], or none
     size_t blk_s2 = 0;   // blocked form: int8_t[2 geometries][8 tiles][64 lanes][16], or none
-    size_t wide_s2 = 0;  // wide blocks: int8_t[4 + 4 + 8 waves][8 tiles][64 lanes][16] (geometries:
-                         // plain 10, canonical 10, plain 11), or none
+    size_t wide_c1 = 0;  // wide blocks: FP4 [n_tiles][ceil(K/64)][64 lanes][32 values], or none
+    size_t wide_s2 = 0;  // wide blocks: int8_t[2 + 2 + 4 + 8 waves][8 tiles][64 lanes][16]
+                         // (geometries: plain 10, canonical 10, plain 11, plain 12), or none
     size_t total = 0;
 };
 
@@ -74,6 +75,7 @@ struct hp_structs {
     std::vector<int8_t> gemm_b;       // blocked form: 0/1 contact matrix + window index rows
     std::vector<int8_t> blk_s2;       // blocked form: per-sequence operand of the second product
     bool wide_ok = false;             // wide blocks apply (pure pair energies, N >= 10)
+    std::vector<int8_t> wide_c1;      // wide blocks: 0/1 contact matrix in FP4
     std::vector<int8_t> wide_s2;      // wide blocks: per-sequence operand of the second product
     std::vector<uint8_t> pair_rows;   // K_pad * 4: (i, j, constant, 0) per product row
     hpmap::WsLayout ws;
@@ -93,11 +95,17 @@ constexpr int kLow8Pair8 = 0x74;                          // (4,7)
 constexpr int kLow8NumPairs = 9;
 
 // Wide blocks of the blocked form: 2^kWideBits = 1024 sequences sharing
-// every monomer above the low 10, scored by the 4 waves of one workgroup.
+// every monomer above the low 10, scored by one workgroup, 2^kWideWaveBits =
+// 512 sequences per wave.
 // Pairs of the low 10 monomers with odd separation >= 3, as x-indices
 // a | b << 4 a byte each: pairs 0 .. 7 in kLow10Pairs0, 8 .. 15 in
 // kLow10Pairs1 (shared by the host tables and the kernel).
 constexpr int kWideBits = 10;
+constexpr int kWideWaveBits = 9;
+// The second product packs the contact counts of two sequences in one
+// accumulator, 6 bits each (no accepted box has more than 28 contacts).
+constexpr uint32_t kScanMaxContacts = 31;
+constexpr uint32_t kScanMaxTiles = 4094;   // 12 bits of a scan key, and one more than the tile
 constexpr uint64_t kLow10Pairs0 = 0x5096857463524130ull;   // (0,3) (1,4) (2,5) (3,6) (4,7) (5,8) (6,9) (0,5)
 constexpr uint64_t kLow10Pairs1 = 0x9092817094837261ull;   // (1,6) (2,7) (3,8) (4,9) (0,7) (1,8) (2,9) (0,9)
 constexpr int kLow10NumPairs = 16;
@@ -107,20 +115,26 @@ constexpr int kLow10NumPairs = 16;
 // with odd N (x-indices, same byte layout):
 constexpr uint64_t kMid10OddPairs0 = 0x7151806096854130ull;  // (0,3) (1,4) (5,8) (6,9) (0,6) (0,8) (1,5) (1,7)
 constexpr uint64_t kMid10OddPairs1 = 0x8464937353826291ull;  // (1,9) (2,6) (2,8) (3,5) (3,7) (3,9) (4,6) (4,8)
-// Wide blocks of 2048 sequences for plain ranges, scored by the 8 waves of
-// one workgroup: the 11 varying monomers are 0 .. 4 and the even monomers
-// 6, 8, .., 16 (pos(x) = x for x < 5, 2 x - 4 after).  Monomers of equal
-// parity are never in contact (odd separation), so the only varying pairs
-// are (0,3), (1,4) and those of monomers 1 and 3 with the six even ones: 14
-// pairs, padded to 16 with two pairs of equal parity whose rows stay zero;
-// base, 11 weights, 16 pair rows and 2 index rows fill 30 of the 32 virtual
-// rows.  The outer monomers 5, 7, .., 15 of a 2^17-sequence chunk index its
-// 64 blocks.  Pairs as x-indices a | b << 4:
+// Wide blocks of 2048 sequences for plain ranges: the 11 varying monomers
+// are 0 .. 4 and the even monomers 6, 8, .., 16 (pos(x) = x for x < 5, 2 x - 4
+// after).  Monomers of equal parity are never in contact (odd separation), so
+// the only varying pairs are (0,3), (1,4) and those of monomers 1 and 3 with
+// the six even ones: 14 pairs, padded to 16 with two pairs of equal parity
+// whose rows stay zero; block term, 11 weights, 16 pair rows and 2 constant
+// rows fill 30 of the 32 virtual rows.  The outer monomers 5, 7, .., 15 of a
+// 2^17-sequence chunk index its 64 blocks.  Pairs as x-indices a | b << 4:
 constexpr int kWide11Bits = 11;
-constexpr int kWide11Waves = 8;
 constexpr int kWide11ChunkBits = 17;
 constexpr uint64_t kW11Pairs0 = 0xA191817161514130ull;   // (0,3) (1,4) (1,5) (1,6) (1,7) (1,8) (1,9) (1,10)
 constexpr uint64_t kW11Pairs1 = 0x4220A39383736353ull;   // (3,5) (3,6) (3,7) (3,8) (3,9) (3,10) (0,2) (2,4)
+// Wide blocks of 4096: monomer 18 varies as well, and the 16 pairs are (0,3),
+// (1,4) and those of monomers 1 and 3 with the seven even ones; 31 virtual
+// rows.  The outer monomers 5, 7, .., 17 of a 2^19-sequence chunk index its
+// 128 blocks.
+constexpr int kWide12Bits = 12;
+constexpr int kWide12ChunkBits = 19;
+constexpr uint64_t kW12Pairs0 = 0xA191817161514130ull;   // (0,3) (1,4) (1,5) (1,6) (1,7) (1,8) (1,9) (1,10)
+constexpr uint64_t kW12Pairs1 = 0xB3A39383736353B1ull;   // (1,11) (3,5) (3,6) (3,7) (3,8) (3,9) (3,10) (3,11)
 
 struct BlockGeometry {
     int pos[8];
@@ -145,7 +159,7 @@ EnumJob make_enum_job(const hp_structs *s, const void *d_ws, uint64_t lo, uint64
 // by the caller (nothing is allocated).
 struct BatchGroup {
     int kb, item_lo, item_hi;   // product depth (blocked: 8 depth + 2 wide + unary, wide 0 none,
-                                // 1 blocks of 1024, 2 blocks of 2048), its items
+                                // 1, 2, 3 blocks of 1024, 2048, 4096), its items
 };
 hp_status plan_batch(const hp_job *jobs, int njobs, int form, size_t ws_bytes, char *host,
                      int *order, int64_t *start, BatchGroup *groups, int *ngroups);

@@ -43,9 +43,10 @@ struct EnumJob {
     int32_t blk_KB, blk_coefB, blk_ngroups;   // first-product depth / 32, m2 B, unary rows
     uint64_t blk_grp[3];                      // unary group of each outer monomer (4 bits)
     const int8_t *blk_s2;           // second-product operand of this geometry (8 x 64 x 16 B)
-    const int8_t *wide_s2;          // wide blocks: second-product operand ((4 + 4 + 8) waves
-                                    // x 8 x 64 x 16 B: plain 10, canonical 10 and plain 11
-                                    // geometries), or null where wide blocks do not apply
+    const int8_t *wide_c1;          // wide blocks: 0/1 contact matrix in FP4
+    const int8_t *wide_s2;          // wide blocks: second-product operand ((2 + 2 + 4 + 8) waves
+                                    // x 8 x 64 x 16 B: plain 10, canonical 10, plain 11 and
+                                    // plain 12 geometries), or null where they do not apply
 };
 
 // Index -> sequence maps of a job.  kSeqPlain: index t is sequence t.
@@ -94,17 +95,22 @@ hipError_t launch_gemm_blocked(const EnumJob &j, int nw, int mode, hipStream_t s
 hipError_t launch_gemm_wide_canonical(const EnumJob &j, hipStream_t st);
 // Staging modes of the blocked form's contact tiles (gemm_blk.h); mode < 0
 // picks by product depth.
-// kBlkStageWide: wide blocks of 1024 sequences per workgroup of 4 waves,
-// the first product shared by the waves (pure pair energies, plain ranges).
+// kBlkStageWide: wide blocks of 1024, 2048 or 4096 sequences per workgroup, the
+// first product shared by the waves (pure pair energies, plain ranges).
 enum BlkStage { kBlkStageLds = 0, kBlkStagePipe = 1, kBlkStageS2Lds = 2, kBlkStageWide = 3 };
 // Batched launch of the blocked form (plain jobs), same work-list layout:
-// items of blk_batch_seqs_per_item() sequences, one wide block of 1024 (wide
-// jobs: blk_batch_wide) or 4 blocks of 256, or one wide block of 2048 (jobs
-// whose range ends are multiples of 2^17: blk_batch_wide8), one workgroup per
-// item; wide = 0, 1 (blocks of 1024) or 2 (blocks of 2048).
+// items of blk_batch_seqs_per_item() sequences (4 blocks of 256) or of one
+// wide block, one workgroup per item; wide = blk_batch_kind, 0 or the wide
+// geometry (wide_kind) of the job.
 uint64_t blk_batch_seqs_per_item();
-bool blk_batch_wide(const hp_structs *s);
-bool blk_batch_wide8(const hp_structs *s, uint64_t lo, uint64_t hi);
+int blk_batch_kind(const hp_structs *s, uint64_t lo, uint64_t hi);
+// Wide geometry of a plain range: 3 (blocks of 4096) when both ends are
+// multiples of 2^19 and monomer 18 exists, 2 (blocks of 2048) for multiples
+// of 2^17 and monomer 16, else or when not `chunked` 1 (blocks of 1024).  The
+// larger blocks share a first product over more sequences.
+int wide_kind(int N, uint64_t lo, uint64_t hi, bool chunked);
+// Blocks (workgroups) of a plain range in that geometry.
+uint64_t wide_blocks(int kind, uint64_t lo, uint64_t hi);
 hipError_t launch_gemm_blk_batch(void *d_batch_ws, int kb, bool unary, int wide, int item_lo,
                                  int item_hi, hipStream_t st);
 // Process-wide launch shape of the blocked form (runtime.cpp).

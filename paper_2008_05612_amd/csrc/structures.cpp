@@ -677,35 +677,40 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
         }
     }
 
-    // Wide blocks (pure pair energies), three geometries: plain (the low 10
-    // monomers vary), reversal-canonical (the 10 around the middle) and
-    // plain 11 (monomers 0 .. 4 and 6, 8, .., 16; N >= 17), see
-    // hp_internal.h.  Wave w of the workgroup holds the 256 sequences whose
-    // varying monomers above the low 8 are the bits of w (4 waves, or 8 for
-    // plain 11).  Same first-product matrix and key scale as above; the
-    // virtual rows are m = 0 the block term, 1 .. nb the weight of varying
-    // monomer m - 1, then the 16 varying pairs (kLow10Pairs, kMid10OddPairs
-    // for odd N canonical, kW11Pairs), then the two index bytes.  Lane l of
-    // tile t of wave w holds block sequence x = 256 w + 32 t + (l & 31) and
-    // its byte q the indicator of row m = 8 (q / 4) + 4 (l / 32) + q % 4.
+    // Wide blocks (pure pair energies), four geometries: plain (the low 10
+    // monomers vary), reversal-canonical (the 10 around the middle), plain 11
+    // (monomers 0 .. 4 and 6, 8, .., 16; N >= 17) and plain 12 (.., 18; N >=
+    // 19), see hp_internal.h.  The first product's contact matrix is 0/1 in
+    // FP4 (code 2 is 1.0), 64 product rows per step: lane l holds conformation
+    // l & 31 and rows 64 step + 32 (l / 32) + n, n = 0 .. 31, a nibble each.
+    // The virtual rows are m = 0 the block term, 1 .. nb the weight of varying
+    // monomer m - 1, then the 16 varying pairs (kLow10Pairs, kMid10OddPairs for
+    // odd N canonical, kW11Pairs, kW12Pairs), and 30 and 31 the constants 1 and
+    // 64.  Lane l of tile t of wave w of the second operand holds the
+    // sequences x = 512 w + 64 t + (l & 31) and x + 32: its byte q is, for row
+    // m = 8 (q / 4) + 4 (l / 32) + q % 4, the indicator of x plus 64 times that
+    // of x + 32, and V = 32 of either sequence (no threshold yet) for the
+    // constants.
     s->wide_ok = false;
+    s->wide_c1.clear();
     s->wide_s2.clear();
     const int wodd = N & 1;
     const int whalf = N >= kWideBits ? (N - kWideBits - wodd) / 2 : 0;
-    const int n_geom = N >= kWide11ChunkBits ? 3 : 2;
-    auto wide_nb = [&](int g) { return g == 2 ? kWide11Bits : kWideBits; };
+    const int n_geom = N >= kWide12ChunkBits ? 4 : N >= kWide11ChunkBits ? 3 : 2;
+    auto wide_nb = [&](int g) { return g == 3 ? kWide12Bits : g == 2 ? kWide11Bits : kWideBits; };
     auto wide_pos = [&](int g, int x) {
         return g == 0 ? x : g == 1 ? whalf + x + (x >= 5 ? wodd : 0) : (x < 5 ? x : 2 * x - 4);
     };
     auto wide_pair = [&](int g, int p) {
-        const uint64_t w = g == 2 ? (p < 8 ? kW11Pairs0 : kW11Pairs1)
+        const uint64_t w = g == 3   ? (p < 8 ? kW12Pairs0 : kW12Pairs1)
+                           : g == 2 ? (p < 8 ? kW11Pairs0 : kW11Pairs1)
                            : (g == 1 && wodd) ? (p < 8 ? kMid10OddPairs0 : kMid10OddPairs1)
                                               : (p < 8 ? kLow10Pairs0 : kLow10Pairs1);
         return int((w >> (8 * (p & 7))) & 0xffu);
     };
     if (s->blk_ok && B == 0 && N >= kWideBits) {
         int maxw = 0;   // largest weight of a varying monomer (all outer monomers H)
-        for (int g = 0; g < n_geom; ++g) {
+        for (int g = 0; g < std::min(n_geom, 3); ++g) {
             bool vary[64] = {};
             for (int x = 0; x < wide_nb(g); ++x)
                 vary[wide_pos(g, x)] = true;
@@ -722,38 +727,50 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
                 }
             }
         }
-        s->wide_ok = int64_t(s->blk_coef) * maxw <= 128;
+        s->wide_ok = int64_t(s->blk_coef) * maxw <= 128 && s->nbp <= kScanMaxContacts &&
+                     n_tiles <= kScanMaxTiles;
     }
     if (s->wide_ok) {
-        const int n_waves = n_geom == 3 ? 4 + 4 + kWide11Waves : 4 + 4;
-        s->wide_s2.assign(size_t(n_waves) * 8 * 64 * 16, 0);
-        for (int slot = 0; slot < n_waves; ++slot) {
-            const int g = slot < 4 ? 0 : slot < 8 ? 1 : 2;
-            const int w = slot < 8 ? slot & 3 : slot - 8;
-            const int row_vv = 1 + wide_nb(g), row_idx = row_vv + 16;
-            for (int t = 0; t < 8; ++t)
-                for (int lane = 0; lane < 64; ++lane) {
-                    const int x = 256 * w + 32 * t + (lane & 31), half = lane >> 5;
-                    for (int q = 0; q < 16; ++q) {
-                        const int m = 8 * (q / 4) + 4 * half + q % 4;
-                        int v = 0;
-                        if (m == 0) {
-                            v = -128;
-                        } else if (m < row_vv) {
-                            v = ((x >> (m - 1)) & 1) ? -128 : 0;
-                        } else if (m < row_idx) {
-                            const int pr = wide_pair(g, m - row_vv);
-                            v = ((x >> (pr & 15)) & (x >> (pr >> 4)) & 1) ? -128 : 0;
-                        } else if (m == row_idx) {
-                            v = 1;
-                        } else if (m == row_idx + 1) {
-                            v = -128;
+        const uint32_t steps = (s->blk_KB + 1) / 2;
+        s->wide_c1.assign(size_t(n_tiles) * steps * 1024, 0);
+        for (uint32_t c = 0; c < n_conf; ++c)
+            for (uint32_t q = 0; q < s->nbp; ++q) {
+                const int i = s->contacts[(size_t(c) * s->nbp + q) * 2];
+                const int j = s->contacts[(size_t(c) * s->nbp + q) * 2 + 1];
+                const uint32_t k = uint32_t(pidx[size_t(i) * N + j]), n = k % 32;
+                const uint32_t lane = c % kTileConf + 32 * (k / 32 % 2);
+                int8_t &b = s->wide_c1[((size_t(c / kTileConf) * steps + k / 64) * 64 + lane) * 16 +
+                                       n / 2];
+                b = int8_t(b | (2 << (4 * (n % 2))));
+            }
+        const int slots[5] = {0, 2, 4, 8, 16};   // first wave of each geometry
+        s->wide_s2.assign(size_t(slots[n_geom]) * 8 * 64 * 16, 0);
+        for (int g = 0; g < n_geom; ++g)
+            for (int slot = slots[g]; slot < slots[g + 1]; ++slot) {
+                const int row_vv = 1 + wide_nb(g);
+                for (int t = 0; t < 8; ++t)
+                    for (int lane = 0; lane < 64; ++lane) {
+                        const int half = lane >> 5;
+                        for (int q = 0; q < 16; ++q) {
+                            const int m = 8 * (q / 4) + 4 * half + q % 4;
+                            auto indicator = [&](int x) {
+                                if (m == 0)
+                                    return 1;
+                                if (m < row_vv)
+                                    return (x >> (m - 1)) & 1;
+                                if (m < row_vv + 16) {
+                                    const int pr = wide_pair(g, m - row_vv);
+                                    return (x >> (pr & 15)) & (x >> (pr >> 4)) & 1;
+                                }
+                                return 0;
+                            };
+                            const int x = 512 * (slot - slots[g]) + 64 * t + (lane & 31);
+                            const int v = m >= 30 ? 32 : indicator(x) + 64 * indicator(x + 32);
+                            s->wide_s2[((size_t(slot) * 8 + t) * 64 + lane) * 16 + q] =
+                                static_cast<int8_t>(v);
                         }
-                        s->wide_s2[((size_t(slot) * 8 + t) * 64 + lane) * 16 + q] =
-                            static_cast<int8_t>(v);
                     }
-                }
-        }
+            }
     }
 
     // pair table for the popcount form, 4 bytes per row (i, j, 0, 0)
@@ -773,7 +790,8 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
     L.gemm_a = up(L.masks + s->masks.size() * 4);
     L.gemm_b = up(L.gemm_a + s->gemm_a.size());
     L.blk_s2 = up(L.gemm_b + s->gemm_b.size());
-    L.wide_s2 = up(L.blk_s2 + s->blk_s2.size());
+    L.wide_c1 = up(L.blk_s2 + s->blk_s2.size());
+    L.wide_s2 = up(L.wide_c1 + s->wide_c1.size());
     L.total = up(L.wide_s2 + s->wide_s2.size());
     return HP_OK;
 }
