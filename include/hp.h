@@ -370,13 +370,13 @@ hp_status hp_enumerate_batch_static(const hp_job *jobs, int njobs, int form, voi
  * while the current tile's keys are updated; 2: as 0, with the per-sequence
  * operand of the second product read from LDS instead of held in registers;
  * 3: wide blocks, one first product per conformation tile shared by the
- * waves of a workgroup: with nw = 8, 4096 sequences (monomers 0 .. 4 and 6,
- * 8, .., 18 vary) where both ends of the range are multiples of 2^19 and N >=
- * 19, 2048 (0 .. 4 and 6, 8, .., 16) for multiples of 2^17 and N >= 17,
- * otherwise 1024 sequences sharing every monomer above the low 10; with nw =
- * 4 always the last -- pure pair energies over plain ranges only, elsewhere
- * mode 3 acts as -1; -1, default: 3 with 8 waves where wide blocks apply,
- * else 2 for K_pad <= 192, else 0).  hp_blocked_selected
+ * waves of a workgroup: 1024 sequences sharing every monomer above the low
+ * 10, and with nw = 8 in ranges beyond 2^21 sequences 4096 (monomers 0 .. 4
+ * and 6, 8, .., 18 vary) in whole chunks of 2^19 where N >= 19 and 2048 (0 ..
+ * 4 and 6, 8, .., 16) in the other whole chunks of 2^17 where N >= 17 -- pure
+ * pair energies over plain ranges only, elsewhere mode 3 acts as -1; -1, default: 3 with 8 waves where wide blocks apply,
+ * else 2 for K_pad <= 192, else 0).  Few sequences (4e5 / ceil(K_pad / 32)
+ * with mode -1) run as columns of the dense scan instead.  hp_blocked_selected
  * reports them (either pointer may be NULL).  Results never depend on the
  * shape.
  * Errors: HP_EINVAL for another value, or mode 3 with nw = 2.
@@ -407,7 +407,11 @@ hp_status hp_autotune_blocked(const hp_structs *s, const void *d_ws, uint64_t se
  * through LDS and each wave overlaps the products of one tile with the key
  * updates of the previous one.  The choice is
  * process-wide per K_pad and shared by all threads; the first listed shape is
- * the default.  The launch configuration never changes results, only speed.
+ * the default.  With it, handles of pure pair energies and of two-letter
+ * tables of small integers run the threshold scan instead, whose launch shape
+ * follows the number of sequences; another shape chosen here, or found faster
+ * than the scan by hp_autotune, runs in its place.  The launch configuration
+ * never changes results, only speed.
  *   hp_gemm_shape_count  number of compiled shapes for K_pad (0 if none);
  *   hp_gemm_shape_info   describe shape idx (any out pointer may be NULL);
  *   hp_gemm_select       make shape idx the choice for K_pad;

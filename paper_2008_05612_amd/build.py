@@ -17,7 +17,8 @@ OBJ = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libhpmap.so")
 SOURCES = ["structures.cpp", "capi.cpp", "capi_static.hip", "runtime.cpp", "kernels_popcount.hip",
            "gemm_kb1_4.hip", "gemm_kb5.hip", "gemm_kb6_10.hip", "gemm_kb11_12.hip",
-           "gemm_batch.hip", "gemm_blk.hip", "gemm_blk_kb1_3.hip", "gemm_blk_kb4.hip",
+           "gemm_batch.hip", "gemm_scan.hip", "gemm_scan_kb1_4.hip", "gemm_scan_kb5_7.hip",
+           "gemm_scan_kb8_10.hip", "gemm_scan_un1_3.hip", "gemm_scan_un4_6.hip", "gemm_blk.hip", "gemm_blk_kb1_3.hip", "gemm_blk_kb4.hip",
            "gemm_blk_kb5.hip", "gemm_blk_kb6_7.hip", "gemm_blk_kb8_9.hip", "gemm_blk_kb10.hip",
            "gemm_blk_kb11_12.hip",
            "kernels_net.hip"]

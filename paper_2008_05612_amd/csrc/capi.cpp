@@ -207,7 +207,9 @@ EnumJob make_enum_job(const hp_structs *s, const void *d_ws, uint64_t lo, uint64
     j.masks = reinterpret_cast<const uint32_t *>(base + s->ws.masks);
     j.gemm_a = reinterpret_cast<const int8_t *>(base + s->ws.gemm_a);
     j.gemm_b = reinterpret_cast<const int8_t *>(base + s->ws.gemm_b);
-    j.wide_c1 = reinterpret_cast<const int8_t *>(base + s->ws.wide_c1);
+    j.scan_c1 = reinterpret_cast<const int8_t *>(base + s->ws.scan_c1);
+    j.scan_un = reinterpret_cast<const int8_t *>(base + s->ws.scan_un);
+    j.scan_kb = s->scan_kb;
     j.wide_s2 = s->wide_ok ? reinterpret_cast<const int8_t *>(base + s->ws.wide_s2) : nullptr;
     j.blk_shift = int32_t(s->blk_shift);
     j.blk_win_tiles = int32_t(s->blk_win_tiles);
@@ -358,7 +360,8 @@ hp_status hp_upload(const hp_structs *s, void *d_ws, size_t ws_bytes, void *stre
         {s->ws.gemm_a, s->gemm_a.data(), s->gemm_a.size()},
         {s->ws.gemm_b, s->gemm_b.data(), s->gemm_b.size()},
         {s->ws.blk_s2, s->blk_s2.data(), s->blk_s2.size()},
-        {s->ws.wide_c1, s->wide_c1.data(), s->wide_c1.size()},
+        {s->ws.scan_c1, s->scan_c1.data(), s->scan_c1.size()},
+        {s->ws.scan_un, s->scan_un.data(), s->scan_un.size()},
         {s->ws.wide_s2, s->wide_s2.data(), s->wide_s2.size()},
     };
     for (const Part &p : parts) {
@@ -382,6 +385,17 @@ struct RunOpts {
     uint64_t *seqs = nullptr;
 };
 
+// Few sequences of the blocked form run faster as columns of their own (the
+// dense scan) than as blocks.  A sweep of blocks over the conformations takes
+// 0.2 us per tile whatever their number, a column 4.1e-7 us per tile and
+// product of its chain (3x3x3, chains of 5: 65536 sequences 0.44 against 0.63
+// ms, 131072 0.81 against 0.63; 6x6, 10: 20000 0.24 against 0.34 ms, 40000 0.36
+// against 0.34).  Only without a selected launch shape.
+bool blocked_small(const hp_structs *s, uint64_t n)
+{
+    return blocked_selected_mode() < 0 && n * uint64_t(s->scan_kb) <= 400000;
+}
+
 // Launches [lo, hi) in blocks of kBlockSeqs indices.  Per-index outputs are
 // offset by the block's position (plain and sampled modes); the designability
 // counters accumulate.
@@ -402,6 +416,8 @@ hp_status run_blocks(const hp_structs *s, const void *d_ws, int form, uint64_t l
             return fail(HP_EUNSUPPORTED, "the blocked form needs N >= 8, per-block bytes "
                                          "within int8 and, with unary rows, depth <= 256");
     }
+    const bool scan = s->scan_kb > 0 && (form == HP_FORM_GEMM_I8 ? !gemm_shape_chosen(int(s->K_pad / 32))
+                                                                 : blocked_small(s, hi_all - lo_all));
     for (uint64_t lo = lo_all; lo < hi_all;) {
         const uint64_t hi = hi_all - lo > kBlockSeqs ? lo + kBlockSeqs : hi_all;
         const uint64_t off = lo - lo_all;
@@ -415,6 +431,7 @@ hp_status run_blocks(const hp_structs *s, const void *d_ws, int form, uint64_t l
         j.gap = o.gap && local ? o.gap + off : o.gap;
         j.seqs = o.seqs ? o.seqs + off : nullptr;
         hipError_t e = form == HP_FORM_POPCOUNT ? launch_popcount(j, hs)
+                       : scan ? launch_scan(j, hs)
                        : form == HP_FORM_BLOCKED_I8 ? launch_gemm_blocked(j, blocked_selected_nw(), blocked_selected_mode(), hs)
                                                     : var->launch(j, hs);
         if (e != hipSuccess)

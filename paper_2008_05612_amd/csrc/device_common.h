@@ -20,7 +20,9 @@
 namespace hpmap {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v16i __attribute__((ext_vector_type(16)));
+typedef float v16f __attribute__((ext_vector_type(16)));
 
 // Median of three, written as max(min(a, b), min(max(a, b), c)), which the
 // backend selects as one v_med3_i32.  No inline assembly here: the compiler
@@ -62,6 +64,95 @@ __device__ __forceinline__ int window_to_global(int k, int conf_base, int win_sh
 {
     const int g = ((k >> win_shift) << kKeyConfBits) | (conf_base + (k & ((1 << win_shift) - 1)));
     return k == 0 ? 0 : g;
+}
+
+// Eight bits spread to the nibbles of a word: FP4 code 1 (0.5) each.
+__device__ __forceinline__ uint32_t fp4_spread(uint32_t b)
+{
+    b = (b | (b << 12)) & 0x000f000fu;
+    b = (b | (b << 6)) & 0x03030303u;
+    return (b | (b << 3)) & 0x11111111u;
+}
+
+// 32 product rows from row `start`, as bits: row k is the pair (i, i + d) of
+// the k-th odd separation d >= 3 in (d, i) order, and its bit is X_i Y_j or Y_i
+// X_j.  A run of separation d is one word, X & (Y >> d) | Y & (X >> d); the 32
+// bits are gathered from the runs that overlap them.
+__device__ __forceinline__ uint32_t pair_bits(uint64_t X, uint64_t Y, int N, int start)
+{
+    uint32_t bits = 0;
+    int s = -start;   // where the run of separation d starts in the word
+    for (int d = 3; d < N; d += 2) {
+        const uint64_t run = (X & (Y >> d)) | (Y & (X >> d));
+        const int len = N - d;
+        if (s < 32 && s + len > 0)
+            bits |= s >= 0 ? uint32_t(run) << s : uint32_t(run >> -s);
+        s += len;
+    }
+    return bits;
+}
+
+// ---- threshold scans ---------------------------------------------------
+// Keys of the scan's two best: (n << 17) | (row << 12) | (tile + 1), the
+// conformation 32 tile + row at count n (tiles fit: kScanMaxTiles); 0 is "no
+// conformation".
+// The same key with the conformation's number in its low bits, as
+// finish_sequence reads it.
+__device__ __forceinline__ int scan_global(int k)
+{
+    const int conf = ((k & 0xfff) - 1) * kTileConf + ((k >> 12) & 31);
+    return k ? (k & ~int(kMaxConf)) | (conf + 1) : 0;
+}
+
+// OR of a lane's 16 accumulators (8 v_or3).
+__device__ __forceinline__ int or16(const v16i &a)
+{
+    int o = a[0];
+#pragma unroll
+    for (int r = 1; r < 15; r += 2)
+        o = o | a[r] | a[r + 1];
+    return o | a[15];
+}
+
+// The two largest of a lane's 16 accumulators by one field, unsigned, as
+// (field << 26) | row: shifting the accumulator left by 26 keeps the lower
+// field alone, by 20 the upper one above the lower (whose bits only break
+// ties).  One shift-or per register and, per two registers, v_max3, v_med3
+// and half of a v_max3; the median is written as the instruction, which the
+// compiler does not find beside the maximum of the same values (its inputs are
+// results of vector instructions, not of the matrix product).
+template <int SHIFT>
+__device__ __forceinline__ void scan_best(const v16i &a, unsigned &b, unsigned &s)
+{
+    b = s = 0;
+#pragma unroll
+    for (int q = 0; q < 16; q += 4) {
+        unsigned m[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            // row of register q in this lane: 8 (q / 4) + 4 half + q % 4
+            const unsigned k0 = (unsigned(a[q + 2 * p]) << SHIFT) | unsigned(2 * q + 2 * p);
+            const unsigned k1 = (unsigned(a[q + 2 * p + 1]) << SHIFT) | unsigned(2 * q + 2 * p + 1);
+            asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m[p]) : "v"(b), "v"(k0), "v"(k1));
+            b = max(max(b, k0), k1);
+        }
+        s = max(max(s, m[0]), m[1]);
+    }
+}
+
+// The two best keys of a column, shared by the waves that score it: keys are
+// distinct, so every key that does not stay best is pushed to the second
+// place, and the pair ends as the two largest whatever the order.
+struct ScanTop2 {
+    unsigned b, s;
+};
+
+// Pushes a lane's two candidates (0: none) for one column.
+__device__ __forceinline__ void scan_push(ScanTop2 *g, unsigned b, unsigned s)
+{
+    const unsigned old = atomicMax(&g->b, b);
+    atomicMax(&g->s, min(old, b));
+    atomicMax(&g->s, s);
 }
 
 // Bits 0 .. n-1 of x reversed (n <= 32).

@@ -34,6 +34,8 @@
 // update as the dense form, which now bounds the kernel.
 #pragma once
 
+#include <type_traits>
+
 #include "gemm_body.h"
 
 namespace hpmap {
@@ -476,11 +478,11 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_blk_batch(BatchHeader *hdr, in
 //   0  plain ranges, 1024 sequences (the low 10 monomers), 2 waves;
 //   1  reversal-canonical blocks, 1024 sequences (the 10 around the middle),
 //      2 waves;
-//   2  plain ranges cut at multiples of 2^17, 2048 sequences (monomers 0 .. 4
+//   2  whole chunks of 2^17 of a plain range, 2048 sequences (monomers 0 .. 4
 //      and the even ones 6 .. 16: equal parity never touches, so 11 varying
 //      monomers have only 14 pairs), 4 waves;
-//   3  plain ranges cut at multiples of 2^19, 4096 sequences (monomers 0 .. 4
-//      and the even ones 6 .. 18: 16 pairs), 8 waves.
+//   3  whole chunks of 2^19, 4096 sequences (monomers 0 .. 4 and the even ones
+//      6 .. 18: 16 pairs), 8 waves.
 //
 // The second product is a threshold scan.  Counts of H-H contacts are at
 // most 31 (kScanMaxContacts), so one int32 accumulator holds two sequences:
@@ -500,14 +502,11 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_blk_batch(BatchHeader *hdr, in
 // conformation the second key names may differ; it is never reported).
 // Simulated on sampled 3x3x3 blocks, 8 % of a wave's tiles hold a hit.
 //
-// The first product runs in FP4 (0/1 weights times the 0/1 contact matrix,
+// The first product runs in FP4 (0/1 weights times 0/1 contacts,
 // depth 64 per MFMA in the time an int8 product of depth 32 takes, exact in
 // the float accumulator), which halves its matrix time and the bytes of the
 // contact matrix that every workgroup reads.
 // ---------------------------------------------------------------------------
-
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 
 // bits 5 and 11 of an accumulator: the count of either sequence reaches its
 // threshold
@@ -553,23 +552,11 @@ __device__ __forceinline__ int wide_pair(const EnumJob &j, int p)
     return int((w >> (8 * (p & 7))) & 0xffu);
 }
 
-// Eight bits spread to the nibbles of a word as FP4 ones (code 2).
-__device__ __forceinline__ uint32_t fp4_ones(uint32_t b)
-{
-    b = (b | (b << 12)) & 0x000f000fu;
-    b = (b | (b << 6)) & 0x03030303u;
-    b = (b | (b << 3)) & 0x11111111u;
-    return b << 1;
-}
-
 // First-product A operand of a wide block, step `st` of this lane: virtual
-// row m over product rows k = 64 st + 32 half + n, n < 32, row k being the
-// pair (i, i + d) of the k-th odd separation d >= 3 in (d, i) order.  Every
-// row is a symmetric function of two monomer sets, bit (i, j) = X_i Y_j or
-// Y_i X_j: the block term has X = Y = the outer H monomers, a weight X = its
-// monomer and Y = the outer H monomers, a varying pair one monomer each.  So
-// a run of separation d is one word, X & (Y >> d) | Y & (X >> d), and the 32
-// bits of a step are gathered from the runs that overlap it.
+// row m over product rows k = 64 st + 32 half + n, n < 32.  Every row is a
+// symmetric function of two monomer sets, bit (i, j) = X_i Y_j or Y_i X_j: the
+// block term has X = Y = the outer H monomers, a weight X = its monomer and Y
+// = the outer H monomers, a varying pair one monomer each.
 template <int G>
 __device__ __forceinline__ v4i wide_v_fragment(const EnumJob &j, uint64_t outer, int m, int half,
                                                int st)
@@ -586,18 +573,10 @@ __device__ __forceinline__ v4i wide_v_fragment(const EnumJob &j, uint64_t outer,
         X = uint64_t(1) << wide_pos<G>(j, pr & 15);
         Y = uint64_t(1) << wide_pos<G>(j, pr >> 4);
     }
-    const int N = j.N;
-    uint32_t bits = 0;
-    int s = -(64 * st + 32 * half);   // where the run of separation d starts in the step
-    for (int d = 3; d < N; d += 2) {
-        const uint64_t run = (X & (Y >> d)) | (Y & (X >> d));
-        const int len = N - d;
-        if (s < 32 && s + len > 0)
-            bits |= s >= 0 ? uint32_t(run) << s : uint32_t(run >> -s);
-        s += len;
-    }
-    return v4i{int(fp4_ones(bits & 0xffu)), int(fp4_ones((bits >> 8) & 0xffu)),
-               int(fp4_ones((bits >> 16) & 0xffu)), int(fp4_ones(bits >> 24))};
+    const uint32_t bits = pair_bits(X, Y, j.N, 64 * st + 32 * half);
+    // twice the spread: weights 2.0 (the contact matrix holds 0.5)
+    return v4i{int(fp4_spread(bits & 0xffu) << 2), int(fp4_spread((bits >> 8) & 0xffu) << 2),
+               int(fp4_spread((bits >> 16) & 0xffu) << 2), int(fp4_spread(bits >> 24) << 2)};
 }
 
 // Canonical wide block index t -> outer bits, as blk_canonical_outer with 10
@@ -639,57 +618,18 @@ __device__ __forceinline__ uint64_t wide_chunk_outer(uint64_t t)
     return o;
 }
 
-// Keys of the scan's two best: (n << 17) | (row << 12) | (tile + 1), the
-// conformation 32 tile + row at count n (tiles fit: kScanMaxTiles); 0 is "no
-// conformation".  V = 32 - T of a sequence whose second-best key is gs: T is
-// one more than that key's count, 0 while it is "no conformation".
-__device__ __forceinline__ int scan_bias(int gs)
+// V = 32 - T of a sequence whose second-best scan key is gs: T is one more
+// than that key's count, 0 while it is "no conformation".
+__device__ __forceinline__ int scan_bias(unsigned gs)
 {
-    return 32 - int((unsigned(gs) + kMaxConf) >> kKeyConfBits);
+    return 32 - int((gs + kMaxConf) >> kKeyConfBits);
 }
 
-// The same key with the conformation's number in its low bits, as
-// finish_sequence reads it.
-__device__ __forceinline__ int scan_global(int k)
+// The two V bytes of a lane pair's sequences in the last word of the second
+// operand of its half-1 lane.
+__device__ __forceinline__ void scan_set_bias(v4i &sf, int lower, int upper, int half)
 {
-    const int conf = ((k & 0xfff) - 1) * kTileConf + ((k >> 12) & 31);
-    return k ? (k & ~int(kMaxConf)) | (conf + 1) : 0;
-}
-
-// OR of a lane's 16 accumulators (8 v_or3).
-__device__ __forceinline__ int or16(const v16i &a)
-{
-    int o = a[0];
-#pragma unroll
-    for (int r = 1; r < 15; r += 2)
-        o = o | a[r] | a[r + 1];
-    return o | a[15];
-}
-
-// The two largest of a lane's 16 accumulators by one field, unsigned, as
-// (field << 26) | row: shifting the accumulator left by 26 keeps the lower
-// field alone, by 20 the upper one above the lower (whose bits only break
-// ties).  One shift-or per register and, per two registers, v_max3, v_med3
-// and half of a v_max3; the median is written as the instruction, which the
-// compiler does not find beside the maximum of the same values (its inputs are
-// results of vector instructions, not of the matrix product).
-template <int SHIFT>
-__device__ __forceinline__ void scan_best(const v16i &a, unsigned &b, unsigned &s)
-{
-    b = s = 0;
-#pragma unroll
-    for (int q = 0; q < 16; q += 4) {
-        unsigned m[2];
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            // row of register q in this lane: 8 (q / 4) + 4 half + q % 4
-            const unsigned k0 = (unsigned(a[q + 2 * p]) << SHIFT) | unsigned(2 * q + 2 * p);
-            const unsigned k1 = (unsigned(a[q + 2 * p + 1]) << SHIFT) | unsigned(2 * q + 2 * p + 1);
-            asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m[p]) : "v"(b), "v"(k0), "v"(k1));
-            b = max(max(b, k0), k1);
-        }
-        s = max(max(s, m[0]), m[1]);
-    }
+    sf[3] = half ? (sf[3] & 0xffff) | (lower << 16) | (upper << 24) : sf[3];
 }
 
 // Absorbs the 32 conformations of tile `tile` into the two best of the
@@ -698,15 +638,23 @@ __device__ __forceinline__ void scan_best(const v16i &a, unsigned &b, unsigned &
 // lane holds the candidates of its own sequence (half 0 the lower field, half
 // 1 the upper) from both halves' rows, and the merge as keys into *g.  A
 // candidate below T, or of an empty column, merges as a key below the second
-// best and changes nothing.  The two V bytes sit in the last word of the
-// second operand of the half-1 lanes.
-__device__ __forceinline__ void scan_absorb(const v4i &a2, v4i &sf, int hit, int2 *g, int tile,
-                                            int half)
+// best and changes nothing.  SHARED: other waves score the same sequences, so
+// the product's V is read back from the operand and the merge is atomic.
+template <bool SHARED>
+__device__ __forceinline__ void scan_absorb(const v4i &a2, v4i &sf, int hit, ScanTop2 *g,
+                                            int tile, int half)
 {
     const v16i zero = {};
     const v16i a = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf, zero, 0, 0, 0);
-    int2 v = *g;
     unsigned b0 = 0, s0 = 0, b1 = 0, s1 = 0;
+    ScanTop2 v = SHARED ? ScanTop2{0, 0} : *g;
+    int bias;
+    if constexpr (SHARED) {
+        const auto w = __builtin_amdgcn_permlane32_swap(sf[3], sf[3], false, false);
+        bias = int((w[1] >> (half ? 24 : 16)) & 0xffu);
+    } else {
+        bias = scan_bias(v.s);
+    }
     if (__any((hit & 32) != 0))
         scan_best<26>(a, b0, s0);
     if (__any((hit & 2048) != 0))
@@ -714,17 +662,23 @@ __device__ __forceinline__ void scan_absorb(const v4i &a2, v4i &sf, int hit, int
     // (x, y) -> ([x of half 0 | y of half 0], [x of half 1 | y of half 1])
     const auto pb = __builtin_amdgcn_permlane32_swap(b0, b1, false, false);
     const auto ps = __builtin_amdgcn_permlane32_swap(s0, s1, false, false);
-    const int base = tile + 1 - (scan_bias(v.y) << kKeyConfBits);
+    const int base = tile + 1 - (bias << kKeyConfBits);
     auto key = [&](unsigned k, int more) {
         return int(((k >> 26) << kKeyConfBits) + ((k & 31) << 12)) + base + more;
     };
-    top2_merge(v.x, v.y, key(pb[0], 0), key(ps[0], 0));
-    top2_merge(v.x, v.y, key(pb[1], 4 << 12), key(ps[1], 4 << 12));
-    *g = v;
-    const int nb = scan_bias(v.y);
+    int best = int(v.b), second = int(v.s);
+    top2_merge(best, second, key(pb[0], 0), key(ps[0], 0));
+    top2_merge(best, second, key(pb[1], 4 << 12), key(ps[1], 4 << 12));
+    unsigned now = unsigned(second);
+    if constexpr (SHARED) {
+        scan_push(g, unsigned(best), unsigned(second));
+        now = g->s;
+    } else {
+        *g = ScanTop2{unsigned(best), unsigned(second)};
+    }
+    const int nb = scan_bias(now);
     const auto pv = __builtin_amdgcn_permlane32_swap(nb, nb, false, false);
-    const int word = int((pv[0] << 16) | (pv[1] << 24));
-    sf[3] = half ? (sf[3] & 0xffff) | word : sf[3];
+    scan_set_bias(sf, int(pv[0]), int(pv[1]), half);
 }
 
 // Second product of one conformation tile: the threshold scan of the wave's
@@ -733,9 +687,9 @@ __device__ __forceinline__ void scan_absorb(const v4i &a2, v4i &sf, int hit, int
 // (forced with sched_group_barrier), when the matrix pipe is more often free.
 // Measured alone, an int8 product takes 34 SIMD cycles, and with n vector
 // instructions beside it 12 + 4.2 n where that is more: 44 for the 8 v_or3.
-template <int NA>
-__device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], int2 *g, int tile,
-                                          int half)
+template <int NA, bool SHARED>
+__device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], ScanTop2 *g,
+                                          int tile, int half)
 {
     const v16i zero = {};
     v16i acc[NA];
@@ -759,35 +713,48 @@ __device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], i
 #pragma unroll
         for (int t = 0; t < kBlkTiles; ++t)
             if (__any((hit[t] & kScanHit) != 0))
-                scan_absorb(a2, sf[t], hit[t], g + t * 64, tile, half);
+                scan_absorb<SHARED>(a2, sf[t], hit[t], g + t * 64, tile, half);
     }
 }
 
-// The work of one workgroup: wave w of NW = wide_waves<G>() scores the 512
-// sequences x = 512 w + 64 t + lane (t = 0 .. 7) of block `blk` (plain 10:
-// sequence >> 10; canonical: canonical block index; chunked: chunk and the
-// outer bits within it).  vlds holds the block's first-product fragments, a2s
-// the packed first products of two groups of NW tiles ([2][NW][64]), gbs
-// every sequence's two best keys ([NW][8][64]).
-template <int KB, int G>
-__device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, v4i *vlds, v4i *a2s,
-                                          int2 *gbs)
+// The work of one workgroup: B blocks from `blk` on (plain 10: sequence >> 10;
+// canonical: canonical block index; chunked: chunk and the outer bits within
+// it), each scored by S groups of NW = wide_waves<G>() waves.  Wave w of a
+// group scores the 512 sequences x = 512 w + 64 t + lane (t = 0 .. 7) of its
+// block against every S-th group of NW conformation tiles.  vlds holds each
+// block's first-product fragments, a2s each group's packed first products of
+// two groups of tiles, gbs every sequence's two best keys.
+template <int KB, int G, int S = 1, int B = 1>
+struct WideShared {
+    static constexpr int NW = wide_waves<G>();
+    v4i vlds[B][wide_steps<KB>() * 64];
+    v4i a2s[B * S][2][NW][64];
+    ScanTop2 gbs[B][NW][kBlkTiles * 64];
+};
+
+template <int KB, int G, int S, int B>
+__device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideShared<KB, G, S, B> &sh)
 {
     constexpr int NW = wide_waves<G>();
     constexpr int KS = wide_steps<KB>();
-    // deep products leave registers for two accumulators (four waves per SIMD)
-    constexpr int kAcc = KS <= 3 ? 3 : 2;
+    // deep products and shared keys leave registers for two accumulators
+    // (four waves per SIMD)
+    constexpr int kAcc = KS <= 3 && S == 1 ? 3 : 2;
+    const int lane = threadIdx.x & 63;
+    const int half = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = w % NW, sp = w / NW % S, bk = w / (NW * S);
+    blk += bk;
+    v4i *const vlds = sh.vlds[bk];
+    auto &a2s = sh.a2s[bk * S + sp];
     bool diag = false;
     const uint64_t outer = G == 1   ? wide_canonical_outer(j, blk, &diag)
                            : G >= 2 ? wide_chunk_outer<G>(blk)
                                     : blk << kWideBits;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int half = lane >> 5;
-    const v4i *__restrict__ C1 = reinterpret_cast<const v4i *>(j.wide_c1);
+    const v4i *__restrict__ C1 = reinterpret_cast<const v4i *>(j.scan_c1);
 
     // the waves build the block's fragments, one step at a time
-    for (int st = wave; st < KS; st += NW)
+    for (int st = w % (NW * S); st < KS; st += NW * S)
         vlds[st * 64 + lane] = wide_v_fragment<G>(j, outer, lane & 31, half, st);
     v4i sf[kBlkTiles];
     const v4i *__restrict__ S2 = reinterpret_cast<const v4i *>(j.wide_s2) +
@@ -801,11 +768,13 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, v4i *v
     // also wait for the contact-tile loads issued one group ahead.
     __builtin_amdgcn_s_waitcnt(0x0f70);
 
-    // this lane's two best (global keys) per sequence tile, in LDS
-    int2 *const top2 = gbs + wave * (kBlkTiles * 64) + lane;
+    // this lane's two best (keys) per sequence tile, in LDS
+    ScanTop2 *const top2 = sh.gbs[bk][wave] + lane;
+    if (sp == 0) {
 #pragma unroll
-    for (int t = 0; t < kBlkTiles; ++t)
-        top2[t * 64] = int2{0, 0};
+        for (int t = 0; t < kBlkTiles; ++t)
+            top2[t * 64] = ScanTop2{0, 0};
+    }
 
     const int n_tiles = j.n_tiles;
     const int n_conf = j.n_conf;
@@ -836,62 +805,80 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, v4i *v
         const int ones = half && tile * kTileConf + (lane & 31) < n_conf ? 0x40010000 : 0;
         v4i p;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
+        for (int q4 = 0; q4 < 4; ++q4) {
             uint32_t x = 0;
 #pragma unroll
             for (int b = 0; b < 4; ++b)
-                x = __builtin_amdgcn_cvt_pk_u8_f32(d1[4 * w + b], b, x);
-            p[w] = int(x);
+                x = __builtin_amdgcn_cvt_pk_u8_f32(d1[4 * q4 + b], b, x);
+            p[q4] = int(x);
         }
         p[3] |= ones;   // rows 30 and 31 of the product are 0
-        a2s[(buf * NW + wave) * 64 + lane] = p;
+        a2s[buf][wave][lane] = p;
     };
 
+    // first tile of this group's g-th group of tiles
+    auto tile0 = [&](int g) { return (g * S + sp) * NW; };
+    const int n_groups = (n_tiles + NW * S - 1) / (NW * S);
     v4i c1[KS];
     __syncthreads();   // vlds
-    if (wave < n_tiles) {
-        load_c1(wave, c1);
-        first(c1, wave, 0);
+    if (tile0(0) + wave < n_tiles) {
+        load_c1(tile0(0) + wave, c1);
+        first(c1, tile0(0) + wave, 0);
     }
-    if (NW + wave < n_tiles)
-        load_c1(NW + wave, c1);
+    if (tile0(1) + wave < n_tiles)
+        load_c1(tile0(1) + wave, c1);
     __syncthreads();
     // The packed first product of the next tile is read from LDS one tile
     // ahead, so no tile starts by waiting for it.  The group's barrier sits
     // before its last tile: by then every wave has read all of this group's
     // buffer and written its first product of the next group, so the next
     // group's first tile can be read ahead as well.
-    v4i a2n = a2s[lane];
-    for (int g = 0; g * NW < n_tiles; ++g) {
+    v4i a2n = a2s[0][0][lane];
+    for (int g = 0; g < n_groups; ++g) {
         const int buf = g & 1;
-        const int nt = (g + 1) * NW + wave;   // this wave's tile of the next group
+        const int nt = tile0(g + 1) + wave;   // this wave's tile of the next group
+        if constexpr (S > 1) {
+            // thresholds raised by the waves that share the sequences: after
+            // every group while they rise fast, then every 8 tiles
+            constexpr int kEvery = NW >= 8 ? 1 : 8 / NW;
+            if (g > 0 && (g <= 8 || g % kEvery == 0)) {
+#pragma unroll
+                for (int t = 0; t < kBlkTiles; ++t) {
+                    const ScanTop2 *const c = sh.gbs[bk][wave] + t * 64 + (lane & 31);
+                    scan_set_bias(sf[t], scan_bias(c[0].s), scan_bias(c[32].s), half);
+                }
+            }
+        }
 #pragma unroll 1
         for (int tt = 0; tt < NW; ++tt) {
-            const int tile = g * NW + tt;
+            const int tile = tile0(g) + tt;
             const v4i a2 = a2n;
             if (tt + 1 < NW) {
-                a2n = a2s[(buf * NW + tt + 1) * 64 + lane];
+                a2n = a2s[buf][tt + 1][lane];
             } else {
                 // the next group's first products are visible, and this
                 // group's buffer is free for the group after it
                 __syncthreads();
-                a2n = a2s[((buf ^ 1) * NW) * 64 + lane];
+                a2n = a2s[buf ^ 1][0][lane];
             }
             if (tile < n_tiles)
-                scan_tile<kAcc>(a2, sf, top2, tile, half);
+                scan_tile<kAcc, (S > 1)>(a2, sf, top2, tile, half);
             if (tt == 0 && nt < n_tiles) {
                 first(c1, nt, buf ^ 1);
-                if (nt + NW < n_tiles)
-                    load_c1(nt + NW, c1);
+                const int n2 = tile0(g + 2) + wave;
+                if (n2 < n_tiles)
+                    load_c1(n2, c1);
             }
         }
     }
+    if constexpr (S > 1)
+        __syncthreads();   // every group's keys
 
     unsigned del = 0;
 #pragma unroll 1
-    for (int t = 0; t < kBlkTiles; ++t) {
-        const int2 k = top2[t * 64];
-        const int2 v = {scan_global(k.x), scan_global(k.y)};
+    for (int t = sp; t < kBlkTiles; t += S) {
+        const ScanTop2 k = top2[t * 64];
+        const int2 v = {scan_global(int(k.b)), scan_global(int(k.s))};
         const int x = wave * 512 + t * 64 + lane;
         if constexpr (G == 1) {
             // off the diagonal the block's reverse is never scored: write both;
@@ -916,53 +903,52 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, v4i *v
     count_deleterious(j, del, lane == 0);
 }
 
-template <int KB, bool CANON>
-__global__ __launch_bounds__(128, 4) void k_gemm_wide(EnumJob j)
+// Blocks of 1024, S groups of 2 waves on each: canonical blocks, and plain
+// ranges of few blocks, whose workgroups split the conformations so that they
+// still fill the compute units.
+template <int KB, bool CANON, int S>
+__global__ __launch_bounds__(128 * S, 4) void k_gemm_wide(EnumJob j)
 {
-    // first-product A operand of the block (the same for every wave), the
-    // packed first products of the current and the next group of tiles and
-    // every sequence's two best keys
-    constexpr int NW = wide_waves<0>();
-    __shared__ v4i vlds[wide_steps<KB>() * 64];
-    __shared__ v4i a2s[2 * NW * 64];
-    __shared__ int2 gbs[NW * kBlkTiles * 64];
-    wide_body<KB, CANON ? 1 : 0>(j, (CANON ? j.lo : j.lo >> kWideBits) + blockIdx.x, vlds, a2s,
-                                 gbs);
+    constexpr int G = CANON ? 1 : 0;
+    __shared__ WideShared<KB, G, S> sh;
+    wide_body<KB, G, S, 1>(j, (CANON ? j.lo : j.lo >> kWideBits) + blockIdx.x, sh);
 }
 
-// Plain ranges cut at multiples of 2^17: blocks of 2048 sequences, 4 waves.
+// A plain range in the largest blocks it holds: workgroups of 8 waves score
+// one block of 4096 (the first c.n3), two of 2048 (the next c.n2 / 2) or four
+// of 1024 sequences.  Smaller blocks lie on both sides of larger ones: block i
+// of a size is block lo + i before the gap, and after it i continues at hi.
 template <int KB>
-__global__ __launch_bounds__(256, 4) void k_gemm_wide_w4(EnumJob j)
+__global__ __launch_bounds__(512, 4) void k_gemm_wide_w8(EnumJob j, WideCut c)
 {
-    constexpr int NW = wide_waves<2>();
-    __shared__ v4i vlds[wide_steps<KB>() * 64];
-    __shared__ v4i a2s[2 * NW * 64];
-    __shared__ int2 gbs[NW * kBlkTiles * 64];
-    wide_body<KB, 2>(j, ((j.lo >> kWide11ChunkBits) << 6) + blockIdx.x, vlds, a2s, gbs);
-}
-
-// Plain ranges cut at multiples of 2^19: blocks of 4096 sequences, 8 waves.
-template <int KB>
-__global__ __launch_bounds__(512, 4) void k_gemm_wide_w8(EnumJob j)
-{
-    constexpr int NW = wide_waves<3>();
-    __shared__ v4i vlds[wide_steps<KB>() * 64];
-    __shared__ v4i a2s[2 * NW * 64];
-    __shared__ int2 gbs[NW * kBlkTiles * 64];
-    wide_body<KB, 3>(j, ((j.lo >> kWide12ChunkBits) << 7) + blockIdx.x, vlds, a2s, gbs);
+    __shared__ union {
+        WideShared<KB, 3> b4096;
+        WideShared<KB, 2, 1, 2> b2048;
+        WideShared<KB, 0, 1, 4> b1024;
+    } sh;
+    const unsigned wg = blockIdx.x;
+    if (wg < c.n3) {
+        wide_body<KB, 3, 1, 1>(j, c.lo3 + wg, sh.b4096);
+    } else if (wg < c.n3 + c.n2 / 2) {
+        const unsigned i = 2 * (wg - c.n3);
+        wide_body<KB, 2, 1, 2>(j, i < c.n2_lo ? c.lo2 + i : c.hi2 + (i - c.n2_lo), sh.b2048);
+    } else {
+        // four consecutive blocks may reach over the gap: their waves differ
+        const unsigned i = 4 * (wg - c.n3 - c.n2 / 2);
+        const unsigned bk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7), b = i + bk;
+        const uint64_t blk = b < c.n1_lo ? c.lo1 + b : c.hi1 + (b - c.n1_lo);
+        wide_body<KB, 0, 1, 4>(j, blk - bk, sh.b1024);
+    }
 }
 
 // Batched wide blocks for jobs of one product depth and geometry G (0, 2 or
 // 3): workgroup b scores the wide block of item item_lo + b, in the job whose
-// item range holds it.
-template <int KB, int G>
-__global__ __launch_bounds__(64 * wide_waves<G>(), 4) void k_gemm_wide_batch(BatchHeader *hdr,
-                                                                             int item_lo)
+// item range holds it, S groups of waves splitting the conformations.
+template <int KB, int G, int S>
+__global__ __launch_bounds__(64 * S * wide_waves<G>(), 4) void k_gemm_wide_batch(BatchHeader *hdr,
+                                                                                 int item_lo)
 {
-    constexpr int NW = wide_waves<G>();
-    __shared__ v4i vlds[wide_steps<KB>() * 64];
-    __shared__ v4i a2s[2 * NW * 64];
-    __shared__ int2 gbs[NW * kBlkTiles * 64];
+    __shared__ WideShared<KB, G, S> sh;
     const EnumJob *jobs = reinterpret_cast<const EnumJob *>(hdr + 1);
     const int njobs = hdr->njobs;
     const int64_t *start = reinterpret_cast<const int64_t *>(jobs + njobs);
@@ -980,14 +966,40 @@ __global__ __launch_bounds__(64 * wide_waves<G>(), 4) void k_gemm_wide_batch(Bat
     const uint64_t blk0 = G == 3   ? (j.lo >> kWide12ChunkBits) << 7
                           : G == 2 ? (j.lo >> kWide11ChunkBits) << 6
                                    : j.lo >> kWideBits;
-    wide_body<KB, G>(j, blk0 + uint64_t(it - start[lo]), vlds, a2s, gbs);
+    wide_body<KB, G, S, 1>(j, blk0 + uint64_t(it - start[lo]), sh);
+}
+
+// Groups of waves per block for a launch of n blocks of `waves` waves each: as
+// many as bring it to 4096 waves (16 per compute unit), at most 16 waves per
+// workgroup.  A sweep over all conformations takes a wave 1.8 ms on 3x3x3
+// however few they are; 2^17 sequences take 0.63 ms split eight ways.
+inline int wide_split(uint64_t n, int waves)
+{
+    int s = 1;
+    while (2 * s * waves <= 16 && 2 * s * waves * n <= 4096)
+        s *= 2;
+    return s;
 }
 
 template <int KB, int G>
 hipError_t launch_wide_batch_g(BatchHeader *hdr, int item_lo, unsigned grid, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_gemm_wide_batch<KB, G>), dim3(grid), dim3(64 * wide_waves<G>()), 0, st,
-                       hdr, item_lo);
+    constexpr int NW = wide_waves<G>();
+    const int s = wide_split(grid, NW);
+    auto go = [&](auto split) {
+        constexpr int S = decltype(split)::value;
+        if constexpr (S * NW <= 16)
+            hipLaunchKernelGGL((k_gemm_wide_batch<KB, G, S>), dim3(grid), dim3(64 * S * NW), 0, st,
+                               hdr, item_lo);
+    };
+    if (s == 8)
+        go(std::integral_constant<int, 8>{});
+    else if (s == 4)
+        go(std::integral_constant<int, 4>{});
+    else if (s == 2)
+        go(std::integral_constant<int, 2>{});
+    else
+        go(std::integral_constant<int, 1>{});
     return hipGetLastError();
 }
 
@@ -1001,22 +1013,34 @@ hipError_t launch_wide_batch(BatchHeader *hdr, int item_lo, unsigned grid, int w
                        : launch_wide_batch_g<KB, 0>(hdr, item_lo, grid, st);
 }
 
+template <int KB, bool CANON>
+hipError_t launch_wide_small(const EnumJob &j, uint64_t n, hipStream_t st)
+{
+    const dim3 grid = dim3(unsigned(n));
+    switch (wide_split(n, wide_waves<0>())) {
+    case 8: hipLaunchKernelGGL((k_gemm_wide<KB, CANON, 8>), grid, dim3(1024), 0, st, j); break;
+    case 4: hipLaunchKernelGGL((k_gemm_wide<KB, CANON, 4>), grid, dim3(512), 0, st, j); break;
+    case 2: hipLaunchKernelGGL((k_gemm_wide<KB, CANON, 2>), grid, dim3(256), 0, st, j); break;
+    default: hipLaunchKernelGGL((k_gemm_wide<KB, CANON, 1>), grid, dim3(128), 0, st, j); break;
+    }
+    return hipGetLastError();
+}
+
+// Plain ranges: with `chunked`, launches of more than 2048 blocks of 1024 (4096
+// waves, 16 per compute unit) take the largest blocks the range holds; fewer
+// (or without) take blocks of 1024, which spread more evenly: 2^20 sequences of
+// 3x3x3 2.2 ms (3.5 ms in the largest blocks, one workgroup per compute unit).
 template <int KB>
 hipError_t launch_wide(const EnumJob &j, bool chunked, hipStream_t st)
 {
-    if (j.mode == kSeqCanonical) {
-        hipLaunchKernelGGL((k_gemm_wide<KB, true>), dim3(unsigned(j.hi - j.lo)),
-                           dim3(64 * wide_waves<1>()), 0, st, j);
-        return hipGetLastError();
-    }
-    const int kind = wide_kind(j.N, j.lo, j.hi, chunked);
-    const dim3 grid(unsigned(wide_blocks(kind, j.lo, j.hi)));
-    if (kind == 3)
-        hipLaunchKernelGGL((k_gemm_wide_w8<KB>), grid, dim3(64 * wide_waves<3>()), 0, st, j);
-    else if (kind == 2)
-        hipLaunchKernelGGL((k_gemm_wide_w4<KB>), grid, dim3(64 * wide_waves<2>()), 0, st, j);
-    else
-        hipLaunchKernelGGL((k_gemm_wide<KB, false>), grid, dim3(64 * wide_waves<0>()), 0, st, j);
+    if (j.mode == kSeqCanonical)
+        return launch_wide_small<KB, true>(j, j.hi - j.lo, st);
+    const uint64_t n = wide_blocks(1, j.lo, j.hi);
+    if (!chunked || n <= 2048)
+        return launch_wide_small<KB, false>(j, n, st);
+    const WideCut c = wide_cut(j.N, j.lo, j.hi);
+    hipLaunchKernelGGL((k_gemm_wide_w8<KB>), dim3(c.n3 + c.n2 / 2 + (c.n1 + 3) / 4), dim3(512), 0, st,
+                       j, c);
     return hipGetLastError();
 }
 

@@ -72,6 +72,36 @@ uint64_t wide_blocks(int kind, uint64_t lo, uint64_t hi)
                        : ((hi - 1) >> kWideBits) - (lo >> kWideBits) + 1;
 }
 
+WideCut wide_cut(int N, uint64_t lo, uint64_t hi)
+{
+    // the whole chunks of 2^bits inside [a, b): empty ones at b
+    auto inner = [](uint64_t a, uint64_t b, int bits, bool use, uint64_t *ia, uint64_t *ib) {
+        const uint64_t m = (uint64_t(1) << bits) - 1;
+        *ia = (a + m) & ~m;
+        *ib = b & ~m;
+        if (!use || *ia >= *ib)
+            *ia = *ib = b;
+    };
+    WideCut c{};
+    uint64_t a2, b2, a3, b3;
+    inner(lo, hi, kWide11ChunkBits, N >= kWide11ChunkBits, &a2, &b2);
+    inner(a2, b2, kWide12ChunkBits, N >= kWide12ChunkBits, &a3, &b3);
+    c.n3 = uint32_t((b3 - a3) >> kWide12Bits);
+    c.lo3 = (a3 >> kWide12ChunkBits) << 7;
+    c.n2_lo = uint32_t((a3 - a2) >> kWide11Bits);
+    c.n2 = c.n2_lo + uint32_t((b2 - b3) >> kWide11Bits);
+    c.lo2 = (a2 >> kWide11ChunkBits) << 6;
+    c.hi2 = (b3 >> kWide11ChunkBits) << 6;
+    auto blocks = [](uint64_t a, uint64_t b) {
+        return a < b ? uint32_t(((b - 1) >> kWideBits) - (a >> kWideBits) + 1) : 0u;
+    };
+    c.n1_lo = blocks(lo, a2);
+    c.n1 = c.n1_lo + blocks(b2, hi);
+    c.lo1 = lo >> kWideBits;
+    c.hi1 = b2 >> kWideBits;
+    return c;
+}
+
 int blk_batch_kind(const hp_structs *s, uint64_t lo, uint64_t hi)
 {
     const int mode = blocked_selected_mode();

@@ -35,7 +35,10 @@ struct WsLayout {
     size_t gemm_a = 0;   // int8_t[n_tiles][K_pad/32][64 lanes][16]
     size_t gemm_b = 0;   // blocked form: int8_t[n_tiles][K_pad/32][64 lanes][16], or none
     size_t blk_s2 = 0;   // blocked form: int8_t[2 geometries][8 tiles][64 lanes][16], or none
-    size_t wide_c1 = 0;  // wide blocks: FP4 [n_tiles][ceil(K/64)][64 lanes][32 values], or none
+    size_t scan_c1 = 0;  // threshold scans: FP4 [n_tiles, even][ceil((K+3)/64)][64 lanes][32
+                         // values] (pure pair energies), or none
+    size_t scan_un = 0;  // FP4 [n_tiles][ceil((K+U+6)/64)][64 lanes][32 values] (two-letter
+                         // tables), or none
     size_t wide_s2 = 0;  // wide blocks: int8_t[2 + 2 + 4 + 8 waves][8 tiles][64 lanes][16]
                          // (geometries: plain 10, canonical 10, plain 11, plain 12), or none
     size_t total = 0;
@@ -75,7 +78,9 @@ struct hp_structs {
     std::vector<int8_t> gemm_b;       // blocked form: 0/1 contact matrix + window index rows
     std::vector<int8_t> blk_s2;       // blocked form: per-sequence operand of the second product
     bool wide_ok = false;             // wide blocks apply (pure pair energies, N >= 10)
-    std::vector<int8_t> wide_c1;      // wide blocks: 0/1 contact matrix in FP4
+    std::vector<int8_t> scan_c1;      // threshold scans: contact matrix in FP4, pure pair energies
+    std::vector<int8_t> scan_un;      // the same with unary rows, two-letter tables
+    int scan_kb = 0;                  // dense scan: products per chain, 0 where it does not apply
     std::vector<int8_t> wide_s2;      // wide blocks: per-sequence operand of the second product
     std::vector<uint8_t> pair_rows;   // K_pad * 4: (i, j, constant, 0) per product row
     hpmap::WsLayout ws;
@@ -105,6 +110,8 @@ constexpr int kWideWaveBits = 9;
 // The second product packs the contact counts of two sequences in one
 // accumulator, 6 bits each (no accepted box has more than 28 contacts).
 constexpr uint32_t kScanMaxContacts = 31;
+// Dense scan with unary rows: thresholds are formed from digits up to this.
+constexpr int64_t kScanMaxUnF = 742;
 constexpr uint32_t kScanMaxTiles = 4094;   // 12 bits of a scan key, and one more than the tile
 constexpr uint64_t kLow10Pairs0 = 0x5096857463524130ull;   // (0,3) (1,4) (2,5) (3,6) (4,7) (5,8) (6,9) (0,5)
 constexpr uint64_t kLow10Pairs1 = 0x9092817094837261ull;   // (1,6) (2,7) (3,8) (4,9) (0,7) (1,8) (2,9) (0,9)

@@ -43,7 +43,9 @@ struct EnumJob {
     int32_t blk_KB, blk_coefB, blk_ngroups;   // first-product depth / 32, m2 B, unary rows
     uint64_t blk_grp[3];                      // unary group of each outer monomer (4 bits)
     const int8_t *blk_s2;           // second-product operand of this geometry (8 x 64 x 16 B)
-    const int8_t *wide_c1;          // wide blocks: 0/1 contact matrix in FP4
+    const int8_t *scan_c1;          // threshold scans, pure pair energies: 0/1 contact matrix in FP4
+    const int8_t *scan_un;          // the same with unary rows (two-letter tables)
+    int32_t scan_kb;                // dense scan: products per chain, 0 where it does not apply
     const int8_t *wide_s2;          // wide blocks: second-product operand ((2 + 2 + 4 + 8) waves
                                     // x 8 x 64 x 16 B: plain 10, canonical 10, plain 11 and
                                     // plain 12 geometries), or null where they do not apply
@@ -84,6 +86,12 @@ int gemm_variants_kb11_12(const GemmVariant **out);
 const GemmVariant *gemm_selected_variant(int KB);
 
 hipError_t launch_popcount(const EnumJob &j, hipStream_t st);
+// Threshold scan of the dense form (gemm_scan.h), any sequences; j.scan_kb > 0.
+hipError_t launch_scan(const EnumJob &j, hipStream_t st);
+// Whether a tile shape other than the default was chosen for product depth KB
+// (hp_gemm_select, hp_autotune): the dense form then runs that shape, else
+// the threshold scan where it applies.
+bool gemm_shape_chosen(int KB);
 // Block-factorised int8 form over a plain range (pure pair energies); nw
 // waves per workgroup (2, 4 or 8), one 256-sequence block per wave; mode 0
 // stages contact tiles through double-buffered LDS, mode 1 through triple-
@@ -111,6 +119,15 @@ int blk_batch_kind(const hp_structs *s, uint64_t lo, uint64_t hi);
 int wide_kind(int N, uint64_t lo, uint64_t hi, bool chunked);
 // Blocks (workgroups) of a plain range in that geometry.
 uint64_t wide_blocks(int kind, uint64_t lo, uint64_t hi);
+// A plain range cut into blocks of 4096 in its whole chunks of 2^19, of 2048
+// in the whole chunks of 2^17 on both sides of those, and of 1024 in the
+// rest.  n3, n2, n1: blocks of each size; those of 2048 and 1024 start at block
+// lo2 / lo1 (n2_lo / n1_lo of them) and go on after the gap at hi2 / hi1.
+struct WideCut {
+    uint64_t lo3, lo2, hi2, lo1, hi1;
+    uint32_t n3, n2, n2_lo, n1, n1_lo;
+};
+WideCut wide_cut(int N, uint64_t lo, uint64_t hi);
 hipError_t launch_gemm_blk_batch(void *d_batch_ws, int kb, bool unary, int wide, int item_lo,
                                  int item_hi, hipStream_t st);
 // Process-wide launch shape of the blocked form (runtime.cpp).

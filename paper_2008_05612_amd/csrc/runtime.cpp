@@ -26,12 +26,15 @@ namespace {
 struct Registry {
     std::vector<GemmVariant> by_kb[kMaxKB + 1];
     std::atomic<int> selected[kMaxKB + 1];
+    std::atomic<bool> chosen[kMaxKB + 1];   // not the default shape: runs instead of the scan
     std::once_flag cache_once;
 
     Registry()
     {
         for (auto &s : selected)
             s.store(0);
+        for (auto &c : chosen)
+            c.store(false);
         int (*groups[])(const GemmVariant **) = {gemm_variants_kb1_4, gemm_variants_kb5,
                                                  gemm_variants_kb6_10, gemm_variants_kb11_12};
         for (auto g : groups) {
@@ -76,7 +79,7 @@ void load_cache()
         if (KB < 1 || KB > kMaxKB)
             continue;
         const int idx = find_shape(KB, T, NW, mode);
-        if (idx >= 0)
+        if (idx >= 0)   // the best of the shapes; the scan still runs where it applies
             registry().selected[KB].store(idx);
     }
     std::fclose(f);
@@ -124,6 +127,15 @@ const GemmVariant *gemm_selected_variant(int KB)
     if (idx < 0 || idx >= int(v.size()))
         idx = 0;
     return &v[idx];
+}
+
+bool gemm_shape_chosen(int KB)
+{
+    if (KB < 1 || KB > kMaxKB)
+        return false;
+    Registry &r = registry();
+    std::call_once(r.cache_once, load_cache);
+    return r.chosen[KB].load();
 }
 
 namespace {
@@ -191,6 +203,7 @@ hp_status hp_gemm_select(uint32_t K_pad, int idx)
     Registry &r = registry();
     std::call_once(r.cache_once, load_cache);
     r.selected[K_pad / 32].store(idx);
+    r.chosen[K_pad / 32].store(idx != 0);
     return HP_OK;
 }
 
@@ -222,16 +235,20 @@ hp_status hp_autotune(const hp_structs *s, const void *d_ws, uint64_t seq_lo, ui
     if (err == hipSuccess)
         err = hipEventCreate(&e1);
     int best_idx = -1;
-    float best_ms = 0.f;
-    for (size_t i = 0; i < vars.size() && err == hipSuccess; ++i) {
+    float best_ms = 0.f, scan_ms = 0.f;
+    // the shapes, and last the threshold scan, which no shape replaces where
+    // it is faster
+    const size_t n_run = vars.size() + (s->scan_kb > 0 ? 1 : 0);
+    for (size_t i = 0; i < n_run && err == hipSuccess; ++i) {
         EnumJob j = make_enum_job(s, d_ws, seq_lo, seq_lo + n_seq, nullptr, nullptr, nullptr,
                                   nullptr);
-        err = vars[i].launch(j, st);   // warm-up (code load, caches)
+        const auto launch = i < vars.size() ? vars[i].launch : launch_scan;
+        err = launch(j, st);   // warm-up (code load, caches)
         if (err != hipSuccess)
             break;
         err = hipEventRecord(e0, st);
         for (int r = 0; r < repeats && err == hipSuccess; ++r)
-            err = vars[i].launch(j, st);
+            err = launch(j, st);
         if (err == hipSuccess)
             err = hipEventRecord(e1, st);
         if (err == hipSuccess)
@@ -240,6 +257,10 @@ hp_status hp_autotune(const hp_structs *s, const void *d_ws, uint64_t seq_lo, ui
         if (err == hipSuccess)
             err = hipEventElapsedTime(&t, e0, e1);
         t /= float(repeats);
+        if (i == vars.size()) {
+            scan_ms = t;
+            break;
+        }
         if (ms)
             ms[i] = t;
         if (err == hipSuccess && (best_idx < 0 || t < best_ms)) {
@@ -256,6 +277,7 @@ hp_status hp_autotune(const hp_structs *s, const void *d_ws, uint64_t seq_lo, ui
     Registry &r = registry();
     std::call_once(r.cache_once, load_cache);
     r.selected[KB].store(best_idx);
+    r.chosen[KB].store(best_idx != 0 && !(s->scan_kb > 0 && scan_ms <= best_ms));
     store_cache(KB, vars[best_idx]);
     if (best)
         *best = best_idx;

@@ -677,13 +677,67 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
         }
     }
 
+    // ---- threshold scans ------------------------------------------------------
+    // Contact matrix of the FP4 products, lane l of step st of a tile holding
+    // conformation l & 31 and rows 64 st + 32 (l / 32) + n, n = 0 .. 31, a
+    // nibble each (code 1 is 0.5, 2 1.0, 4 2.0, 5 3.0, 6 4.0, 7 6.0).
+    // Pure pair energies: contacts 0.5, and in the last 32-row block in use the
+    // threshold rows 29 .. 31 (6.0, 2.0, 0.5; gemm_scan.h); the dense scan
+    // reads tiles in pairs, so their number is made even, and an empty column
+    // keeps the first of these rows.  Two-letter tables: contacts 1.0, unary
+    // rows the contact count c_i, and in the last step the threshold rows 58 ..
+    // 63 (0.5, four 6.0, 1.0).
+    s->scan_c1.clear();
+    s->scan_un.clear();
+    s->scan_kb = 0;
+    if (n_tiles <= kScanMaxTiles && B == 0 && s->nbp <= kScanMaxContacts) {
+        s->scan_kb = int((s->K + 3 + 31) / 32);
+        const uint32_t steps = (s->K + 3 + 63) / 64, last = uint32_t(s->scan_kb) - 1;
+        const uint32_t tiles = (n_tiles + 1) & ~1u;
+        s->scan_c1.assign(size_t(tiles) * steps * 1024, 0);
+        auto set = [&](uint32_t c, uint32_t k, int code) {
+            const uint32_t lane = c % kTileConf + 32 * (k / 32 % 2), n = k % 32;
+            int8_t &b = s->scan_c1[((size_t(c / kTileConf) * steps + k / 64) * 64 + lane) * 16 + n / 2];
+            b = int8_t(b | (code << (4 * (n % 2))));
+        };
+        for (uint32_t c = 0; c < tiles * kTileConf; ++c) {
+            set(c, 32 * last + 29, 7);
+            if (c >= n_conf)
+                continue;
+            set(c, 32 * last + 30, 4);
+            set(c, 32 * last + 31, 1);
+            for (uint32_t q = 0; q < s->nbp; ++q)
+                set(c, uint32_t(pidx[size_t(s->contacts[(size_t(c) * s->nbp + q) * 2]) * N +
+                                     s->contacts[(size_t(c) * s->nbp + q) * 2 + 1]]), 1);
+        }
+    } else if (n_tiles <= kScanMaxTiles && B > 0 && A <= 15 && B <= 15 && cmax <= 4 &&
+               fmax <= kScanMaxUnF) {
+        s->scan_kb = int((s->K + s->U + 6 + 63) / 64);
+        const uint32_t steps = uint32_t(s->scan_kb);
+        s->scan_un.assign(size_t(n_tiles) * steps * 1024, 0);
+        auto set = [&](uint32_t c, uint32_t k, int code) {
+            const uint32_t lane = c % kTileConf + 32 * (k / 32 % 2), n = k % 32;
+            int8_t &b = s->scan_un[((size_t(c / kTileConf) * steps + k / 64) * 64 + lane) * 16 + n / 2];
+            b = int8_t(b | (code << (4 * (n % 2))));
+        };
+        static const int count_code[5] = {0, 2, 4, 5, 6};
+        static const int tail_code[6] = {1, 7, 7, 7, 7, 2};
+        for (uint32_t c = 0; c < n_conf; ++c) {
+            for (uint32_t q = 0; q < s->nbp; ++q)
+                set(c, uint32_t(pidx[size_t(s->contacts[(size_t(c) * s->nbp + q) * 2]) * N +
+                                     s->contacts[(size_t(c) * s->nbp + q) * 2 + 1]]), 2);
+            for (uint32_t i = 0; i < s->U; ++i)
+                set(c, s->K + i, count_code[deg[size_t(c) * N + i]]);
+            for (uint32_t r = 0; r < 6; ++r)
+                set(c, 64 * steps - 6 + r, tail_code[r]);
+        }
+    }
+
     // Wide blocks (pure pair energies), four geometries: plain (the low 10
     // monomers vary), reversal-canonical (the 10 around the middle), plain 11
     // (monomers 0 .. 4 and 6, 8, .., 16; N >= 17) and plain 12 (.., 18; N >=
-    // 19), see hp_internal.h.  The first product's contact matrix is 0/1 in
-    // FP4 (code 2 is 1.0), 64 product rows per step: lane l holds conformation
-    // l & 31 and rows 64 step + 32 (l / 32) + n, n = 0 .. 31, a nibble each.
-    // The virtual rows are m = 0 the block term, 1 .. nb the weight of varying
+    // 19), see hp_internal.h.  The first product reads the scan matrix; its
+    // virtual rows are m = 0 the block term, 1 .. nb the weight of varying
     // monomer m - 1, then the 16 varying pairs (kLow10Pairs, kMid10OddPairs for
     // odd N canonical, kW11Pairs, kW12Pairs), and 30 and 31 the constants 1 and
     // 64.  Lane l of tile t of wave w of the second operand holds the
@@ -692,7 +746,6 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
     // of x + 32, and V = 32 of either sequence (no threshold yet) for the
     // constants.
     s->wide_ok = false;
-    s->wide_c1.clear();
     s->wide_s2.clear();
     const int wodd = N & 1;
     const int whalf = N >= kWideBits ? (N - kWideBits - wodd) / 2 : 0;
@@ -728,21 +781,10 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
             }
         }
         s->wide_ok = int64_t(s->blk_coef) * maxw <= 128 && s->nbp <= kScanMaxContacts &&
-                     n_tiles <= kScanMaxTiles;
+                     s->scan_kb > 0 &&
+                     (s->K + 3 + 63) / 64 == (s->blk_KB + 1) / 2;
     }
     if (s->wide_ok) {
-        const uint32_t steps = (s->blk_KB + 1) / 2;
-        s->wide_c1.assign(size_t(n_tiles) * steps * 1024, 0);
-        for (uint32_t c = 0; c < n_conf; ++c)
-            for (uint32_t q = 0; q < s->nbp; ++q) {
-                const int i = s->contacts[(size_t(c) * s->nbp + q) * 2];
-                const int j = s->contacts[(size_t(c) * s->nbp + q) * 2 + 1];
-                const uint32_t k = uint32_t(pidx[size_t(i) * N + j]), n = k % 32;
-                const uint32_t lane = c % kTileConf + 32 * (k / 32 % 2);
-                int8_t &b = s->wide_c1[((size_t(c / kTileConf) * steps + k / 64) * 64 + lane) * 16 +
-                                       n / 2];
-                b = int8_t(b | (2 << (4 * (n % 2))));
-            }
         const int slots[5] = {0, 2, 4, 8, 16};   // first wave of each geometry
         s->wide_s2.assign(size_t(slots[n_geom]) * 8 * 64 * 16, 0);
         for (int g = 0; g < n_geom; ++g)
@@ -790,8 +832,9 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
     L.gemm_a = up(L.masks + s->masks.size() * 4);
     L.gemm_b = up(L.gemm_a + s->gemm_a.size());
     L.blk_s2 = up(L.gemm_b + s->gemm_b.size());
-    L.wide_c1 = up(L.blk_s2 + s->blk_s2.size());
-    L.wide_s2 = up(L.wide_c1 + s->wide_c1.size());
+    L.scan_c1 = up(L.blk_s2 + s->blk_s2.size());
+    L.scan_un = up(L.scan_c1 + s->scan_c1.size());
+    L.wide_s2 = up(L.scan_un + s->scan_un.size());
     L.total = up(L.wide_s2 + s->wide_s2.size());
     return HP_OK;
 }
