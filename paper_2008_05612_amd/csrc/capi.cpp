@@ -207,6 +207,7 @@ EnumJob make_enum_job(const hp_structs *s, const void *d_ws, uint64_t lo, uint64
     j.masks = reinterpret_cast<const uint32_t *>(base + s->ws.masks);
     j.gemm_a = reinterpret_cast<const int8_t *>(base + s->ws.gemm_a);
     j.gemm_b = reinterpret_cast<const int8_t *>(base + s->ws.gemm_b);
+    j.scan_c2q = reinterpret_cast<const uint16_t *>(base + s->ws.scan_c2q);
     j.scan_c1 = reinterpret_cast<const int8_t *>(base + s->ws.scan_c1);
     j.scan_un = reinterpret_cast<const int8_t *>(base + s->ws.scan_un);
     j.scan_kb = s->scan_kb;
@@ -225,6 +226,7 @@ EnumJob make_enum_job(const hp_structs *s, const void *d_ws, uint64_t lo, uint64
     j.W = int32_t(s->W);
     j.KB = int32_t(s->K_pad / 32);
     j.n_conf = int32_t(s->n_conf);
+    j.n_class = int32_t(s->n_class);
     j.n_tiles = int32_t((s->n_conf + kTileConf - 1) / kTileConf);
     j.U = int32_t(s->U);
     j.win_tiles = int32_t(s->win_tiles);
@@ -360,6 +362,7 @@ hp_status hp_upload(const hp_structs *s, void *d_ws, size_t ws_bytes, void *stre
         {s->ws.gemm_a, s->gemm_a.data(), s->gemm_a.size()},
         {s->ws.gemm_b, s->gemm_b.data(), s->gemm_b.size()},
         {s->ws.blk_s2, s->blk_s2.data(), s->blk_s2.size()},
+        {s->ws.scan_c2q, s->scan_c2q.data(), s->scan_c2q.size() * 2},
         {s->ws.scan_c1, s->scan_c1.data(), s->scan_c1.size()},
         {s->ws.scan_un, s->scan_un.data(), s->scan_un.size()},
         {s->ws.wide_s2, s->wide_s2.data(), s->wide_s2.size()},

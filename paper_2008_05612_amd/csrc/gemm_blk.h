@@ -34,6 +34,7 @@
 // update as the dense form, which now bounds the kernel.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 
 #include "gemm_body.h"
@@ -420,10 +421,10 @@ __device__ __forceinline__ void blk_body(const EnumJob &j, uint64_t blk0, v4i *l
             // a diagonal block holds each sequence and its reverse itself
             const uint64_t sq = blk_sequence(j, outer, t * 32 + col);
             const uint64_t rs = diag ? sq : __builtin_bitreverse64(sq) >> (64 - j.N);
-            del += finish_sequence(j, sq, sq, rs, half == 0 && blk < j.hi, gb[t], gs[t], 1);
+            del += finish_sequence(j, j.c2q, sq, sq, rs, half == 0 && blk < j.hi, gb[t], gs[t], 1);
         } else {
             const uint64_t idx = outer + uint64_t(t * 32 + col);
-            del += finish_sequence(j, idx, idx, idx, half == 0 && idx >= j.lo && idx < j.hi,
+            del += finish_sequence(j, j.c2q, idx, idx, idx, half == 0 && idx >= j.lo && idx < j.hi,
                                    gb[t], gs[t], 1);
         }
     }
@@ -632,53 +633,39 @@ __device__ __forceinline__ void scan_set_bias(v4i &sf, int lower, int upper, int
     sf[3] = half ? (sf[3] & 0xffff) | (lower << 16) | (upper << 24) : sf[3];
 }
 
-// Absorbs the 32 conformations of tile `tile` into the two best of the
-// column's sequences: the scan's product again, the two best rows of each
-// field that has a hit, an exchange between the lane halves after which a
-// lane holds the candidates of its own sequence (half 0 the lower field, half
-// 1 the upper) from both halves' rows, and the merge as keys into *g.  A
-// candidate below T, or of an empty column, merges as a key below the second
-// best and changes nothing.  SHARED: other waves score the same sequences, so
-// the product's V is read back from the operand and the merge is atomic.
-template <bool SHARED>
-__device__ __forceinline__ void scan_absorb(const v4i &a2, v4i &sf, int hit, ScanTop2 *g,
-                                            int tile, int half)
+// Absorbs the 32 conformations of tile `tile` into the two best of a tile's
+// sequences, top[col] and top[col + 32]: the scan's product again, and for each
+// field that has a hit the two best of the lane's 16 rows as keys, pushed with
+// LDS atomics (both lane halves, and in split blocks other waves, score the
+// same sequences).  The V that the product was formed with are the operand's
+// own bytes.  A candidate below T is pushed for nothing, one of an empty column
+// is none.
+__device__ __forceinline__ void scan_absorb(const v4i &a2, v4i &sf, int hit, ScanTop2 *top, int tile,
+                                            int lane)
 {
+    const int half = lane >> 5, col = lane & 31;
     const v16i zero = {};
     const v16i a = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf, zero, 0, 0, 0);
-    unsigned b0 = 0, s0 = 0, b1 = 0, s1 = 0;
-    ScanTop2 v = SHARED ? ScanTop2{0, 0} : *g;
-    int bias;
-    if constexpr (SHARED) {
-        const auto w = __builtin_amdgcn_permlane32_swap(sf[3], sf[3], false, false);
-        bias = int((w[1] >> (half ? 24 : 16)) & 0xffu);
-    } else {
-        bias = scan_bias(v.s);
-    }
-    if (__any((hit & 32) != 0))
-        scan_best<26>(a, b0, s0);
-    if (__any((hit & 2048) != 0))
-        scan_best<20>(a, b1, s1);
-    // (x, y) -> ([x of half 0 | y of half 0], [x of half 1 | y of half 1])
-    const auto pb = __builtin_amdgcn_permlane32_swap(b0, b1, false, false);
-    const auto ps = __builtin_amdgcn_permlane32_swap(s0, s1, false, false);
-    const int base = tile + 1 - (bias << kKeyConfBits);
-    auto key = [&](unsigned k, int more) {
-        return int(((k >> 26) << kKeyConfBits) + ((k & 31) << 12)) + base + more;
+    const auto w = __builtin_amdgcn_permlane32_swap(sf[3], sf[3], false, false);
+    const unsigned word = unsigned(w[1]);   // of the half-1 lane
+    const int at = tile + 1 + (half << 14);
+    auto push = [&](unsigned b, unsigned s, unsigned bias, ScanTop2 *g) {
+        const int base = at - int(bias << kKeyConfBits);
+        auto key = [&](unsigned k) {
+            return unsigned(max(0, int(((k >> 26) << kKeyConfBits) + ((k & 31) << 12)) + base));
+        };
+        scan_push(g, key(b), key(s));
     };
-    int best = int(v.b), second = int(v.s);
-    top2_merge(best, second, key(pb[0], 0), key(ps[0], 0));
-    top2_merge(best, second, key(pb[1], 4 << 12), key(ps[1], 4 << 12));
-    unsigned now = unsigned(second);
-    if constexpr (SHARED) {
-        scan_push(g, unsigned(best), unsigned(second));
-        now = g->s;
-    } else {
-        *g = ScanTop2{unsigned(best), unsigned(second)};
+    unsigned b, s;
+    if (__any((hit & 32) != 0)) {
+        scan_best<26>(a, b, s);
+        push(b, s, (word >> 16) & 0xffu, top + col);
     }
-    const int nb = scan_bias(now);
-    const auto pv = __builtin_amdgcn_permlane32_swap(nb, nb, false, false);
-    scan_set_bias(sf, int(pv[0]), int(pv[1]), half);
+    if (__any((hit & 2048) != 0)) {
+        scan_best<20>(a, b, s);
+        push(b, s, word >> 24, top + col + 32);
+    }
+    scan_set_bias(sf, scan_bias(top[col].s), scan_bias(top[col + 32].s), half);
 }
 
 // Second product of one conformation tile: the threshold scan of the wave's
@@ -687,9 +674,9 @@ __device__ __forceinline__ void scan_absorb(const v4i &a2, v4i &sf, int hit, Sca
 // (forced with sched_group_barrier), when the matrix pipe is more often free.
 // Measured alone, an int8 product takes 34 SIMD cycles, and with n vector
 // instructions beside it 12 + 4.2 n where that is more: 44 for the 8 v_or3.
-template <int NA, bool SHARED>
-__device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], ScanTop2 *g,
-                                          int tile, int half)
+template <int NA>
+__device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], ScanTop2 *top,
+                                          int tile, int lane)
 {
     const v16i zero = {};
     v16i acc[NA];
@@ -713,7 +700,7 @@ __device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], S
 #pragma unroll
         for (int t = 0; t < kBlkTiles; ++t)
             if (__any((hit[t] & kScanHit) != 0))
-                scan_absorb<SHARED>(a2, sf[t], hit[t], g + t * 64, tile, half);
+                scan_absorb(a2, sf[t], hit[t], top + t * 64, tile, lane);
     }
 }
 
@@ -730,16 +717,19 @@ struct WideShared {
     v4i vlds[B][wide_steps<KB>() * 64];
     v4i a2s[B * S][2][NW][64];
     ScanTop2 gbs[B][NW][kBlkTiles * 64];
+    unsigned del;
 };
 
-template <int KB, int G, int S, int B>
-__device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideShared<KB, G, S, B> &sh)
+// LOOP: called in a loop over blocks, which costs registers.
+template <int KB, int G, int S, int B, bool LOOP = false>
+__device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideShared<KB, G, S, B> &sh,
+                                          unsigned *hist = nullptr)
 {
     constexpr int NW = wide_waves<G>();
     constexpr int KS = wide_steps<KB>();
-    // deep products and shared keys leave registers for two accumulators
+    // deep products, shared keys and loops leave registers for two accumulators
     // (four waves per SIMD)
-    constexpr int kAcc = KS <= 3 && S == 1 ? 3 : 2;
+    constexpr int kAcc = KS <= 3 && S == 1 && !LOOP ? 3 : 2;
     const int lane = threadIdx.x & 63;
     const int half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -753,6 +743,8 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
                                     : blk << kWideBits;
     const v4i *__restrict__ C1 = reinterpret_cast<const v4i *>(j.scan_c1);
 
+    if (threadIdx.x == 0)
+        sh.del = 0;
     // the waves build the block's fragments, one step at a time
     for (int st = w % (NW * S); st < KS; st += NW * S)
         vlds[st * 64 + lane] = wide_v_fragment<G>(j, outer, lane & 31, half, st);
@@ -768,12 +760,12 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
     // also wait for the contact-tile loads issued one group ahead.
     __builtin_amdgcn_s_waitcnt(0x0f70);
 
-    // this lane's two best (keys) per sequence tile, in LDS
-    ScanTop2 *const top2 = sh.gbs[bk][wave] + lane;
+    // the two best keys of this wave's sequences, 64 per tile, in LDS
+    ScanTop2 *const top2 = sh.gbs[bk][wave];
     if (sp == 0) {
 #pragma unroll
         for (int t = 0; t < kBlkTiles; ++t)
-            top2[t * 64] = ScanTop2{0, 0};
+            top2[t * 64 + lane] = ScanTop2{0, 0};
     }
 
     const int n_tiles = j.n_tiles;
@@ -844,7 +836,7 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
             if (g > 0 && (g <= 8 || g % kEvery == 0)) {
 #pragma unroll
                 for (int t = 0; t < kBlkTiles; ++t) {
-                    const ScanTop2 *const c = sh.gbs[bk][wave] + t * 64 + (lane & 31);
+                    const ScanTop2 *const c = top2 + t * 64 + (lane & 31);
                     scan_set_bias(sf[t], scan_bias(c[0].s), scan_bias(c[32].s), half);
                 }
             }
@@ -862,7 +854,7 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
                 a2n = a2s[buf ^ 1][0][lane];
             }
             if (tile < n_tiles)
-                scan_tile<kAcc, (S > 1)>(a2, sf, top2, tile, half);
+                scan_tile<kAcc>(a2, sf, top2, tile, lane);
             if (tt == 0 && nt < n_tiles) {
                 first(c1, nt, buf ^ 1);
                 const int n2 = tile0(g + 2) + wave;
@@ -877,7 +869,7 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
     unsigned del = 0;
 #pragma unroll 1
     for (int t = sp; t < kBlkTiles; t += S) {
-        const ScanTop2 k = top2[t * 64];
+        const ScanTop2 k = top2[t * 64 + lane];
         const int2 v = {scan_global(int(k.b)), scan_global(int(k.s))};
         const int x = wave * 512 + t * 64 + lane;
         if constexpr (G == 1) {
@@ -888,19 +880,21 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
             for (int b = 0; b < kWideBits; ++b)
                 sq |= uint64_t((x >> b) & 1) << wide_pos<1>(j, b);
             const uint64_t rs = diag ? sq : __builtin_bitreverse64(sq) >> (64 - j.N);
-            del += finish_sequence(j, sq, sq, rs, blk < j.hi, v.x, v.y, j.A);
+            del += finish_sequence(j, j.scan_c2q, sq, sq, rs, blk < j.hi, v.x, v.y, j.A);
         } else if constexpr (G >= 2) {
             uint64_t sq = outer | uint64_t(x & 31);
 #pragma unroll
             for (int b = 5; b < wide_bits<G>(); ++b)
                 sq |= uint64_t((x >> b) & 1) << wide_pos<G>(j, b);
-            del += finish_sequence(j, sq, sq, sq, sq >= j.lo && sq < j.hi, v.x, v.y, j.A);
+            del += finish_sequence(j, j.scan_c2q, sq, sq, sq, sq >= j.lo && sq < j.hi, v.x, v.y,
+                                   j.A, hist);
         } else {
             const uint64_t idx = outer + uint64_t(x);
-            del += finish_sequence(j, idx, idx, idx, idx >= j.lo && idx < j.hi, v.x, v.y, j.A);
+            del += finish_sequence(j, j.scan_c2q, idx, idx, idx, idx >= j.lo && idx < j.hi, v.x,
+                                   v.y, j.A, hist);
         }
     }
-    count_deleterious(j, del, lane == 0);
+    count_deleterious_wg(j, del, &sh.del);
 }
 
 // Blocks of 1024, S groups of 2 waves on each: canonical blocks, and plain
@@ -914,31 +908,59 @@ __global__ __launch_bounds__(128 * S, 4) void k_gemm_wide(EnumJob j)
     wide_body<KB, G, S, 1>(j, (CANON ? j.lo : j.lo >> kWideBits) + blockIdx.x, sh);
 }
 
+template <int KB>
+union WidePlainShared {
+    WideShared<KB, 3> b4096;
+    WideShared<KB, 2, 1, 2> b2048;
+    WideShared<KB, 0, 1, 4> b1024;
+};
+
 // A plain range in the largest blocks it holds: workgroups of 8 waves score
 // one block of 4096 (the first c.n3), two of 2048 (the next c.n2 / 2) or four
 // of 1024 sequences.  Smaller blocks lie on both sides of larger ones: block i
 // of a size is block lo + i before the gap, and after it i continues at hi.
-template <int KB>
-__global__ __launch_bounds__(512, 4) void k_gemm_wide_w8(EnumJob j, WideCut c)
+template <int KB, bool LOOP>
+__device__ __forceinline__ void wide_plain(const EnumJob &j, const WideCut &c, unsigned wg,
+                                           WidePlainShared<KB> &sh, unsigned *hist)
 {
-    __shared__ union {
-        WideShared<KB, 3> b4096;
-        WideShared<KB, 2, 1, 2> b2048;
-        WideShared<KB, 0, 1, 4> b1024;
-    } sh;
-    const unsigned wg = blockIdx.x;
     if (wg < c.n3) {
-        wide_body<KB, 3, 1, 1>(j, c.lo3 + wg, sh.b4096);
+        wide_body<KB, 3, 1, 1, LOOP>(j, c.lo3 + wg, sh.b4096, hist);
     } else if (wg < c.n3 + c.n2 / 2) {
         const unsigned i = 2 * (wg - c.n3);
-        wide_body<KB, 2, 1, 2>(j, i < c.n2_lo ? c.lo2 + i : c.hi2 + (i - c.n2_lo), sh.b2048);
+        wide_body<KB, 2, 1, 2, LOOP>(j, i < c.n2_lo ? c.lo2 + i : c.hi2 + (i - c.n2_lo), sh.b2048,
+                                     hist);
     } else {
         // four consecutive blocks may reach over the gap: their waves differ
         const unsigned i = 4 * (wg - c.n3 - c.n2 / 2);
         const unsigned bk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7), b = i + bk;
         const uint64_t blk = b < c.n1_lo ? c.lo1 + b : c.hi1 + (b - c.n1_lo);
-        wide_body<KB, 0, 1, 4>(j, blk - bk, sh.b1024);
+        wide_body<KB, 0, 1, 4, LOOP>(j, blk - bk, sh.b1024, hist);
     }
+}
+
+template <int KB>
+__global__ __launch_bounds__(512, 4) void k_gemm_wide_w8(EnumJob j, WideCut c)
+{
+    __shared__ WidePlainShared<KB> sh;
+    wide_plain<KB, false>(j, c, blockIdx.x, sh, nullptr);
+}
+
+// The same for boxes of few classes (and conformations): n_wg workgroups' work
+// by two workgroups per compute unit, which count the designability of all
+// their blocks in LDS (2^24 sequences of 5x5 with all outputs 1.25 ms, 2.26 ms
+// with an atomic per designing sequence).
+template <int KB>
+__global__ __launch_bounds__(512, 4) void k_gemm_wide_few(EnumJob j, WideCut c, unsigned n_wg)
+{
+    __shared__ WidePlainShared<KB> sh;
+    __shared__ unsigned counts[kHistClasses];
+    zero_hist(j, counts);
+#pragma unroll 1
+    for (unsigned wg = blockIdx.x; wg < n_wg; wg += gridDim.x) {
+        wide_plain<KB, true>(j, c, wg, sh, counts);
+        __syncthreads();   // the next block's state, or the counts
+    }
+    flush_hist(j, counts);
 }
 
 // Batched wide blocks for jobs of one product depth and geometry G (0, 2 or
@@ -1039,8 +1061,15 @@ hipError_t launch_wide(const EnumJob &j, bool chunked, hipStream_t st)
     if (!chunked || n <= 2048)
         return launch_wide_small<KB, false>(j, n, st);
     const WideCut c = wide_cut(j.N, j.lo, j.hi);
-    hipLaunchKernelGGL((k_gemm_wide_w8<KB>), dim3(c.n3 + c.n2 / 2 + (c.n1 + 3) / 4), dim3(512), 0, st,
-                       j, c);
+    const unsigned n_wg = c.n3 + c.n2 / 2 + (c.n1 + 3) / 4;
+    if constexpr (KB <= 5) {   // boxes of few classes: up to 27 monomers, but for 2 x n
+        if (j.n_class <= kHistClasses) {
+            hipLaunchKernelGGL((k_gemm_wide_few<KB>), dim3(std::min(n_wg, 512u)), dim3(512), 0, st, j,
+                               c, n_wg);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((k_gemm_wide_w8<KB>), dim3(n_wg), dim3(512), 0, st, j, c);
     return hipGetLastError();
 }
 

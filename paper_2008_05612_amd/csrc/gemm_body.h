@@ -264,7 +264,7 @@ __device__ __forceinline__ void gemm_body(const EnumJob &j, uint64_t seq0_wg, v4
         const uint64_t idx = seq0 + t * 32 + col;
         uint64_t rs;
         const uint64_t sq = sequence_at(j, idx, &rs);
-        del += finish_sequence(j, idx, sq, rs, half == 0 && idx < j.hi, gb[t], gs[t], 1);
+        del += finish_sequence(j, j.c2q, idx, sq, rs, half == 0 && idx < j.hi, gb[t], gs[t], 1);
     }
     count_deleterious(j, del, lane == 0);
 }

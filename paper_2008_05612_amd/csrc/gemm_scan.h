@@ -190,7 +190,8 @@ __device__ __forceinline__ void scan_absorb_dense(const v16i &a, int T, ScanTop2
 // KB steps; TT column tiles per wave; Q groups of columns, S waves each.
 template <int KB, bool UN, int TT, int Q, int S>
 __device__ __forceinline__ void scan_dense_body(const EnumJob &j, uint64_t seq0, ScanFrag<UN> *frag,
-                                                ScanTop2 *top)
+                                                ScanTop2 *top, unsigned *del_sum,
+                                                unsigned *hist)
 {
     constexpr int kCols = Q * TT * 32;
     const int lane = threadIdx.x & 63;
@@ -200,6 +201,10 @@ __device__ __forceinline__ void scan_dense_body(const EnumJob &j, uint64_t seq0,
 
     for (int i = threadIdx.x; i < kCols; i += 64 * Q * S)
         top[i] = ScanTop2{0, 0};
+    if (threadIdx.x == 0)
+        *del_sum = 0;
+    if (hist)
+        zero_hist(j, hist);
     // second operands, through LDS: waves that share them form them together,
     // [Q TT][KB][64]; a wave of its own one tile at a time, [Q][KB][64] (kept
     // out of registers until whole, which an unrolled loop would not)
@@ -311,10 +316,12 @@ __device__ __forceinline__ void scan_dense_body(const EnumJob &j, uint64_t seq0,
             sq = sequence_at(j, idx, &rs);
             v = top[i];
         }
-        del += finish_sequence(j, idx, sq, rs, in, scan_global(int(v.b)), scan_global(int(v.s)),
-                               UN ? 1 : j.A);
+        del += finish_sequence(j, j.scan_c2q, idx, sq, rs, in, scan_global(int(v.b)),
+                               scan_global(int(v.s)), UN ? 1 : j.A, hist);
     }
-    count_deleterious(j, del, lane == 0);
+    count_deleterious_wg(j, del, del_sum);
+    if (hist)
+        flush_hist(j, hist);
 }
 
 template <int KB, bool UN, int TT, int Q, int S, int WPE>
@@ -322,7 +329,12 @@ __global__ __launch_bounds__(64 * Q * S, WPE) void k_scan(EnumJob j)
 {
     __shared__ ScanFrag<UN> frag[(S > 1 ? Q * TT : Q) * KB * 64];
     __shared__ ScanTop2 top[Q * TT * 32];
-    scan_dense_body<KB, UN, TT, Q, S>(j, j.lo + uint64_t(blockIdx.x) * (Q * TT * 32), frag, top);
+    __shared__ unsigned del_sum;
+    // classes in LDS where the workgroup's sequences are several per class
+    constexpr int kHist = Q * TT * 32 / 4;
+    __shared__ unsigned counts[kHist];
+    scan_dense_body<KB, UN, TT, Q, S>(j, j.lo + uint64_t(blockIdx.x) * (Q * TT * 32), frag, top,
+                                      &del_sum, j.n_class <= kHist ? counts : nullptr);
 }
 
 template <int KB, bool UN, int TT, int Q, int S, int WPE>
@@ -349,10 +361,12 @@ hipError_t launch_scan_kb(const EnumJob &j, hipStream_t st)
     constexpr int kBig = kWords * 4 <= 96 ? 4 : UN ? 3 : 2;
     const uint64_t n = j.hi - j.lo;
     const int steps = UN ? j.n_tiles : (j.n_tiles + 1) / 2;
-    if (n >= uint64_t(256) * 8 * kBig * 32 || steps < 16)
+    if (steps < 16)
+        return launch_scan_shape<KB, UN, kBig, 8, 1, 2>(j, st);
+    if (n >= uint64_t(256) * 8 * kBig * 32)
         return launch_scan_shape<KB, UN, kBig, 4, 1, 2>(j, st);
-    constexpr bool kFour = kWords <= (UN ? 24 : 20);   // two tiles fit four waves per SIMD
-    constexpr bool kOne = kWords <= 36 && KB <= 8;     // one tile does
+    constexpr bool kFour = kWords <= (UN ? 18 : 20);   // two tiles fit four waves per SIMD
+    constexpr bool kOne = kWords <= 36 && (UN || KB <= 5);   // one tile does
     if (n <= 256 * 32)
         return launch_scan_shape<KB, UN, 1, 1, kOne ? 16 : 8, kOne ? 4 : 2>(j, st);
     if (kFour && n <= 256 * 64)

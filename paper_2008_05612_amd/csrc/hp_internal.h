@@ -35,6 +35,7 @@ struct WsLayout {
     size_t gemm_a = 0;   // int8_t[n_tiles][K_pad/32][64 lanes][16]
     size_t gemm_b = 0;   // blocked form: int8_t[n_tiles][K_pad/32][64 lanes][16], or none
     size_t blk_s2 = 0;   // blocked form: int8_t[2 geometries][8 tiles][64 lanes][16], or none
+    size_t scan_c2q = 0; // uint16_t[n_conf], the scan's order of conformations, or none
     size_t scan_c1 = 0;  // threshold scans: FP4 [n_tiles, even][ceil((K+3)/64)][64 lanes][32
                          // values] (pure pair energies), or none
     size_t scan_un = 0;  // FP4 [n_tiles][ceil((K+U+6)/64)][64 lanes][32 values] (two-letter
@@ -78,6 +79,7 @@ struct hp_structs {
     std::vector<int8_t> gemm_b;       // blocked form: 0/1 contact matrix + window index rows
     std::vector<int8_t> blk_s2;       // blocked form: per-sequence operand of the second product
     bool wide_ok = false;             // wide blocks apply (pure pair energies, N >= 10)
+    std::vector<uint16_t> scan_c2q;   // conformation -> class in the order of the scan matrices
     std::vector<int8_t> scan_c1;      // threshold scans: contact matrix in FP4, pure pair energies
     std::vector<int8_t> scan_un;      // the same with unary rows, two-letter tables
     int scan_kb = 0;                  // dense scan: products per chain, 0 where it does not apply

@@ -24,6 +24,7 @@ struct EnumJob {
     uint64_t lo, hi;                // sequence range [lo, hi)
     int32_t N, K, W, KB;            // chain length, pairs, pair-mask words, K_pad/32
     int32_t n_conf, n_tiles;        // conformations, 32-conformation tiles
+    int32_t n_class;                // phenotypes
     int32_t U;                      // unary product rows (0 for pure HP)
     int32_t win_tiles, win_shift;   // int8-form key windows
     int32_t A, B, e0;               // F = A n + B u, E = e0 - F
@@ -43,6 +44,7 @@ struct EnumJob {
     int32_t blk_KB, blk_coefB, blk_ngroups;   // first-product depth / 32, m2 B, unary rows
     uint64_t blk_grp[3];                      // unary group of each outer monomer (4 bits)
     const int8_t *blk_s2;           // second-product operand of this geometry (8 x 64 x 16 B)
+    const uint16_t *scan_c2q;       // conformation -> class in the order of the scan matrices
     const int8_t *scan_c1;          // threshold scans, pure pair energies: 0/1 contact matrix in FP4
     const int8_t *scan_un;          // the same with unary rows (two-letter tables)
     int32_t scan_kb;                // dense scan: products per chain, 0 where it does not apply
@@ -98,6 +100,8 @@ bool gemm_shape_chosen(int KB);
 // buffered LDS with the next tile's first product overlapping this tile's
 // key updates.
 hipError_t launch_gemm_blocked(const EnumJob &j, int nw, int mode, hipStream_t st);
+// Most classes of a box whose designability is counted in LDS first.
+constexpr int kHistClasses = 1024;
 // Reversal-canonical wide blocks [j.lo, j.hi) (j.mode kSeqCanonical,
 // j.half_bits the outer monomers on each side).
 hipError_t launch_gemm_wide_canonical(const EnumJob &j, hipStream_t st);

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void k_popcount(EnumJob j, const uint32_t *__r
             n0 = j.A * n0 + j.B * unary_sum(m + W, j.planes, j.uw, s_lo, s_hi);
         top2_add1(best, second, (n0 << kKeyConfBits) | (c + 1));
     }
-    const unsigned del = finish_sequence(j, idx, s, rs, valid, best, second, UN ? 1 : j.A);
+    const unsigned del = finish_sequence(j, j.c2q, idx, s, rs, valid, best, second, UN ? 1 : j.A);
     count_deleterious(j, del, (threadIdx.x & 63) == 0);
 }
 
