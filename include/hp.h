@@ -373,10 +373,12 @@ hp_status hp_enumerate_batch_static(const hp_job *jobs, int njobs, int form, voi
  * waves of a workgroup: 1024 sequences sharing every monomer above the low
  * 10, and with nw = 8 in ranges beyond 2^21 sequences 4096 (monomers 0 .. 4
  * and 6, 8, .., 18 vary) in whole chunks of 2^19 where N >= 19 and 2048 (0 ..
- * 4 and 6, 8, .., 16) in the other whole chunks of 2^17 where N >= 17 -- pure
- * pair energies over plain ranges only, elsewhere mode 3 acts as -1; -1, default: 3 with 8 waves where wide blocks apply,
- * else 2 for K_pad <= 192, else 0).  Few sequences (4e5 / ceil(K_pad / 32)
- * with mode -1) run as columns of the dense scan instead.  hp_blocked_selected
+ * 4 and 6, 8, .., 16) in the other whole chunks of 2^17 where N >= 17; blocks
+ * of 1024 throughout with two-letter tables.  Plain ranges only, elsewhere
+ * mode 3 acts as -1; -1, default: 3 with 8 waves where wide blocks apply, else
+ * 2 for K_pad <= 192, else 0).  With mode -1 few sequences run as columns of
+ * the dense scan instead: up to 4e5 / ceil(K_pad / 32), with two-letter tables
+ * 2.7e5 / ceil(K_pad / 64).  hp_blocked_selected
  * reports them (either pointer may be NULL).  Results never depend on the
  * shape.
  * Errors: HP_EINVAL for another value, or mode 3 with nw = 2.

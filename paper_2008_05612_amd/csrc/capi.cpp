@@ -211,6 +211,7 @@ EnumJob make_enum_job(const hp_structs *s, const void *d_ws, uint64_t lo, uint64
     j.scan_c1 = reinterpret_cast<const int8_t *>(base + s->ws.scan_c1);
     j.scan_un = reinterpret_cast<const int8_t *>(base + s->ws.scan_un);
     j.scan_kb = s->scan_kb;
+    j.wide_un = s->wide_un;
     j.wide_s2 = s->wide_ok ? reinterpret_cast<const int8_t *>(base + s->ws.wide_s2) : nullptr;
     j.blk_shift = int32_t(s->blk_shift);
     j.blk_win_tiles = int32_t(s->blk_win_tiles);
@@ -393,10 +394,12 @@ struct RunOpts {
 // 0.2 us per tile whatever their number, a column 4.1e-7 us per tile and
 // product of its chain (3x3x3, chains of 5: 65536 sequences 0.44 against 0.63
 // ms, 131072 0.81 against 0.63; 6x6, 10: 20000 0.24 against 0.34 ms, 40000 0.36
-// against 0.34).  Only without a selected launch shape.
+// against 0.34).  Products of two-letter tables take longer (3x3x3, chains of 3:
+// 50000 sequences 0.50 against 0.83 ms, 100000 0.87 against 0.83; 5x5, 50000
+// 46 against 69 us, 100000 70 against 57).  Only without a selected launch shape.
 bool blocked_small(const hp_structs *s, uint64_t n)
 {
-    return blocked_selected_mode() < 0 && n * uint64_t(s->scan_kb) <= 400000;
+    return blocked_selected_mode() < 0 && n * uint64_t(s->scan_kb) <= (s->B ? 270000u : 400000u);
 }
 
 // Launches [lo, hi) in blocks of kBlockSeqs indices.  Per-index outputs are

@@ -421,11 +421,11 @@ __device__ __forceinline__ void blk_body(const EnumJob &j, uint64_t blk0, v4i *l
             // a diagonal block holds each sequence and its reverse itself
             const uint64_t sq = blk_sequence(j, outer, t * 32 + col);
             const uint64_t rs = diag ? sq : __builtin_bitreverse64(sq) >> (64 - j.N);
-            del += finish_sequence(j, j.c2q, sq, sq, rs, half == 0 && blk < j.hi, gb[t], gs[t], 1);
+            del += finish_sequence(j, j.scan_c2q, sq, sq, rs, half == 0 && blk < j.hi, gb[t], gs[t], 1);
         } else {
             const uint64_t idx = outer + uint64_t(t * 32 + col);
-            del += finish_sequence(j, j.c2q, idx, idx, idx, half == 0 && idx >= j.lo && idx < j.hi,
-                                   gb[t], gs[t], 1);
+            del += finish_sequence(j, j.scan_c2q, idx, idx, idx,
+                                   half == 0 && idx >= j.lo && idx < j.hi, gb[t], gs[t], 1);
         }
     }
     count_deleterious(j, del, lane == 0);
@@ -507,6 +507,16 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_blk_batch(BatchHeader *hdr, in
 // depth 64 per MFMA in the time an int8 product of depth 32 takes, exact in
 // the float accumulator), which halves its matrix time and the bytes of the
 // contact matrix that every workgroup reads.
+//
+// Two-letter tables (G 4: plain ranges, 1024 sequences, 4 waves) have one
+// sequence per accumulator: F = A n + B sum_i c_i h_i reaches hundreds.  The weights
+// A h + B and the block term's A h h' + B (h + h') are bytes, so the first
+// product is the int8 one; the block term takes two digits of 64, in rows 0
+// and 29, and so does T - 1 in the operand's constants.  With indicator bytes
+// -h the accumulator is T - 1 - F, whose sign bit says that F reaches T; the
+// OR of 16 accumulators takes the same 8 instructions.  A step of the 3x3x3
+// map: 21.0 ms (29.9 ms in blocks of 256 whose waves each form the first
+// product and test the largest of 16 keys).
 // ---------------------------------------------------------------------------
 
 // bits 5 and 11 of an accumulator: the count of either sequence reaches its
@@ -516,14 +526,19 @@ constexpr int kScanHit = (1 << 5) | (1 << 11);
 template <int G>
 constexpr int wide_bits() { return G == 3 ? kWide12Bits : G == 2 ? kWide11Bits : kWideBits; }
 template <int G>
-constexpr int wide_waves() { return 1 << (wide_bits<G>() - kWideWaveBits); }
+constexpr bool wide_table() { return G == 4; }
+template <int G>
+constexpr int wide_waves() { return G == 4 ? 4 : 1 << (wide_bits<G>() - kWideWaveBits); }
+// sequences of a wave's tile
+template <int G>
+constexpr int wide_cols() { return G == 4 ? 32 : 64; }
 // virtual rows: 0 block term, 1 .. nb weights, then 16 pairs; 30 and 31 the
 // constants 1 and 64
 template <int G>
 constexpr int wide_row_vv() { return 1 + wide_bits<G>(); }
-// first-product steps of depth 64 for pair depth KB * 32
-template <int KB>
-constexpr int wide_steps() { return (KB + 1) / 2; }
+// first-product steps for pair depth KB * 32: of depth 64, or 32 with tables
+template <int KB, int G>
+constexpr int wide_steps() { return wide_table<G>() ? KB : (KB + 1) / 2; }
 // waves of the second-product table before those of geometry G
 template <int G>
 constexpr int wide_s2_slot() { return G == 0 ? 0 : G == 1 ? 2 : G == 2 ? 4 : 8; }
@@ -578,6 +593,69 @@ __device__ __forceinline__ v4i wide_v_fragment(const EnumJob &j, uint64_t outer,
     // twice the spread: weights 2.0 (the contact matrix holds 0.5)
     return v4i{int(fp4_spread(bits & 0xffu) << 2), int(fp4_spread((bits >> 8) & 0xffu) << 2),
                int(fp4_spread((bits >> 16) & 0xffu) << 2), int(fp4_spread(bits >> 24) << 2)};
+}
+
+// The same for two-letter tables: step `st` covers rows k = 32 st + 16 half + n, n <
+// 16, as int8 A X_i Y_j (or Y_i X_j) + B (X_i + X_j); the pair rows have no B.
+__device__ __forceinline__ v4i wide_un_fragment(const EnumJob &j, uint64_t outer, int m, int half,
+                                                int st)
+{
+    constexpr int kRowVV = wide_row_vv<4>();
+    const uint64_t all = (uint64_t(1) << j.N) - 1;
+    uint64_t X = 0, Y = 0, U = 0;
+    if (m == 0 || m == 29) {
+        X = Y = U = outer;
+    } else if (m < kRowVV) {
+        X = U = uint64_t(1) << (m - 1);
+        Y = outer;
+    } else if (m < kRowVV + 16) {
+        const int pr = wide_pair<4>(j, m - kRowVV);
+        X = uint64_t(1) << (pr & 15);
+        Y = uint64_t(1) << (pr >> 4);
+    }
+    const uint32_t ab = pair_bits(X, Y, j.N, 32 * st) >> (16 * half);
+    const uint32_t one = pair_bits(U, all, j.N, 32 * st) >> (16 * half);
+    const uint32_t two = pair_bits(U, U, j.N, 32 * st) >> (16 * half);
+    v4i w;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+        uint32_t word = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int n = 4 * q4 + b;
+            const uint32_t v = uint32_t(j.A) * ((ab >> n) & 1u) +
+                               uint32_t(j.B) * (((one >> n) & 1u) + ((two >> n) & 1u));
+            word |= v << (8 * b);
+        }
+        w[q4] = int(word);
+    }
+    return w;
+}
+
+// Second operand of a table's sequences x = 32 tile + (lane & 31): byte q of this
+// lane is minus the indicator of x for row 8 (q / 4) + 4 half + q % 4, -64 for
+// the block term's upper digit; the constants hold T - 1 = -1 (no threshold yet).
+__device__ __forceinline__ v4i wide_un_operand(const EnumJob &j, int x, int half)
+{
+    constexpr int kRowVV = wide_row_vv<4>();
+    v4i w;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+        uint32_t word = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int m = 8 * q4 + 4 * half + b;
+            const int pr = wide_pair<4>(j, (m - kRowVV) & 15);
+            const bool pair = m >= kRowVV && m < kRowVV + 16;
+            const int first = pair ? pr & 15 : m - 1, second = pair ? pr >> 4 : m - 1;
+            int v = -((x >> (first & 15)) & (x >> (second & 15)) & 1);
+            v = m == 0 ? -1 : m == 29 ? -64 : m == 30 ? 63 : m == 31 ? -1 : v;
+            v = m == 27 || m == 28 ? 0 : v;
+            word |= uint32_t(v & 0xff) << (8 * b);
+        }
+        w[q4] = int(word);
+    }
+    return w;
 }
 
 // Canonical wide block index t -> outer bits, as blk_canonical_outer with 10
@@ -668,13 +746,58 @@ __device__ __forceinline__ void scan_absorb(const v4i &a2, v4i &sf, int hit, Sca
     scan_set_bias(sf, scan_bias(top[col].s), scan_bias(top[col + 32].s), half);
 }
 
+// The same for two-letter tables: T - 1 of a sequence whose second-best key is
+// gs, its digits as the operand's bytes, and the absorption of a tile into
+// top[col].  Only the accumulators below 0 are candidates, as (T - 1) + e with
+// e = -accumulator.
+__device__ __forceinline__ int scan_un_threshold(unsigned gs)
+{
+    return int((gs + kMaxConf) >> kKeyConfBits) - 1;
+}
+
+__device__ __forceinline__ void scan_un_set(v4i &sf, unsigned gs, int half)
+{
+    const int t = scan_un_threshold(gs);
+    scan_set_bias(sf, t & 63, (t >> 6) & 0xff, half);
+}
+
+__device__ __forceinline__ void scan_un_absorb(const v4i &a2, v4i &sf, ScanTop2 *top, int tile,
+                                               int lane)
+{
+    const int half = lane >> 5, col = lane & 31;
+    const v16i zero = {};
+    const v16i a = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf, zero, 0, 0, 0);
+    const auto w = __builtin_amdgcn_permlane32_swap(sf[3], sf[3], false, false);
+    const int word = int(w[1]);   // of the half-1 lane: the T - 1 this product had
+    const int t = 64 * (word >> 24) + ((word >> 16) & 63);
+    int b = 0, s = 0;   // the two smallest below 0, as 32 accumulator + row
+#pragma unroll
+    for (int q = 0; q < 16; q += 4) {
+        int m[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int k0 = int(unsigned(a[q + 2 * p]) << 5 | unsigned(2 * q + 2 * p));
+            const int k1 = int(unsigned(a[q + 2 * p + 1]) << 5 | unsigned(2 * q + 2 * p + 1));
+            m[p] = med3_i32(b, k0, k1);
+            b = min(min(b, k0), k1);
+        }
+        s = min(min(s, m[0]), m[1]);
+    }
+    auto key = [&](int k) {
+        const unsigned at = unsigned((t - (k >> 5)) << kKeyConfBits) + unsigned((k & 31) << 12);
+        return k < 0 ? at + unsigned(tile + 1 + (half << 14)) : 0u;
+    };
+    scan_push(top + col, key(b), key(s));
+    scan_un_set(sf, top[col].s, half);
+}
+
 // Second product of one conformation tile: the threshold scan of the wave's
-// 512 sequences.  NA accumulators: with three, each OR chain reads a product
+// 512 sequences (tables: 256).  NA accumulators: with three, each OR chain reads a product
 // issued a full chain earlier; the next product is issued after the chain
 // (forced with sched_group_barrier), when the matrix pipe is more often free.
 // Measured alone, an int8 product takes 34 SIMD cycles, and with n vector
 // instructions beside it 12 + 4.2 n where that is more: 44 for the 8 v_or3.
-template <int NA>
+template <int NA, bool UN>
 __device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], ScanTop2 *top,
                                           int tile, int lane)
 {
@@ -696,7 +819,14 @@ __device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], S
         }
     }
     const int any = (hit[0] | hit[1] | hit[2]) | (hit[3] | hit[4]) | (hit[5] | hit[6] | hit[7]);
-    if (__builtin_expect(__any((any & kScanHit) != 0), 0)) {
+    if constexpr (UN) {
+        if (__builtin_expect(__any(any < 0), 0)) {
+#pragma unroll
+            for (int t = 0; t < kBlkTiles; ++t)
+                if (__any(hit[t] < 0))
+                    scan_un_absorb(a2, sf[t], top + t * 32, tile, lane);
+        }
+    } else if (__builtin_expect(__any((any & kScanHit) != 0), 0)) {
 #pragma unroll
         for (int t = 0; t < kBlkTiles; ++t)
             if (__any((hit[t] & kScanHit) != 0))
@@ -714,9 +844,9 @@ __device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], S
 template <int KB, int G, int S = 1, int B = 1>
 struct WideShared {
     static constexpr int NW = wide_waves<G>();
-    v4i vlds[B][wide_steps<KB>() * 64];
+    v4i vlds[B][wide_steps<KB, G>() * 64];
     v4i a2s[B * S][2][NW][64];
-    ScanTop2 gbs[B][NW][kBlkTiles * 64];
+    ScanTop2 gbs[B][NW][kBlkTiles * wide_cols<G>()];
     unsigned del;
 };
 
@@ -726,10 +856,12 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
                                           unsigned *hist = nullptr)
 {
     constexpr int NW = wide_waves<G>();
-    constexpr int KS = wide_steps<KB>();
-    // deep products, shared keys and loops leave registers for two accumulators
+    constexpr int KS = wide_steps<KB, G>();
+    constexpr bool UN = wide_table<G>();
+    constexpr int kCols = wide_cols<G>();
+    // deep products, tables, shared keys and loops leave registers for two accumulators
     // (four waves per SIMD)
-    constexpr int kAcc = KS <= 3 && S == 1 && !LOOP ? 3 : 2;
+    constexpr int kAcc = KS <= 3 && !UN && S == 1 && !LOOP ? 3 : 2;
     const int lane = threadIdx.x & 63;
     const int half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -739,21 +871,28 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
     auto &a2s = sh.a2s[bk * S + sp];
     bool diag = false;
     const uint64_t outer = G == 1   ? wide_canonical_outer(j, blk, &diag)
-                           : G >= 2 ? wide_chunk_outer<G>(blk)
-                                    : blk << kWideBits;
-    const v4i *__restrict__ C1 = reinterpret_cast<const v4i *>(j.scan_c1);
+                           : G == 2 || G == 3 ? wide_chunk_outer<G>(blk)
+                                              : blk << kWideBits;
+    const v4i *__restrict__ C1 = reinterpret_cast<const v4i *>(UN ? j.gemm_b : j.scan_c1);
 
     if (threadIdx.x == 0)
         sh.del = 0;
     // the waves build the block's fragments, one step at a time
     for (int st = w % (NW * S); st < KS; st += NW * S)
-        vlds[st * 64 + lane] = wide_v_fragment<G>(j, outer, lane & 31, half, st);
+        vlds[st * 64 + lane] = UN ? wide_un_fragment(j, outer, lane & 31, half, st)
+                                  : wide_v_fragment<G>(j, outer, lane & 31, half, st);
     v4i sf[kBlkTiles];
-    const v4i *__restrict__ S2 = reinterpret_cast<const v4i *>(j.wide_s2) +
-                                 (wide_s2_slot<G>() + wave) * (kBlkTiles * 64);
+    if constexpr (UN) {
 #pragma unroll
-    for (int t = 0; t < kBlkTiles; ++t)
-        sf[t] = S2[t * 64 + lane];
+        for (int t = 0; t < kBlkTiles; ++t)
+            sf[t] = wide_un_operand(j, wave * 256 + t * 32 + (lane & 31), half);
+    } else {
+        const v4i *__restrict__ S2 = reinterpret_cast<const v4i *>(j.wide_s2) +
+                                     (wide_s2_slot<G>() + wave) * (kBlkTiles * 64);
+#pragma unroll
+        for (int t = 0; t < kBlkTiles; ++t)
+            sf[t] = S2[t * 64 + lane];
+    }
     // Wait for these loads here (s_waitcnt vmcnt(0)): the compiler's wait
     // counts are the same for every pass of the tile loop, so loads of the
     // second operand still counted as in flight there would make each pass
@@ -764,8 +903,8 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
     ScanTop2 *const top2 = sh.gbs[bk][wave];
     if (sp == 0) {
 #pragma unroll
-        for (int t = 0; t < kBlkTiles; ++t)
-            top2[t * 64 + lane] = ScanTop2{0, 0};
+        for (int i = lane; i < kBlkTiles * kCols; i += 64)
+            top2[i] = ScanTop2{0, 0};
     }
 
     const int n_tiles = j.n_tiles;
@@ -783,7 +922,27 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
     // 8 (q / 4) + 4 half + q % 4 of the result is byte q of this lane's second
     // operand, and the two constant rows are bytes 14 and 15 of half 1
     // (0 in columns beyond the last conformation, whose accumulators stay 0)
+    auto first_un = [&](const v4i (&c1)[KS], int tile, int buf) {
+        v16i d1;
+#pragma unroll
+        for (int st = 0; st < KS; ++st) {
+            const v16i zero = {};
+            d1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(vlds[st * 64 + lane], c1[st],
+                                                       st == 0 ? zero : d1, 0, 0, 0);
+        }
+        // the block term's digits: row 0 is byte 0 of half 0, row 29 byte 13 of half 1
+        d1[0] = half ? d1[0] : d1[0] & 63;
+        d1[13] = half ? d1[13] >> 6 : d1[13];
+        const int ones = half && tile * kTileConf + (lane & 31) < n_conf ? 0x40010000 : 0;
+        v4i p = pack_d1(d1);
+        p[3] |= ones;   // rows 30 and 31 of the product are 0
+        a2s[buf][wave][lane] = p;
+    };
     auto first = [&](const v4i (&c1)[KS], int tile, int buf) {
+        if constexpr (UN) {
+            first_un(c1, tile, buf);
+            return;
+        }
         v16f d1;
 #pragma unroll
         for (int st = 0; st < KS; ++st) {
@@ -836,8 +995,11 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
             if (g > 0 && (g <= 8 || g % kEvery == 0)) {
 #pragma unroll
                 for (int t = 0; t < kBlkTiles; ++t) {
-                    const ScanTop2 *const c = top2 + t * 64 + (lane & 31);
-                    scan_set_bias(sf[t], scan_bias(c[0].s), scan_bias(c[32].s), half);
+                    const ScanTop2 *const c = top2 + t * kCols + (lane & 31);
+                    if constexpr (UN)
+                        scan_un_set(sf[t], c[0].s, half);
+                    else
+                        scan_set_bias(sf[t], scan_bias(c[0].s), scan_bias(c[32].s), half);
                 }
             }
         }
@@ -854,7 +1016,7 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
                 a2n = a2s[buf ^ 1][0][lane];
             }
             if (tile < n_tiles)
-                scan_tile<kAcc>(a2, sf, top2, tile, lane);
+                scan_tile<kAcc, UN>(a2, sf, top2, tile, lane);
             if (tt == 0 && nt < n_tiles) {
                 first(c1, nt, buf ^ 1);
                 const int n2 = tile0(g + 2) + wave;
@@ -868,10 +1030,10 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
 
     unsigned del = 0;
 #pragma unroll 1
-    for (int t = sp; t < kBlkTiles; t += S) {
+    for (int t = sp; t < kBlkTiles * kCols / 64; t += S) {
         const ScanTop2 k = top2[t * 64 + lane];
         const int2 v = {scan_global(int(k.b)), scan_global(int(k.s))};
-        const int x = wave * 512 + t * 64 + lane;
+        const int x = wave * (kBlkTiles * kCols) + t * 64 + lane;
         if constexpr (G == 1) {
             // off the diagonal the block's reverse is never scored: write both;
             // a diagonal block holds each sequence and its reverse itself
@@ -881,7 +1043,7 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
                 sq |= uint64_t((x >> b) & 1) << wide_pos<1>(j, b);
             const uint64_t rs = diag ? sq : __builtin_bitreverse64(sq) >> (64 - j.N);
             del += finish_sequence(j, j.scan_c2q, sq, sq, rs, blk < j.hi, v.x, v.y, j.A);
-        } else if constexpr (G >= 2) {
+        } else if constexpr (G == 2 || G == 3) {
             uint64_t sq = outer | uint64_t(x & 31);
 #pragma unroll
             for (int b = 5; b < wide_bits<G>(); ++b)
@@ -891,7 +1053,7 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
         } else {
             const uint64_t idx = outer + uint64_t(x);
             del += finish_sequence(j, j.scan_c2q, idx, idx, idx, idx >= j.lo && idx < j.hi, v.x,
-                                   v.y, j.A, hist);
+                                   v.y, UN ? 1 : j.A, hist);
         }
     }
     count_deleterious_wg(j, del, &sh.del);
@@ -991,6 +1153,30 @@ __global__ __launch_bounds__(64 * S * wide_waves<G>(), 4) void k_gemm_wide_batch
     wide_body<KB, G, S, 1>(j, blk0 + uint64_t(it - start[lo]), sh);
 }
 
+// Two-letter tables: blocks of 1024, S groups of 4 waves on each.
+template <int KB, int S>
+__global__ __launch_bounds__(256 * S, 4) void k_gemm_wide_un(EnumJob j)
+{
+    __shared__ WideShared<KB, 4, S> sh;
+    wide_body<KB, 4, S, 1>(j, (j.lo >> kWideBits) + blockIdx.x, sh);
+}
+
+// The same for boxes of few classes, as k_gemm_wide_few (5x5 with all outputs, 98
+// blocks 57 us against 85, 2^20 sequences 0.14 ms; from 64 blocks on).
+template <int KB>
+__global__ __launch_bounds__(256, 4) void k_gemm_wide_un_few(EnumJob j, unsigned n_blocks)
+{
+    __shared__ WideShared<KB, 4> sh;
+    __shared__ unsigned counts[kHistClasses];
+    zero_hist(j, counts);
+#pragma unroll 1
+    for (unsigned b = blockIdx.x; b < n_blocks; b += gridDim.x) {
+        wide_body<KB, 4, 1, 1, true>(j, (j.lo >> kWideBits) + b, sh, counts);
+        __syncthreads();   // the next block's state, or the counts
+    }
+    flush_hist(j, counts);
+}
+
 // Groups of waves per block for a launch of n blocks of `waves` waves each: as
 // many as bring it to 4096 waves (16 per compute unit), at most 16 waves per
 // workgroup.  A sweep over all conformations takes a wave 1.8 ms on 3x3x3
@@ -1052,18 +1238,22 @@ hipError_t launch_wide_small(const EnumJob &j, uint64_t n, hipStream_t st)
 // waves, 16 per compute unit) take the largest blocks the range holds; fewer
 // (or without) take blocks of 1024, which spread more evenly: 2^20 sequences of
 // 3x3x3 2.2 ms (3.5 ms in the largest blocks, one workgroup per compute unit).
+// Boxes of few classes take k_gemm_wide_few from 384 blocks on, where its LDS
+// counts gain more than its larger workgroups lose: 5x5 with all outputs, 196
+// blocks 109 us against 68, 489 blocks 118 against 134, 977 112 against 233.
 template <int KB>
 hipError_t launch_wide(const EnumJob &j, bool chunked, hipStream_t st)
 {
     if (j.mode == kSeqCanonical)
         return launch_wide_small<KB, true>(j, j.hi - j.lo, st);
     const uint64_t n = wide_blocks(1, j.lo, j.hi);
-    if (!chunked || n <= 2048)
+    const bool few = KB <= 5 && j.n_class <= kHistClasses;   // up to 27 monomers, but for 2 x n
+    if (!chunked || n <= (few ? 384 : 2048))
         return launch_wide_small<KB, false>(j, n, st);
     const WideCut c = wide_cut(j.N, j.lo, j.hi);
     const unsigned n_wg = c.n3 + c.n2 / 2 + (c.n1 + 3) / 4;
-    if constexpr (KB <= 5) {   // boxes of few classes: up to 27 monomers, but for 2 x n
-        if (j.n_class <= kHistClasses) {
+    if constexpr (KB <= 5) {
+        if (few) {
             hipLaunchKernelGGL((k_gemm_wide_few<KB>), dim3(std::min(n_wg, 512u)), dim3(512), 0, st, j,
                                c, n_wg);
             return hipGetLastError();
@@ -1129,8 +1319,32 @@ hipError_t launch_blk_unary(const EnumJob &j, hipStream_t st)
 }
 
 template <int KB>
+hipError_t launch_wide_un(const EnumJob &j, hipStream_t st)
+{
+    if constexpr (KB > kBlkUnaryMaxKB) {
+        return hipErrorInvalidValue;
+    } else {
+        const uint64_t n = wide_blocks(1, j.lo, j.hi);
+        if (n >= 64 && j.n_class <= kHistClasses) {
+            hipLaunchKernelGGL((k_gemm_wide_un_few<KB>), dim3(unsigned(std::min<uint64_t>(n, 1024))), dim3(256), 0, st, j,
+                               unsigned(n));
+            return hipGetLastError();
+        }
+        const dim3 grid = dim3(unsigned(n));
+        switch (wide_split(n, wide_waves<4>())) {
+        case 4: hipLaunchKernelGGL((k_gemm_wide_un<KB, 4>), grid, dim3(1024), 0, st, j); break;
+        case 2: hipLaunchKernelGGL((k_gemm_wide_un<KB, 2>), grid, dim3(512), 0, st, j); break;
+        default: hipLaunchKernelGGL((k_gemm_wide_un<KB, 1>), grid, dim3(256), 0, st, j); break;
+        }
+        return hipGetLastError();
+    }
+}
+
+template <int KB>
 hipError_t launch_blk(const EnumJob &j, int nw, int mode, hipStream_t st)
 {
+    if (mode == kBlkStageWide && j.wide_un)
+        return launch_wide_un<KB>(j, st);
     if (j.blk_ngroups > 0 || j.blk_coefB != 0)
         return launch_blk_unary<KB>(j, st);
     if (mode == kBlkStageWide)

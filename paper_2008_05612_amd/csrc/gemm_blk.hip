@@ -124,12 +124,11 @@ hipError_t launch_gemm_blocked(const EnumJob &j, int nw, int mode, hipStream_t s
     // automatic staging: shallow products keep the second operand in LDS,
     // which frees registers for a fourth wave per SIMD (measured faster for
     // K_pad <= 160, slower for 320)
-    // wide blocks cover plain ranges with pure pair energies only; elsewhere
+    // wide blocks cover plain ranges only; elsewhere
     // the staging falls back to the automatic choice, which takes wide blocks
     // where they apply (measured faster at every depth) and otherwise keeps
     // the second operand in LDS for shallow products
-    const bool wide_ok = j.wide_s2 && j.mode == kSeqPlain && j.blk_ngroups == 0 &&
-                         j.blk_coefB == 0;
+    const bool wide_ok = j.mode == kSeqPlain && (j.wide_s2 || j.wide_un);
     // wide blocks: the largest that the range allows by default or when 8
     // waves are selected; blocks of 1024 when 4 are
     const bool wide8 = mode < 0 || nw == 8;

@@ -79,6 +79,7 @@ struct hp_structs {
     std::vector<int8_t> gemm_b;       // blocked form: 0/1 contact matrix + window index rows
     std::vector<int8_t> blk_s2;       // blocked form: per-sequence operand of the second product
     bool wide_ok = false;             // wide blocks apply (pure pair energies, N >= 10)
+    bool wide_un = false;             // wide blocks of two-letter tables apply (N >= 10)
     std::vector<uint16_t> scan_c2q;   // conformation -> class in the order of the scan matrices
     std::vector<int8_t> scan_c1;      // threshold scans: contact matrix in FP4, pure pair energies
     std::vector<int8_t> scan_un;      // the same with unary rows, two-letter tables

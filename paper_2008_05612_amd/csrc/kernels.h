@@ -44,10 +44,11 @@ struct EnumJob {
     int32_t blk_KB, blk_coefB, blk_ngroups;   // first-product depth / 32, m2 B, unary rows
     uint64_t blk_grp[3];                      // unary group of each outer monomer (4 bits)
     const int8_t *blk_s2;           // second-product operand of this geometry (8 x 64 x 16 B)
-    const uint16_t *scan_c2q;       // conformation -> class in the order of the scan matrices
+    const uint16_t *scan_c2q;       // conformation -> class in the order of gemm_b and the scan matrices
     const int8_t *scan_c1;          // threshold scans, pure pair energies: 0/1 contact matrix in FP4
     const int8_t *scan_un;          // the same with unary rows (two-letter tables)
     int32_t scan_kb;                // dense scan: products per chain, 0 where it does not apply
+    int32_t wide_un;                // wide blocks of two-letter tables apply
     const int8_t *wide_s2;          // wide blocks: second-product operand ((2 + 2 + 4 + 8) waves
                                     // x 8 x 64 x 16 B: plain 10, canonical 10, plain 11 and
                                     // plain 12 geometries), or null where they do not apply

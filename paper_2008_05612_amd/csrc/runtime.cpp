@@ -309,7 +309,7 @@ hp_status hp_autotune_blocked(const hp_structs *s, const void *d_ws, uint64_t se
         // shapes 0 .. 8: nw x staging mode; shape 9: wide blocks, where they
         // apply (8 waves: the largest blocks that the range allows)
         const int nw = i < 9 ? kNW[i / 3] : 8, mode = i < 9 ? i % 3 : 3;
-        if (i == 9 && !(s->wide_ok && j.blk_ngroups == 0 && j.blk_coefB == 0)) {
+        if (i == 9 && !s->wide_ok && !s->wide_un) {
             if (ms)
                 ms[i] = -1.f;
             continue;

@@ -509,6 +509,53 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
         a_byte(c, s->K + s->U + 1) = static_cast<int8_t>(-static_cast<int>(idx1 >> 7));
     }
 
+    // The scans absorb a tile whenever some sequence of it gains, so they take
+    // the conformations in an order of its own: sorted by the contact counts of
+    // the monomers, from the middle of the chain outwards, so that one tile's
+    // conformations gain together, and the tiles then spread by a stride near
+    // the golden section, so that the thresholds rise early.  Simulated tiles
+    // absorbed per 512 sequences: 3x3x3 513 in the natural order, 408; 6x6 532,
+    // 439; 5x5 141, 99.
+    std::vector<uint32_t> scan_order(n_conf);   // position -> conformation
+    {
+        std::vector<int> mono(N);
+        for (int i = 0; i < N; ++i)
+            mono[i] = i;
+        std::stable_sort(mono.begin(), mono.end(), [&](int a, int b) {
+            return std::abs(2 * a - N + 1) < std::abs(2 * b - N + 1);
+        });
+        // counts are at most 5: 3 bits each, 21 monomers a word
+        std::vector<std::array<uint64_t, 2>> rank(n_conf);
+        for (uint32_t c = 0; c < n_conf; ++c) {
+            rank[c] = {0, 0};
+            for (int r = 0; r < N; ++r)
+                rank[c][r / 21] |= uint64_t(7 - deg[size_t(c) * N + mono[r]]) << (60 - 3 * (r % 21));
+        }
+        std::vector<uint32_t> sorted(n_conf);
+        for (uint32_t c = 0; c < n_conf; ++c)
+            sorted[c] = c;
+        std::stable_sort(sorted.begin(), sorted.end(),
+                         [&](uint32_t a, uint32_t b) { return rank[a] < rank[b]; });
+        // whole tiles are permuted; a partial one stays last
+        const uint32_t whole = n_conf / kTileConf;
+        uint32_t stride = std::max(1u, uint32_t(0.6180339887 * whole) | 1u);
+        auto gcd = [](uint32_t a, uint32_t b) {
+            while (b) {
+                const uint32_t t = a % b;
+                a = b;
+                b = t;
+            }
+            return a;
+        };
+        while (whole > 1 && gcd(stride, whole) != 1)
+            ++stride;
+        for (uint32_t p = 0; p < n_conf; ++p) {
+            const uint32_t t = p / kTileConf;
+            const uint32_t from = t < whole ? uint32_t(uint64_t(t) * stride % whole) : t;
+            scan_order[p] = sorted[from * kTileConf + p % kTileConf];
+        }
+    }
+
     // ---- blocked int8 form ----------------------------------------------------
     // For a block of sequences sharing every monomer outside 8 varying ones,
     // F = base + sum_v h_v w_v + sum_{varying pairs} A C_vv' h_v h_v'
@@ -625,15 +672,13 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
                 uint32_t lane = col + 32 * (kk / 16);
                 return s->gemm_b[((size_t(t) * bkb + kb) * 64 + lane) * 16 + kk % 16];
             };
-            for (uint32_t c = 0; c < n_conf; ++c) {
-                for (uint32_t q = 0; q < s->nbp; ++q) {
-                    const int i = s->contacts[(size_t(c) * s->nbp + q) * 2];
-                    const int j = s->contacts[(size_t(c) * s->nbp + q) * 2 + 1];
-                    b_byte(c, pidx[size_t(i) * N + j]) = 1;
-                }
-                const uint32_t u = c % bconf + 1;
-                b_byte(c, s->K) = static_cast<int8_t>(u & 127);
-                b_byte(c, s->K + 1) = static_cast<int8_t>(u >> 7);
+            for (uint32_t p = 0; p < n_conf; ++p) {
+                const uint8_t *pair = s->contacts.data() + size_t(scan_order[p]) * s->nbp * 2;
+                for (uint32_t q = 0; q < s->nbp; ++q)
+                    b_byte(p, pidx[size_t(pair[2 * q]) * N + pair[2 * q + 1]]) = 1;
+                const uint32_t u = p % bconf + 1;
+                b_byte(p, s->K) = static_cast<int8_t>(u & 127);
+                b_byte(p, s->K + 1) = static_cast<int8_t>(u >> 7);
             }
         }
     }
@@ -687,56 +732,10 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
     // keeps the first of these rows.  Two-letter tables: contacts 1.0, unary
     // rows the contact count c_i, and in the last step the threshold rows 58 ..
     // 63 (0.5, four 6.0, 1.0).
-    // The scan absorbs a tile whenever some sequence of it gains, so it takes
-    // the conformations in an order of its own: sorted by the contact counts of
-    // the monomers, from the middle of the chain outwards, so that one tile's
-    // conformations gain together, and the tiles then spread by a stride near
-    // the golden section, so that the thresholds rise early.  Simulated tiles
-    // absorbed per 512 sequences: 3x3x3 513 in the natural order, 408; 6x6 532,
-    // 439; 5x5 141, 99.
     s->scan_c1.clear();
     s->scan_un.clear();
     s->scan_c2q.clear();
     s->scan_kb = 0;
-    std::vector<uint32_t> scan_order(n_conf);   // position -> conformation
-    {
-        std::vector<int> mono(N);
-        for (int i = 0; i < N; ++i)
-            mono[i] = i;
-        std::stable_sort(mono.begin(), mono.end(), [&](int a, int b) {
-            return std::abs(2 * a - N + 1) < std::abs(2 * b - N + 1);
-        });
-        // counts are at most 5: 3 bits each, 21 monomers a word
-        std::vector<std::array<uint64_t, 2>> rank(n_conf);
-        for (uint32_t c = 0; c < n_conf; ++c) {
-            rank[c] = {0, 0};
-            for (int r = 0; r < N; ++r)
-                rank[c][r / 21] |= uint64_t(7 - deg[size_t(c) * N + mono[r]]) << (60 - 3 * (r % 21));
-        }
-        std::vector<uint32_t> sorted(n_conf);
-        for (uint32_t c = 0; c < n_conf; ++c)
-            sorted[c] = c;
-        std::stable_sort(sorted.begin(), sorted.end(),
-                         [&](uint32_t a, uint32_t b) { return rank[a] < rank[b]; });
-        // whole tiles are permuted; a partial one stays last
-        const uint32_t whole = n_conf / kTileConf;
-        uint32_t stride = std::max(1u, uint32_t(0.6180339887 * whole) | 1u);
-        auto gcd = [](uint32_t a, uint32_t b) {
-            while (b) {
-                const uint32_t t = a % b;
-                a = b;
-                b = t;
-            }
-            return a;
-        };
-        while (whole > 1 && gcd(stride, whole) != 1)
-            ++stride;
-        for (uint32_t p = 0; p < n_conf; ++p) {
-            const uint32_t t = p / kTileConf;
-            const uint32_t from = t < whole ? uint32_t(uint64_t(t) * stride % whole) : t;
-            scan_order[p] = sorted[from * kTileConf + p % kTileConf];
-        }
-    }
     if (n_tiles <= kScanMaxTiles && B == 0 && s->nbp <= kScanMaxContacts) {
         s->scan_kb = int((s->K + 3 + 31) / 32);
         const uint32_t steps = (s->K + 3 + 63) / 64, last = uint32_t(s->scan_kb) - 1;
@@ -780,7 +779,7 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
                 set(p, 64 * steps - 6 + r, tail_code[r]);
         }
     }
-    if (s->scan_kb) {
+    if (s->scan_kb || s->blk_ok) {
         s->scan_c2q.resize(n_conf);
         for (uint32_t p = 0; p < n_conf; ++p)
             s->scan_c2q[p] = s->c2q[scan_order[p]];
@@ -798,7 +797,11 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
     // m = 8 (q / 4) + 4 (l / 32) + q % 4, the indicator of x plus 64 times that
     // of x + 32, and V = 32 of either sequence (no threshold yet) for the
     // constants.
-    s->wide_ok = false;
+    //
+    // Two-letter tables take plain blocks of 10 (wide_un): rows 0 and 29 the
+    // block term, split into digits of 64, then the same rows; the weights A
+    // h + B reach the bytes, and F below 2^13 the threshold's two digits.
+    s->wide_ok = s->wide_un = false;
     s->wide_s2.clear();
     const int wodd = N & 1;
     const int whalf = N >= kWideBits ? (N - kWideBits - wodd) / 2 : 0;
@@ -814,7 +817,7 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
                                               : (p < 8 ? kLow10Pairs0 : kLow10Pairs1);
         return int((w >> (8 * (p & 7))) & 0xffu);
     };
-    if (s->blk_ok && B == 0 && N >= kWideBits) {
+    if (s->blk_ok && N >= kWideBits) {
         int maxw = 0;   // largest weight of a varying monomer (all outer monomers H)
         for (int g = 0; g < std::min(n_geom, 3); ++g) {
             bool vary[64] = {};
@@ -829,11 +832,13 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
                         const int b = s->contacts[(size_t(c) * s->nbp + q) * 2 + 1];
                         with_outer += (a == v && !vary[b]) || (b == v && !vary[a]);
                     }
-                    maxw = std::max(maxw, int(A) * with_outer);
+                    maxw = std::max(maxw, int(A * with_outer + B * deg[size_t(c) * N + v]));
                 }
             }
         }
-        s->wide_ok = int64_t(s->blk_coef) * maxw <= 128 && s->nbp <= kScanMaxContacts &&
+        s->wide_un = B > 0 && maxw <= 127 && A + 2 * B <= 127 && fmax < (1 << 13) &&
+                     n_tiles <= kScanMaxTiles;
+        s->wide_ok = B == 0 && int64_t(s->blk_coef) * maxw <= 128 && s->nbp <= kScanMaxContacts &&
                      s->scan_kb > 0 &&
                      (s->K + 3 + 63) / 64 == (s->blk_KB + 1) / 2;
     }
