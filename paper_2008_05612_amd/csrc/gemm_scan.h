@@ -353,7 +353,10 @@ hipError_t launch_scan_shape(const EnumJob &j, hipStream_t st)
 // splitting the conformations (2^14 draws on 3x3x3: 0.114 ms with 64 columns,
 // 0.154 with 32; 2^13: 0.106 and 0.084).  Waves per SIMD follow the registers of
 // the second operands (4 KB TT words, FP6 6 KB TT).  Boxes of few conformations
-// have none to split.
+// have none to split: there up to 2^17 sequences take a tile per wave (4x4, Table
+// 1, 4000 sequences 8.9 us, with TT columns 18.8; 5x4, 2^17 draws 33 and 50 us),
+// more take TT again, whose class counts in LDS cover more sequences (4x4, 2^18
+// draws 28 and 19 us).
 template <int KB, bool UN>
 hipError_t launch_scan_kb(const EnumJob &j, hipStream_t st)
 {
@@ -361,6 +364,8 @@ hipError_t launch_scan_kb(const EnumJob &j, hipStream_t st)
     constexpr int kBig = kWords * 4 <= 96 ? 4 : UN ? 3 : 2;
     const uint64_t n = j.hi - j.lo;
     const int steps = UN ? j.n_tiles : (j.n_tiles + 1) / 2;
+    if (steps < 16 && n <= 1 << 17)
+        return launch_scan_shape<KB, UN, 1, 8, 1, 2>(j, st);
     if (steps < 16)
         return launch_scan_shape<KB, UN, kBig, 8, 1, 2>(j, st);
     if (n >= uint64_t(256) * 8 * kBig * 32)
