@@ -827,10 +827,14 @@ __device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], S
                     scan_un_absorb(a2, sf[t], top + t * 32, tile, lane);
         }
     } else if (__builtin_expect(__any((any & kScanHit) != 0), 0)) {
+        // ahead of the other waves, which will wait for this one at the group's
+        // barrier (2^24 sequences of 5x5: 1.10 ms, 1.17 without)
+        __builtin_amdgcn_s_setprio(2);
 #pragma unroll
         for (int t = 0; t < kBlkTiles; ++t)
             if (__any((hit[t] & kScanHit) != 0))
                 scan_absorb(a2, sf[t], hit[t], top + t * 64, tile, lane);
+        __builtin_amdgcn_s_setprio(0);
     }
 }
 
