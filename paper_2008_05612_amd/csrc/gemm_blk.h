@@ -485,23 +485,31 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_blk_batch(BatchHeader *hdr, in
 //   3  whole chunks of 2^19, 4096 sequences (monomers 0 .. 4 and the even ones
 //      6 .. 18: 16 pairs), 8 waves.
 //
-// The second product is a threshold scan.  Counts of H-H contacts are at
-// most 31 (kScanMaxContacts), so one int32 accumulator holds two sequences:
-// column `col` of sequence tile t carries x = 64 t + col and x + 32, whose
-// operands differ in one varying monomer, with indicator bytes h(x) +
-// 64 h(x + 32), and two constant virtual rows (1 and 64, the last two of the
-// 32) carry V = 32 - T of each, T being the smallest count that can still
-// change that sequence's two best (one more than its second best).  The
-// accumulator is
-//   64 (32 + n(x + 32) - T(x + 32)) + (32 + n(x) - T(x)),
-// both fields within 0 .. 63, and bits 11 and 5 say whether n reaches T.  A
-// lane ORs its 16 accumulators (8 v_or3 per product, for 32 conformations x
-// 64 sequences), and only a tile in which some bit is set is absorbed.  A
+// The second product is a threshold scan.  Counts of H-H contacts are at most 31
+// (kScanMaxContacts), so 6 bits hold 32 + n - T, T being the smallest count that
+// can still change a sequence's two best (one more than its second best), and
+// the top one of them says whether n reaches T.  One float accumulator holds
+// four such fields: two sequences, x = 64 t + col and x + 32, times two
+// conformation tiles.  The product has depth 64; its two halves carry the same 32
+// virtual rows of a conformation (FP6: weights to 15, the block term as a digit
+// of 8s and one of 1s, rows 29 and 0) against the indicators of x and of x + 32
+// (FP4), with block scales 2^6 apart, and V = 32 - T of each as 9 a + b, two FP4
+// digits beside the constants 9 and 1 (rows 30 and 31).  The second tile's
+// product adds at scales 2^12 higher.  Starting from 4.0 with units of 2^-21,
+// the accumulator's bits hold the fields from bit 0 on: bits 5, 11 and 17 are the
+// guards of three, and the fourth's carries into the exponent (bit 24; it then
+// displaces the others, so both tiles are looked at).  All of it is exact below
+// the carry.  A lane ORs its 16 accumulators: 8 v_or3 per two products, for 64
+// conformations x 64 sequences, and only a tile in which some bit is set is
+// absorbed.  A
 // conformation below T can change neither the lowest energy, nor its
 // conformation when unique, nor whether it is unique, nor the gap to the
 // second-lowest energy, so every output is that of updating every key (which
 // conformation the second key names may differ; it is never reported).
-// Simulated on sampled 3x3x3 blocks, 8 % of a wave's tiles hold a hit.
+// Simulated on sampled 3x3x3 blocks, 8 % of a wave's tiles hold a hit.  In int8
+// (two fields, 8 v_or3 per product) the vector instructions took longer than the
+// products: alone, 2 tiles x 64 sequences 98 SIMD cycles against 88; a step of
+// the 3x3x3 map 43.3 ms against 38.6.
 //
 // The first product runs in FP4 (0/1 weights times 0/1 contacts,
 // depth 64 per MFMA in the time an int8 product of depth 32 takes, exact in
@@ -519,9 +527,13 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_blk_batch(BatchHeader *hdr, in
 // product and test the largest of 16 keys).
 // ---------------------------------------------------------------------------
 
-// bits 5 and 11 of an accumulator: the count of either sequence reaches its
-// threshold
-constexpr int kScanHit = (1 << 5) | (1 << 11);
+// Guard bits of an accumulator, as the bits of a float in [4, 8): bits 5, 11 and
+// 17 are those of the three lower fields; the fourth's carries into the
+// exponent and sets bit 24.
+constexpr int kScanHit = (1 << 5) | (1 << 11) | (1 << 17) | (1 << 24);
+// scales of the four fields (E8M0; a unit product is 2^-4, a field's unit 2^-21
+// 2^6 f), the two of one conformation tile in the lane halves
+constexpr int kScanScale = 110, kScanField = 6;
 
 template <int G>
 constexpr int wide_bits() { return G == 3 ? kWide12Bits : G == 2 ? kWide11Bits : kWideBits; }
@@ -532,8 +544,8 @@ constexpr int wide_waves() { return G == 4 ? 4 : 1 << (wide_bits<G>() - kWideWav
 // sequences of a wave's tile
 template <int G>
 constexpr int wide_cols() { return G == 4 ? 32 : 64; }
-// virtual rows: 0 block term, 1 .. nb weights, then 16 pairs; 30 and 31 the
-// constants 1 and 64
+// virtual rows: 0 and 29 block term, 1 .. nb weights, then 16 pairs; 30 and 31
+// constants
 template <int G>
 constexpr int wide_row_vv() { return 1 + wide_bits<G>(); }
 // first-product steps for pair depth KB * 32: of depth 64, or 32 with tables
@@ -579,7 +591,7 @@ __device__ __forceinline__ v4i wide_v_fragment(const EnumJob &j, uint64_t outer,
 {
     constexpr int kRowVV = wide_row_vv<G>();
     uint64_t X = 0, Y = 0;
-    if (m == 0) {
+    if (m == 0 || m == 29) {
         X = Y = outer;
     } else if (m < kRowVV) {
         X = uint64_t(1) << wide_pos<G>(j, m - 1);
@@ -704,31 +716,63 @@ __device__ __forceinline__ int scan_bias(unsigned gs)
     return 32 - int((gs + kMaxConf) >> kKeyConfBits);
 }
 
-// The two V bytes of a lane pair's sequences in the last word of the second
+// V = 9 a + b, a = 0 .. 4, b = -4 .. 4, as the lane's two FP4 digits (codes of
+// half units) beside the rows 9 and 1.
+__device__ __forceinline__ void scan_set_v(v4i &sf, int v)
+{
+    const int a = (v + 4) / 9, b = v - 9 * a;
+    sf[3] = int((unsigned(sf[3]) & 0x0f0fffffu) | unsigned(a << 20) |
+                (unsigned(b < 0 ? 8 - b : b) << 28));
+}
+
+__device__ __forceinline__ int scan_get_v(unsigned word)
+{
+    const int b = int(word >> 28);
+    return 9 * int((word >> 20) & 15u) + (b & 8 ? 8 - b : b);
+}
+
+// The two V bytes of a table tile's sequence in the last word of the second
 // operand of its half-1 lane.
 __device__ __forceinline__ void scan_set_bias(v4i &sf, int lower, int upper, int half)
 {
     sf[3] = half ? (sf[3] & 0xffff) | (lower << 16) | (upper << 24) : sf[3];
 }
 
+__device__ __forceinline__ v16f scan_product(const v6i &a2, const v4i &sf, const v16f &c, int scale)
+{
+    const v8i a = {a2[0], a2[1], a2[2], a2[3], a2[4], a2[5], 0, 0};
+    const v8i b = {sf[0], sf[1], sf[2], sf[3], 0, 0, 0, 0};
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 2, 4, 0, scale, 0, 127);
+}
+
+__device__ __forceinline__ v16f scan_four()
+{
+    v16f c;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        c[r] = 4.0f;
+    return c;
+}
+
 // Absorbs the 32 conformations of tile `tile` into the two best of a tile's
-// sequences, top[col] and top[col + 32]: the scan's product again, and for each
-// field that has a hit the two best of the lane's 16 rows as keys, pushed with
-// LDS atomics (both lane halves, and in split blocks other waves, score the
-// same sequences).  The V that the product was formed with are the operand's
-// own bytes.  A candidate below T is pushed for nothing, one of an empty column
-// is none.
-__device__ __forceinline__ void scan_absorb(const v4i &a2, v4i &sf, int hit, ScanTop2 *top, int tile,
-                                            int lane)
+// sequences, top[col] and top[col + 32]: the scan's product of this tile alone
+// and, for each field that has a hit, the two best of the lane's 16 rows as
+// keys, pushed with LDS atomics (both lane halves, and in split blocks other
+// waves, score the same sequences).  The V that the product was formed with
+// are the operands' own digits.  A candidate below T is pushed for nothing, one
+// of an empty column is none.
+__device__ __forceinline__ void scan_absorb(const v6i &a2, v4i &sf, ScanTop2 *top, int tile, int lane)
 {
     const int half = lane >> 5, col = lane & 31;
-    const v16i zero = {};
-    const v16i a = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf, zero, 0, 0, 0);
+    const v16i a = __builtin_bit_cast(
+        v16i, scan_product(a2, sf, scan_four(), kScanScale + kScanField * half));
+    const int hit = or16(a);
+    if (!__any((hit & (32 | 2048)) != 0))
+        return;
     const auto w = __builtin_amdgcn_permlane32_swap(sf[3], sf[3], false, false);
-    const unsigned word = unsigned(w[1]);   // of the half-1 lane
     const int at = tile + 1 + (half << 14);
-    auto push = [&](unsigned b, unsigned s, unsigned bias, ScanTop2 *g) {
-        const int base = at - int(bias << kKeyConfBits);
+    auto push = [&](unsigned b, unsigned s, int bias, ScanTop2 *g) {
+        const int base = at - (bias << kKeyConfBits);
         auto key = [&](unsigned k) {
             return unsigned(max(0, int(((k >> 26) << kKeyConfBits) + ((k & 31) << 12)) + base));
         };
@@ -737,13 +781,13 @@ __device__ __forceinline__ void scan_absorb(const v4i &a2, v4i &sf, int hit, Sca
     unsigned b, s;
     if (__any((hit & 32) != 0)) {
         scan_best<26>(a, b, s);
-        push(b, s, (word >> 16) & 0xffu, top + col);
+        push(b, s, scan_get_v(w[0]), top + col);
     }
     if (__any((hit & 2048) != 0)) {
         scan_best<20>(a, b, s);
-        push(b, s, word >> 24, top + col + 32);
+        push(b, s, scan_get_v(w[1]), top + col + 32);
     }
-    scan_set_bias(sf, scan_bias(top[col].s), scan_bias(top[col + 32].s), half);
+    scan_set_v(sf, scan_bias(top[lane].s));
 }
 
 // The same for two-letter tables: T - 1 of a sequence whose second-best key is
@@ -791,50 +835,75 @@ __device__ __forceinline__ void scan_un_absorb(const v4i &a2, v4i &sf, ScanTop2 
     scan_un_set(sf, top[col].s, half);
 }
 
-// Second product of one conformation tile: the threshold scan of the wave's
-// 512 sequences (tables: 256).  NA accumulators: with three, each OR chain reads a product
-// issued a full chain earlier; the next product is issued after the chain
-// (forced with sched_group_barrier), when the matrix pipe is more often free.
-// Measured alone, an int8 product takes 34 SIMD cycles, and with n vector
-// instructions beside it 12 + 4.2 n where that is more: 44 for the 8 v_or3.
-template <int NA, bool UN>
-__device__ __forceinline__ void scan_tile(const v4i &a2, v4i (&sf)[kBlkTiles], ScanTop2 *top,
+// Second product of two conformation tiles: the threshold scan of the wave's 512
+// sequences.  One accumulator beside the constant (the compiler keeps the 4.0 of
+// the first product's input in registers, which leaves no room for more at
+// four waves per SIMD): the other waves fill the matrix pipe meanwhile.
+__device__ __forceinline__ void scan_pair(const v6i (&a2)[2], v4i (&sf)[kBlkTiles], ScanTop2 *top,
                                           int tile, int lane)
 {
-    const v16i zero = {};
-    v16i acc[NA];
+    const int scale = kScanScale + (lane >> 5) * kScanField;
+    const v16f four = scan_four();
+    v16f acc[2];
     int hit[kBlkTiles];
-#pragma unroll
-    for (int t = 0; t < NA - 1; ++t)
-        acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf[t], zero, 0, 0, 0);
+    auto product = [&](int t) {
+        return scan_product(a2[1], sf[t], scan_product(a2[0], sf[t], four, scale),
+                            scale + 2 * kScanField);
+    };
+    acc[0] = product(0);
 #pragma unroll
     for (int t = 0; t < kBlkTiles; ++t) {
-        const int n = t + NA - 1;
-        if (n < kBlkTiles)
-            acc[n % NA] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf[n], zero, 0, 0, 0);
-        hit[t] = or16(acc[t % NA]);
-        if (n < kBlkTiles) {
+        if (t + 1 < kBlkTiles)
+            acc[(t + 1) & 1] = product(t + 1);
+        hit[t] = or16(__builtin_bit_cast(v16i, acc[t & 1]));
+        if (t + 1 < kBlkTiles) {
+            __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        }
+    }
+    const int any = (hit[0] | hit[1] | hit[2]) | (hit[3] | hit[4]) | (hit[5] | hit[6] | hit[7]);
+    if (__builtin_expect(__any((any & kScanHit) != 0), 0)) {
+        // ahead of the other waves, which will wait for this one at the group's
+        // barrier (2^24 sequences of 5x5: 1.10 ms, 1.17 without)
+        __builtin_amdgcn_s_setprio(2);
+#pragma unroll
+        for (int t = 0; t < kBlkTiles; ++t) {
+            // a carry displaces the lower fields: both tiles are looked at
+            if (__any((hit[t] & ((1 << 5) | (1 << 11) | (1 << 24))) != 0))
+                scan_absorb(a2[0], sf[t], top + t * 64, tile, lane);
+            if (__any((hit[t] & ((1 << 17) | (1 << 24))) != 0))
+                scan_absorb(a2[1], sf[t], top + t * 64, tile + 1, lane);
+        }
+        __builtin_amdgcn_s_setprio(0);
+    }
+}
+
+// The same for two-letter tables, one conformation tile and 256 sequences.
+// Measured alone, an int8 product takes 34 SIMD cycles, and with n vector
+// instructions beside it 12 + 4.2 n where that is more: 44 for the 8 v_or3.
+__device__ __forceinline__ void scan_un_tile(const v4i &a2, v4i (&sf)[kBlkTiles], ScanTop2 *top,
+                                             int tile, int lane)
+{
+    const v16i zero = {};
+    v16i acc[2];
+    int hit[kBlkTiles];
+    acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf[0], zero, 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < kBlkTiles; ++t) {
+        if (t + 1 < kBlkTiles)
+            acc[(t + 1) & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, sf[t + 1], zero, 0, 0, 0);
+        hit[t] = or16(acc[t & 1]);
+        if (t + 1 < kBlkTiles) {
             __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         }
     }
     const int any = (hit[0] | hit[1] | hit[2]) | (hit[3] | hit[4]) | (hit[5] | hit[6] | hit[7]);
-    if constexpr (UN) {
-        if (__builtin_expect(__any(any < 0), 0)) {
-#pragma unroll
-            for (int t = 0; t < kBlkTiles; ++t)
-                if (__any(hit[t] < 0))
-                    scan_un_absorb(a2, sf[t], top + t * 32, tile, lane);
-        }
-    } else if (__builtin_expect(__any((any & kScanHit) != 0), 0)) {
-        // ahead of the other waves, which will wait for this one at the group's
-        // barrier (2^24 sequences of 5x5: 1.10 ms, 1.17 without)
-        __builtin_amdgcn_s_setprio(2);
+    if (__builtin_expect(__any(any < 0), 0)) {
 #pragma unroll
         for (int t = 0; t < kBlkTiles; ++t)
-            if (__any((hit[t] & kScanHit) != 0))
-                scan_absorb(a2, sf[t], hit[t], top + t * 64, tile, lane);
-        __builtin_amdgcn_s_setprio(0);
+            if (__any(hit[t] < 0))
+                scan_un_absorb(a2, sf[t], top + t * 32, tile, lane);
     }
 }
 
@@ -849,7 +918,7 @@ template <int KB, int G, int S = 1, int B = 1>
 struct WideShared {
     static constexpr int NW = wide_waves<G>();
     v4i vlds[B][wide_steps<KB, G>() * 64];
-    v4i a2s[B * S][2][NW][64];
+    v4i a2s[B * S][2][NW][64];   // pure: 6 words of 32 conformations
     ScanTop2 gbs[B][NW][kBlkTiles * wide_cols<G>()];
     unsigned del;
 };
@@ -863,12 +932,13 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
     constexpr int KS = wide_steps<KB, G>();
     constexpr bool UN = wide_table<G>();
     constexpr int kCols = wide_cols<G>();
-    // deep products, tables, shared keys and loops leave registers for two accumulators
-    // (four waves per SIMD)
-    constexpr int kAcc = KS <= 3 && !UN && S == 1 && !LOOP ? 3 : 2;
-    const int lane = threadIdx.x & 63;
+    // in a loop, nothing that depends on the lane is kept over the blocks
+    unsigned tid = threadIdx.x;
+    if constexpr (LOOP)
+        asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
     const int half = lane >> 5;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = w % NW, sp = w / NW % S, bk = w / (NW * S);
     blk += bk;
     v4i *const vlds = sh.vlds[bk];
@@ -922,10 +992,10 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
         for (int st = 0; st < KS; ++st)
             c1[st] = src[st * 64];
     };
-    // first product of a tile into this wave's slot of buffer `buf`: row
+    // first product of a tile into this wave's slot of buffer `buf`.  Tables: row
     // 8 (q / 4) + 4 half + q % 4 of the result is byte q of this lane's second
-    // operand, and the two constant rows are bytes 14 and 15 of half 1
-    // (0 in columns beyond the last conformation, whose accumulators stay 0)
+    // operand, and the two constant rows are bytes 14 and 15 of half 1 (0 in
+    // columns beyond the last conformation, whose accumulators stay 0)
     auto first_un = [&](const v4i (&c1)[KS], int tile, int buf) {
         v16i d1;
 #pragma unroll
@@ -957,18 +1027,25 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
             d1 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, st == 0 ? zero : d1, 4, 4,
                                                                  0, 0, 0, 0);
         }
-        const int ones = half && tile * kTileConf + (lane & 31) < n_conf ? 0x40010000 : 0;
-        v4i p;
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            uint32_t x = 0;
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                x = __builtin_amdgcn_cvt_pk_u8_f32(d1[4 * q4 + b], b, x);
-            p[q4] = int(x);
-        }
-        p[3] |= ones;   // rows 30 and 31 of the product are 0
-        a2s[buf][wave][lane] = p;
+        // the block term's digits, and the constants 9 and 1 of real columns
+        const float f0 = 8.0f * __builtin_floorf(0.125f * d1[0]);
+        const float f13 = 8.0f * __builtin_floorf(0.125f * d1[13]);
+        const bool real = tile * kTileConf + (lane & 31) < n_conf;
+        d1[0] = half ? d1[0] : d1[0] - f0;
+        d1[13] = half ? f13 : d1[13];
+        d1[14] = half ? (real ? 9.0f : 0.0f) : d1[14];
+        d1[15] = half ? (real ? 1.0f : 0.0f) : d1[15];
+        // 16 values as FP6, d1[i] and d1[8 + i] in turn, in eighths; the other
+        // 16 of the conversion are not used
+        const v16f up = __builtin_shufflevector(d1, d1, 8, 9, 10, 11, 12, 13, 14, 15, 8, 9, 10, 11,
+                                                12, 13, 14, 15);
+        const auto p = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(d1, up, 8.0f);
+        // words 0 .. 3 of the 32 conformations, then words 4 and 5
+        int *const dst = reinterpret_cast<int *>(a2s[buf][wave]);
+        const int conf = lane & 31;
+        dst[half ? 4 * conf + 3 : 4 * conf] = int(p[0]);
+        dst[half ? 128 + 2 * conf : 4 * conf + 1] = int(p[1]);
+        dst[half ? 129 + 2 * conf : 4 * conf + 2] = int(p[2]);
     };
 
     // first tile of this group's g-th group of tiles
@@ -976,19 +1053,41 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
     const int n_groups = (n_tiles + NW * S - 1) / (NW * S);
     v4i c1[KS];
     __syncthreads();   // vlds
-    if (tile0(0) + wave < n_tiles) {
+    // first product of tile `tile`, loaded; zeros beyond the last, which may be
+    // the second of a pair
+    auto next_first = [&](int tile, int buf) {
+        if (tile < n_tiles)
+            first(c1, tile, buf);
+        else
+            a2s[buf][wave][lane] = v4i{0, 0, 0, 0};
+    };
+    if (tile0(0) + wave < n_tiles)
         load_c1(tile0(0) + wave, c1);
-        first(c1, tile0(0) + wave, 0);
-    }
+    next_first(tile0(0) + wave, 0);
     if (tile0(1) + wave < n_tiles)
         load_c1(tile0(1) + wave, c1);
     __syncthreads();
-    // The packed first product of the next tile is read from LDS one tile
-    // ahead, so no tile starts by waiting for it.  The group's barrier sits
-    // before its last tile: by then every wave has read all of this group's
-    // buffer and written its first product of the next group, so the next
-    // group's first tile can be read ahead as well.
-    v4i a2n = a2s[0][0][lane];
+    // The group's barrier sits before its last products: by then every wave has
+    // read all of this group's buffer and written its first product of the next
+    // group.  Tables read each packed first product one tile ahead of its use;
+    // pairs leave no registers for that.
+    constexpr int kStep = UN ? 1 : 2;   // conformation tiles at a time
+    std::conditional_t<UN, v4i, v6i> a2[kStep];
+    auto read = [&](int buf, int tt) {
+#pragma unroll
+        for (int i = 0; i < kStep; ++i) {
+            const v4i *src = a2s[buf][tt + i];
+            if constexpr (UN) {
+                a2[i] = src[lane];
+            } else {
+                const v4i q = src[lane & 31];
+                const int2 r = reinterpret_cast<const int2 *>(src + 32)[lane & 31];
+                a2[i] = v6i{q[0], q[1], q[2], q[3], r.x, r.y};
+            }
+        }
+    };
+    if constexpr (UN)
+        read(0, 0);
     for (int g = 0; g < n_groups; ++g) {
         const int buf = g & 1;
         const int nt = tile0(g + 1) + wave;   // this wave's tile of the next group
@@ -999,33 +1098,42 @@ __device__ __forceinline__ void wide_body(const EnumJob &j, uint64_t blk, WideSh
             if (g > 0 && (g <= 8 || g % kEvery == 0)) {
 #pragma unroll
                 for (int t = 0; t < kBlkTiles; ++t) {
-                    const ScanTop2 *const c = top2 + t * kCols + (lane & 31);
                     if constexpr (UN)
-                        scan_un_set(sf[t], c[0].s, half);
+                        scan_un_set(sf[t], top2[t * 32 + (lane & 31)].s, half);
                     else
-                        scan_set_bias(sf[t], scan_bias(c[0].s), scan_bias(c[32].s), half);
+                        scan_set_v(sf[t], scan_bias(top2[t * 64 + lane].s));
                 }
             }
         }
 #pragma unroll 1
-        for (int tt = 0; tt < NW; ++tt) {
+        for (int tt = 0; tt < NW; tt += kStep) {
             const int tile = tile0(g) + tt;
-            const v4i a2 = a2n;
-            if (tt + 1 < NW) {
-                a2n = a2s[buf][tt + 1][lane];
-            } else {
-                // the next group's first products are visible, and this
-                // group's buffer is free for the group after it
-                __syncthreads();
-                a2n = a2s[buf ^ 1][0][lane];
-            }
-            if (tile < n_tiles)
-                scan_tile<kAcc, UN>(a2, sf, top2, tile, lane);
-            if (tt == 0 && nt < n_tiles) {
-                first(c1, nt, buf ^ 1);
+            [[maybe_unused]] const auto now = a2[0];
+            if (tt == 0) {
+                next_first(nt, buf ^ 1);
                 const int n2 = tile0(g + 2) + wave;
                 if (n2 < n_tiles)
                     load_c1(n2, c1);
+            }
+            if constexpr (UN) {
+                if (tt + kStep < NW) {
+                    read(buf, tt + kStep);
+                } else {
+                    // the next group's first products are visible, and this
+                    // group's buffer is free for the group after it
+                    __syncthreads();
+                    read(buf ^ 1, 0);
+                }
+            } else {
+                read(buf, tt);
+                if (tt + kStep >= NW)
+                    __syncthreads();
+            }
+            if (tile < n_tiles) {
+                if constexpr (UN)
+                    scan_un_tile(now, sf, top2, tile, lane);
+                else
+                    scan_pair(a2, sf, top2, tile, lane);
             }
         }
     }

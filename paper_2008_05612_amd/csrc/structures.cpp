@@ -789,14 +789,16 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
     // monomers vary), reversal-canonical (the 10 around the middle), plain 11
     // (monomers 0 .. 4 and 6, 8, .., 16; N >= 17) and plain 12 (.., 18; N >=
     // 19), see hp_internal.h.  The first product reads the scan matrix; its
-    // virtual rows are m = 0 the block term, 1 .. nb the weight of varying
-    // monomer m - 1, then the 16 varying pairs (kLow10Pairs, kMid10OddPairs for
-    // odd N canonical, kW11Pairs, kW12Pairs), and 30 and 31 the constants 1 and
-    // 64.  Lane l of tile t of wave w of the second operand holds the
-    // sequences x = 512 w + 64 t + (l & 31) and x + 32: its byte q is, for row
-    // m = 8 (q / 4) + 4 (l / 32) + q % 4, the indicator of x plus 64 times that
-    // of x + 32, and V = 32 of either sequence (no threshold yet) for the
-    // constants.
+    // virtual rows are m = 0 and 29 the block term (its ones and eights), 1 .. nb
+    // the weight of varying monomer m - 1, then the 16 varying pairs
+    // (kLow10Pairs, kMid10OddPairs for odd N canonical, kW11Pairs, kW12Pairs), and
+    // 30 and 31 the constants 9 and 1.  Lane l of tile t of wave w of the second
+    // operand holds the sequence x = 512 w + 64 t + l: its nibble n is, for the
+    // row that value n of the packed first product is (n < 16 of the lower half
+    // of the lanes, n >= 16 of the upper; value 2 i is the half's i-th register,
+    // 2 i + 1 its (8 + i)-th, register q being row 8 (q / 4) + 4 half + q % 4),
+    // the indicator of x as FP4 0.5, and for the constants the digits of V = 32
+    // (no threshold yet).
     //
     // Two-letter tables take plain blocks of 10 (wide_un): rows 0 and 29 the
     // block term, split into digits of 64, then the same rows; the weights A
@@ -850,24 +852,23 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
                 const int row_vv = 1 + wide_nb(g);
                 for (int t = 0; t < 8; ++t)
                     for (int lane = 0; lane < 64; ++lane) {
-                        const int half = lane >> 5;
-                        for (int q = 0; q < 16; ++q) {
-                            const int m = 8 * (q / 4) + 4 * half + q % 4;
-                            auto indicator = [&](int x) {
-                                if (m == 0)
-                                    return 1;
-                                if (m < row_vv)
-                                    return (x >> (m - 1)) & 1;
-                                if (m < row_vv + 16) {
-                                    const int pr = wide_pair(g, m - row_vv);
-                                    return (x >> (pr & 15)) & (x >> (pr >> 4)) & 1;
-                                }
-                                return 0;
-                            };
-                            const int x = 512 * (slot - slots[g]) + 64 * t + (lane & 31);
-                            const int v = m >= 30 ? 32 : indicator(x) + 64 * indicator(x + 32);
-                            s->wide_s2[((size_t(slot) * 8 + t) * 64 + lane) * 16 + q] =
-                                static_cast<int8_t>(v);
+                        const int x = 512 * (slot - slots[g]) + 64 * t + lane;
+                        for (int n = 0; n < 32; ++n) {
+                            const int q = n % 2 * 8 + n % 16 / 2;
+                            const int m = 8 * (q / 4) + 4 * (n / 16) + q % 4;
+                            int v = 0;   // V = 32 = 9 * 4 - 4
+                            if (m == 0 || m == 29) {
+                                v = 1;
+                            } else if (m < row_vv) {
+                                v = (x >> (m - 1)) & 1;
+                            } else if (m < row_vv + 16) {
+                                const int pr = wide_pair(g, m - row_vv);
+                                v = (x >> (pr & 15)) & (x >> (pr >> 4)) & 1;
+                            } else if (m >= 30) {
+                                v = m == 30 ? 4 : 8 + 4;
+                            }
+                            int8_t &b = s->wide_s2[((size_t(slot) * 8 + t) * 64 + lane) * 16 + n / 2];
+                            b = static_cast<int8_t>(b | (v << (n % 2 * 4)));
                         }
                     }
             }
