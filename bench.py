@@ -2,8 +2,9 @@
 """Benchmark of the HP genotype-phenotype map hot path on one MI355X.
 
 One step = the whole path over the 3x3x3 cube: ground states of all 2^27
-sequences against all 103346 conformations (block-factorised int8-MFMA form:
-energy products, min/unique/argmin epilogue, designability atomics), then the
+sequences against all 103346 conformations (block-factorised MFMA form: exact
+energy products in FP4 and FP6, threshold scan for min/unique/argmin,
+designability atomics), then the
 single-mutation neighbour counts (with the phi row of the most designable
 phenotype) and the neutral-network union-find over the full map.  Structures
 are enumerated and uploaded once before timing; all inputs are resident in
@@ -12,9 +13,10 @@ HBM.
 Roofline of the dominant kernel: the method's work per (sequence,
 conformation) pair is nbp contact products h_i h_j and their sum (Eq. 1; 28
 contacts per 3x3x3 conformation), i.e. 2 nbp integer operations, priced
-against the dense int8 MFMA peak of the contraction's data type.  What the
+against the dense peak of the type the products run in (FP4 and FP6 for
+wide blocks, int8 otherwise; "extra" has the int8 fraction too).  What the
 kernel issues instead (depth-32 products, the first product per block, the
-vector-ALU test of each product) is reported under "extra".
+vector-ALU scan of each product) is reported under "extra".
 
 Prints ONE JSON line.  Extra measurements (dense int8 and popcount forms, the
 full 6x6 map, the mixed-lattice batch, the sampling mode, per-kernel times) go
@@ -35,6 +37,7 @@ sys.path.insert(0, ROOT)
 METRIC = ("seq×structure evals/s + full-map wall time (3×3×3, 6×6); "
           "% int8 MFMA peak")
 PEAK_INT8_TOPS = 5000.0          # MI355X dense int8 MFMA, TOP/s
+PEAK_FP4_TOPS = 10000.0          # dense FP4 and FP6 MFMA, twice the int8 depth in the same time
 PEAK_VALU_TOPS = 256 * 2.4e9 * 64 / 1e12   # 32-bit VALU lane-ops/s: 256 CU x 64 lanes/clk x 2.4 GHz
 # with two VALU instructions issued per quad-cycle (gfx950 dual issue; the
 # popcount form's two-operand instructions reach it)
@@ -195,7 +198,7 @@ def main():
     achieved_tops = method_ops / (enum_ms * 1e-3) / 1e12
     # MFMA work the blocked form issues, in the time of int8 products: one
     # depth-32 product per pair (wide blocks: per two, which share an
-    # accumulator), plus the per-block first product (32 virtual rows, K_pad
+    # FP6 x FP4 product of depth 64), plus the per-block first product (32 virtual rows, K_pad
     # deep; wide blocks: ceil(K_pad / 64) FP4 steps, each in the time of an int8
     # product of depth 32) per conformation tile, once per block of 256
     # sequences, or of 1024 or 4096 for wide blocks
@@ -205,6 +208,7 @@ def main():
     blk_mfma_ops = (2.0 * 32 * pairs / (2 if blk_mode == 3 else 1) +
                     2.0 * first_depth * 32 * 32 * n_tiles * (total // block_seqs))
     evals_per_s = pairs / (ms_step * 1e-3)
+    peak = PEAK_FP4_TOPS if blk_mode == 3 else PEAK_INT8_TOPS
     src_hash = kernel_source_hash()
 
     result = {
@@ -218,11 +222,11 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "i8",
+        "dtype": "exact integers (FP6 x FP4 MFMA)" if blk_mode == 3 else "i8",
         "data": "synthetic",
         "config": {
             "workload": "3x3x3 full map: all 2^27 sequences x 103346 conformations "
-                        "(block-factorised int8-MFMA form) + single-mutation neighbour "
+                        "(block-factorised MFMA form) + single-mutation neighbour "
                         "counts + union-find",
             "lattice": "3x3x3", "N": N, "sequences": total, "n_conf": n_conf,
             "n_class": s.n_class, "K": s.K, "K_pad": s.K_pad, "nbp": s.nbp,
@@ -232,11 +236,11 @@ def main():
         "roofline": {
             "bound": "mfma",
             "achieved": achieved_tops,
-            "peak": PEAK_INT8_TOPS,
+            "peak": peak,
             "unit": "TOP/s",
-            "frac": achieved_tops / PEAK_INT8_TOPS,
+            "frac": achieved_tops / peak,
             "traffic": recorded_traffic(kname, src_hash),
-            "kernel": kname + " (hp_enumerate, blocked int8 form)",
+            "kernel": kname + " (hp_enumerate, blocked form)",
             "ops_per_unit": 2 * s.nbp,
             "unit_of_work": "one (sequence, conformation) pair: nbp contact products and "
                             "their sum (Eq. 1)",
@@ -248,6 +252,7 @@ def main():
         "full_map_ms_3x3x3": ms_step,
         "kernel_ms": {k: float(np.mean(v)) for k, v in kms.items()},
         "enumerate_evals_per_s": pairs / (enum_ms * 1e-3),
+        "blocked_int8_peak_frac": achieved_tops / PEAK_INT8_TOPS,
         # matrix-pipe utilisation: what the blocked kernel issues
         "blocked_mfma_pipe_frac": blk_mfma_ops / (enum_ms * 1e-3) / 1e12 / PEAK_INT8_TOPS,
         "blocked_mfma_ops_per_pair": blk_mfma_ops / pairs,
@@ -371,14 +376,18 @@ def extra_measurements(hp, s, ws, dev, blocked_map):
     t.stop()
     torch.cuda.synchronize()
     T, NW, mode = hp.hp_gemm_shapes(s.K_pad)[hp.hp_gemm_selected(s.K_pad)]
-    res["dense_gemm_i8_shape"] = {"T": T, "NW": NW, "mode": mode}
+    # the first shape stands for the threshold scan, which picks its own
+    scan = hp.hp_gemm_selected(s.K_pad) == 0
+    res["dense_gemm_i8_shape"] = "scan" if scan else {"T": T, "NW": NW, "mode": mode}
     res["dense_gemm_i8_full_map_ms_3x3x3"] = t.ms()
     res["dense_gemm_i8_evals_per_s"] = total * s.n_conf / (t.ms() * 1e-3)
-    # the method's work (2 nbp per pair) and the matrix pipe's (2 K_pad per
-    # pair: a dense product over every odd-separation pair row)
+    # the method's work (2 nbp per pair) and the matrix pipe's, in the time of
+    # int8 products (2 K_pad per pair: a dense product over every odd-separation
+    # pair row; the scan's FP4 products are twice as deep in that time)
+    pipe_ops = s.K_pad if scan else 2 * s.K_pad
     res["dense_gemm_i8_method_frac"] = (2.0 * s.nbp * total * s.n_conf / (t.ms() * 1e-3) /
                                         1e12 / PEAK_INT8_TOPS)
-    res["dense_gemm_i8_mfma_pipe_frac"] = (2.0 * s.K_pad * total * s.n_conf /
+    res["dense_gemm_i8_mfma_pipe_frac"] = (float(pipe_ops) * total * s.n_conf /
                                            (t.ms() * 1e-3) / 1e12 / PEAK_INT8_TOPS)
     res["blocked_map_equals_dense_map"] = bool(torch.equal(dense, blocked_map))
     # the same full map from reversal-canonical blocks only (about half the work)
@@ -491,8 +500,9 @@ def extra_measurements(hp, s, ws, dev, blocked_map):
         torch.cuda.synchronize()
         rate = nn * s6.n_conf / (t.ms() * 1e-3)
         res["6x6_block_%s_evals_per_s" % name] = rate
-    res["6x6_gemm_i8_mfma_pipe_frac"] = (res["6x6_block_gemm_i8_evals_per_s"] * 2 * s6.K_pad /
-                                         (PEAK_INT8_TOPS * 1e12))
+    res["6x6_gemm_i8_mfma_pipe_frac"] = (res["6x6_block_gemm_i8_evals_per_s"] *
+                                         (1 if hp.hp_gemm_selected(s6.K_pad) == 0 else 2) *
+                                         s6.K_pad / (PEAK_INT8_TOPS * 1e12))
     res["6x6_blocked_method_frac"] = (res["6x6_block_blocked_i8_evals_per_s"] * 2 * s6.nbp /
                                       (PEAK_INT8_TOPS * 1e12))
     del d6
