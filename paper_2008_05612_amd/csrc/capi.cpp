@@ -391,15 +391,15 @@ struct RunOpts {
 
 // Few sequences of the blocked form run faster as columns of their own (the
 // dense scan) than as blocks.  A sweep of blocks over the conformations takes
-// 0.2 us per tile whatever their number, a column 4.1e-7 us per tile and
-// product of its chain (3x3x3, chains of 5: 65536 sequences 0.44 against 0.63
-// ms, 131072 0.81 against 0.63; 6x6, 10: 20000 0.24 against 0.34 ms, 40000 0.36
-// against 0.34).  Products of two-letter tables take longer (3x3x3, chains of 3:
+// 0.15 us per tile whatever their number, a column 4.1e-7 us per tile and
+// product of its chain (3x3x3, chains of 5: 65536 sequences 0.44 against 0.49
+// ms, 80000 0.51 against 0.49; 6x6, 10: 20000 0.24 against 0.31 ms, 40000 0.36
+// against 0.31).  Products of two-letter tables take longer (3x3x3, chains of 3:
 // 50000 sequences 0.50 against 0.83 ms, 100000 0.87 against 0.83; 5x5, 50000
 // 46 against 69 us, 100000 70 against 57).  Only without a selected launch shape.
 bool blocked_small(const hp_structs *s, uint64_t n)
 {
-    return blocked_selected_mode() < 0 && n * uint64_t(s->scan_kb) <= (s->B ? 270000u : 400000u);
+    return blocked_selected_mode() < 0 && n * uint64_t(s->scan_kb) <= (s->B ? 270000u : 340000u);
 }
 
 // Launches [lo, hi) in blocks of kBlockSeqs indices.  Per-index outputs are

@@ -864,7 +864,7 @@ __device__ __forceinline__ void scan_pair(const v6i (&a2)[2], v4i (&sf)[kBlkTile
     const int any = (hit[0] | hit[1] | hit[2]) | (hit[3] | hit[4]) | (hit[5] | hit[6] | hit[7]);
     if (__builtin_expect(__any((any & kScanHit) != 0), 0)) {
         // ahead of the other waves, which will wait for this one at the group's
-        // barrier (2^24 sequences of 5x5: 1.10 ms, 1.17 without)
+        // barrier (with int8 products, 2^24 sequences of 5x5: 1.10 ms, 1.17 without)
         __builtin_amdgcn_s_setprio(2);
 #pragma unroll
         for (int t = 0; t < kBlkTiles; ++t) {
@@ -1292,7 +1292,7 @@ __global__ __launch_bounds__(256, 4) void k_gemm_wide_un_few(EnumJob j, unsigned
 // Groups of waves per block for a launch of n blocks of `waves` waves each: as
 // many as bring it to 4096 waves (16 per compute unit), at most 16 waves per
 // workgroup.  A sweep over all conformations takes a wave 1.8 ms on 3x3x3
-// however few they are; 2^17 sequences take 0.63 ms split eight ways.
+// however few they are; 2^17 sequences take 0.49 ms split eight ways.
 inline int wide_split(uint64_t n, int waves)
 {
     int s = 1;
@@ -1349,10 +1349,11 @@ hipError_t launch_wide_small(const EnumJob &j, uint64_t n, hipStream_t st)
 // Plain ranges: with `chunked`, launches of more than 2048 blocks of 1024 (4096
 // waves, 16 per compute unit) take the largest blocks the range holds; fewer
 // (or without) take blocks of 1024, which spread more evenly: 2^20 sequences of
-// 3x3x3 2.2 ms (3.5 ms in the largest blocks, one workgroup per compute unit).
+// 3x3x3 1.8 ms (3.5 ms in the largest blocks, one workgroup per compute unit);
+// 2^22 5.0 ms in the largest, 6.1 ms in blocks of 1024.
 // Boxes of few classes take k_gemm_wide_few from 384 blocks on, where its LDS
 // counts gain more than its larger workgroups lose: 5x5 with all outputs, 196
-// blocks 109 us against 68, 489 blocks 118 against 134, 977 112 against 233.
+// blocks 109 us against 69, 489 blocks 121 against 137, 977 120 against 239.
 template <int KB>
 hipError_t launch_wide(const EnumJob &j, bool chunked, hipStream_t st)
 {
