@@ -840,7 +840,8 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
         }
         s->wide_un = B > 0 && maxw <= 127 && A + 2 * B <= 127 && fmax < (1 << 13) &&
                      n_tiles <= kScanMaxTiles;
-        s->wide_ok = B == 0 && int64_t(s->blk_coef) * maxw <= 128 && s->nbp <= kScanMaxContacts &&
+        // (weights are counts of contacts, at most 5: FP6 holds 15 exactly)
+        s->wide_ok = B == 0 && maxw <= 15 * A && int64_t(s->blk_coef) * maxw <= 128 && s->nbp <= kScanMaxContacts &&
                      s->scan_kb > 0 &&
                      (s->K + 3 + 63) / 64 == (s->blk_KB + 1) / 2;
     }
