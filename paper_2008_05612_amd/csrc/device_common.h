@@ -115,13 +115,23 @@ __device__ __forceinline__ int or16(const v16i &a)
     return o | a[15];
 }
 
+// Median of three, unsigned, as the instruction, which the compiler does not
+// find beside the maximum of the same values.  It does not look into the
+// assembly either and sets no wait states between a matrix product and this
+// reader of its registers: b and c have to be results of vector instructions,
+// never an accumulator as it is.
+__device__ __forceinline__ unsigned med3_u32(unsigned a, unsigned b, unsigned c)
+{
+    unsigned m;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+    return m;
+}
+
 // The two largest of a lane's 16 accumulators by one field, unsigned, as
 // (field << 26) | row: shifting the accumulator left by 26 keeps the lower
 // field alone, by 20 the upper one above the lower (whose bits only break
 // ties).  One shift-or per register and, per two registers, v_max3, v_med3
-// and half of a v_max3; the median is written as the instruction, which the
-// compiler does not find beside the maximum of the same values (its inputs are
-// results of vector instructions, not of the matrix product).
+// and half of a v_max3.
 template <int SHIFT>
 __device__ __forceinline__ void scan_best(const v16i &a, unsigned &b, unsigned &s)
 {
@@ -134,7 +144,7 @@ __device__ __forceinline__ void scan_best(const v16i &a, unsigned &b, unsigned &
             // row of register q in this lane: 8 (q / 4) + 4 half + q % 4
             const unsigned k0 = (unsigned(a[q + 2 * p]) << SHIFT) | unsigned(2 * q + 2 * p);
             const unsigned k1 = (unsigned(a[q + 2 * p + 1]) << SHIFT) | unsigned(2 * q + 2 * p + 1);
-            asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m[p]) : "v"(b), "v"(k0), "v"(k1));
+            m[p] = med3_u32(b, k0, k1);
             b = max(max(b, k0), k1);
         }
         s = max(max(s, m[0]), m[1]);

@@ -165,21 +165,21 @@ __device__ __forceinline__ void scan_absorb_dense(const v16i &a, int T, ScanTop2
     } else {
         // T - 1/2 - F in eighths: negative where F reaches T, and the more so
         // the larger F, which unsigned order of the bits keeps; the low bits
-        // of the mantissa are 0 (F < 2^10) and take the row
+        // of the mantissa are 0 (F < 2^10) and take the row, plus one: each key
+        // is then the result of an OR, which med3_u32 needs
         unsigned b = 0, s = 0;
 #pragma unroll
         for (int q = 0; q < 16; q += 2) {
-            const unsigned r = 8 * (q / 4) + q % 4;
+            const unsigned r = 8 * (q / 4) + q % 4 + 1;
             const unsigned k0 = unsigned(a[q]) | r, k1 = unsigned(a[q + 1]) | (r + 1);
-            unsigned m;
-            asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m) : "v"(b), "v"(k0), "v"(k1));
+            const unsigned m = med3_u32(b, k0, k1);
             b = max(max(b, k0), k1);
             s = max(s, m);
         }
         auto key = [&](unsigned k) {
             const float v = __uint_as_float(k & ~31u);   // -(F - T + 1/2) / 8
             const int F = T + int(-8.0f * v);
-            return int(k) < 0 ? (unsigned(F) << kKeyConfBits) + ((k & 31) << 12) +
+            return int(k) < 0 ? (unsigned(F) << kKeyConfBits) + (((k & 31) - 1) << 12) +
                                     unsigned(4 * half << 12) + unsigned(tile + 1)
                               : 0u;
         };
