@@ -253,7 +253,14 @@ __device__ __forceinline__ void scan_dense_body(const EnumJob &j, uint64_t seq0,
             a[st] = UN ? src[st * 64] : src[st * 32];
     };
     const int scale = half ? 127 + 2 + 16 : 127 + 2;   // unit 1/4, upper field 2^16
-    auto raise = [&](int t, int now) {   // tile t's threshold in the second operand
+    // Tile t's threshold in the second operand, T[t], is that of half 0's key: the
+    // two lanes of a column have to hold the same one, since scan_absorb_dense
+    // decodes fields that either half's digits went into with the lane's own T.
+    // Other waves push to the key meanwhile, and nothing says that a read of it
+    // serves both halves at once.
+    auto raise = [&](int t, unsigned second) {
+        const auto both = __builtin_amdgcn_permlane32_swap(second, second, false, false);
+        const int now = max(int(scan_threshold(both[0])), T[t]);
         T[t] = now;
         int &w = pf[t][KB - 1].w[UN ? 5 : 3];
         if constexpr (!UN)
@@ -287,12 +294,11 @@ __device__ __forceinline__ void scan_dense_body(const EnumJob &j, uint64_t seq0,
             const int o = or16(bits);
             if (__any(UN ? o < 0 : (o & kScanPureHit) != 0)) {
                 scan_absorb_dense<UN>(bits, T[t], &mine[t * 32], UN ? p : 2 * p, half);
-                raise(t, int(scan_threshold(mine[t * 32].s)));
+                raise(t, mine[t * 32].s);
             } else if (S > 1) {
                 // what the waves that share these columns raised
-                const int now = int(scan_threshold(second[t]));
-                if (__any(now > T[t]))
-                    raise(t, max(now, T[t]));
+                if (__any(int(scan_threshold(second[t])) > T[t]))
+                    raise(t, second[t]);
             }
         }
     };
