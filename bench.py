@@ -376,8 +376,7 @@ def extra_measurements(hp, s, ws, dev, blocked_map):
     t.stop()
     torch.cuda.synchronize()
     T, NW, mode = hp.hp_gemm_shapes(s.K_pad)[hp.hp_gemm_selected(s.K_pad)]
-    # the first shape stands for the threshold scan, which picks its own
-    scan = hp.hp_gemm_selected(s.K_pad) == 0
+    scan = mode == 3   # the threshold scan picks its own launch shape
     res["dense_gemm_i8_shape"] = "scan" if scan else {"T": T, "NW": NW, "mode": mode}
     res["dense_gemm_i8_full_map_ms_3x3x3"] = t.ms()
     res["dense_gemm_i8_evals_per_s"] = total * s.n_conf / (t.ms() * 1e-3)
@@ -500,8 +499,9 @@ def extra_measurements(hp, s, ws, dev, blocked_map):
         torch.cuda.synchronize()
         rate = nn * s6.n_conf / (t.ms() * 1e-3)
         res["6x6_block_%s_evals_per_s" % name] = rate
+    scan6 = hp.hp_gemm_shapes(s6.K_pad)[hp.hp_gemm_selected(s6.K_pad)][2] == 3
     res["6x6_gemm_i8_mfma_pipe_frac"] = (res["6x6_block_gemm_i8_evals_per_s"] *
-                                         (1 if hp.hp_gemm_selected(s6.K_pad) == 0 else 2) *
+                                         (1 if scan6 else 2) *
                                          s6.K_pad / (PEAK_INT8_TOPS * 1e12))
     res["6x6_blocked_method_frac"] = (res["6x6_block_blocked_i8_evals_per_s"] * 2 * s6.nbp /
                                       (PEAK_INT8_TOPS * 1e12))

@@ -401,28 +401,30 @@ hp_status hp_autotune_blocked(const hp_structs *s, const void *d_ws, uint64_t se
                               int *best_mode, void *stream);
 
 /*
- * Tile shapes of the int8 form and their autotuning.  Several shapes are
+ * Tile shapes of the dense form and their autotuning.  Several int8 shapes are
  * compiled per product depth K_pad (hp_info.K_pad).  A shape is (T, NW, mode):
  * T sequence tiles of 32 per wave, NW waves per workgroup, and mode 0 when
  * the contact-matrix tiles are staged through LDS by the workgroup, 1 when
  * every wave loads them from global memory itself, 2 when they are staged
  * through LDS and each wave overlaps the products of one tile with the key
- * updates of the previous one.  The choice is
- * process-wide per K_pad and shared by all threads; the first listed shape is
- * the default.  With it, handles of pure pair energies and of two-letter
- * tables of small integers run the threshold scan instead, whose launch shape
- * follows the number of sequences; another shape chosen here, or found faster
- * than the scan by hp_autotune, runs in its place.  The launch configuration
- * never changes results, only speed.
- *   hp_gemm_shape_count  number of compiled shapes for K_pad (0 if none);
+ * updates of the previous one.  The last listed shape, (0, 0, 3), is the
+ * threshold scan, whose launch shape follows the number of sequences: the
+ * default.  It covers handles of pure pair energies and of two-letter tables
+ * of small integers; other handles run a compiled shape beside it, the first
+ * listed unless hp_autotune found another.  The choice is process-wide per
+ * K_pad and shared by all threads.  The launch configuration never changes
+ * results, only speed.
+ *   hp_gemm_shape_count  number of listed shapes for K_pad (0 if none);
  *   hp_gemm_shape_info   describe shape idx (any out pointer may be NULL);
- *   hp_gemm_select       make shape idx the choice for K_pad;
+ *   hp_gemm_select       make shape idx the choice for K_pad: a compiled shape
+ *                        for every handle, or (the last) the default;
  *   hp_gemm_selected     current choice for K_pad (-1 if none compiled);
  *   hp_autotune          time every shape of the handle's K_pad on sequences
  *                        [seq_lo, seq_lo + n_seq) (no outputs written,
  *                        `repeats` launches each after one warm-up), select
  *                        the fastest, write per-shape milliseconds to ms[]
- *                        (hp_gemm_shape_count entries, may be NULL) and its
+ *                        (hp_gemm_shape_count entries, may be NULL; -1 for the
+ *                        scan where it does not cover the handle) and its
  *                        index to *best (may be NULL).  Synchronises `stream`.
  *                        If the environment variable HP_TUNE_CACHE names a
  *                        file, the choice is recorded there and read back by

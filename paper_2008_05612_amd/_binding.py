@@ -487,8 +487,9 @@ def hp_components(s: Structures, phen_map, labels, compsize, ncomp=None, largest
 
 
 def hp_gemm_shapes(K_pad: int):
-    """Compiled tile shapes of the int8 form for one product depth, as
-    (T, NW, mode) tuples in library order."""
+    """Tile shapes of the dense form for one product depth, as (T, NW, mode)
+    tuples in library order: the compiled int8 shapes, then the threshold scan
+    (mode 3), the default."""
     L = library()
     out = []
     for i in range(L.hp_gemm_shape_count(K_pad)):
@@ -508,8 +509,9 @@ def hp_gemm_selected(K_pad: int) -> int:
 
 
 def hp_autotune(s: Structures, ws, seq_lo: int, n_seq: int, repeats: int = 2, stream=None):
-    """Time every compiled shape of s.K_pad on [seq_lo, seq_lo+n_seq), select the
-    fastest; returns (best index, list of milliseconds per shape)."""
+    """Time every shape of s.K_pad on [seq_lo, seq_lo+n_seq), select the fastest;
+    returns (best index, list of milliseconds per shape; -1 for the scan where
+    it does not cover the handle)."""
     import torch
     n = library().hp_gemm_shape_count(s.K_pad)
     ms = (ctypes.c_float * max(n, 1))()

@@ -422,7 +422,7 @@ hp_status run_blocks(const hp_structs *s, const void *d_ws, int form, uint64_t l
             return fail(HP_EUNSUPPORTED, "the blocked form needs N >= 8, per-block bytes "
                                          "within int8 and, with unary rows, depth <= 256");
     }
-    const bool scan = s->scan_kb > 0 && (form == HP_FORM_GEMM_I8 ? !gemm_shape_chosen(int(s->K_pad / 32))
+    const bool scan = s->scan_kb > 0 && (form == HP_FORM_GEMM_I8 ? gemm_scans(int(s->K_pad / 32))
                                                                  : blocked_small(s, hi_all - lo_all));
     for (uint64_t lo = lo_all; lo < hi_all;) {
         const uint64_t hi = hi_all - lo > kBlockSeqs ? lo + kBlockSeqs : hi_all;

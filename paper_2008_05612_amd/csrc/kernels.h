@@ -91,10 +91,11 @@ const GemmVariant *gemm_selected_variant(int KB);
 hipError_t launch_popcount(const EnumJob &j, hipStream_t st);
 // Threshold scan of the dense form (gemm_scan.h), any sequences; j.scan_kb > 0.
 hipError_t launch_scan(const EnumJob &j, hipStream_t st);
-// Whether a tile shape other than the default was chosen for product depth KB
-// (hp_gemm_select, hp_autotune): the dense form then runs that shape, else
-// the threshold scan where it applies.
-bool gemm_shape_chosen(int KB);
+// Whether the dense form runs the threshold scan at product depth KB where it
+// covers the handle (the default), or the selected tile shape for every handle
+// (hp_gemm_select, hp_autotune).
+bool gemm_scans(int KB);
+constexpr int kGemmModeScan = 3;   // the scan's entry in the list of shapes
 // Block-factorised int8 form over a plain range (pure pair energies); nw
 // waves per workgroup (2, 4 or 8), one 256-sequence block per wave; mode 0
 // stages contact tiles through double-buffered LDS, mode 1 through triple-

@@ -1,7 +1,7 @@
-// Runtime pieces of libhpmap around the int8 kernels: the registry of compiled
-// tile shapes, the process-wide shape choice per product depth (and the
-// blocked form's waves per workgroup), the autotuner that times the shapes
-// on the device, and its on-disk cache.
+// Runtime pieces of libhpmap around the matrix-core kernels: the registry of
+// compiled tile shapes, the process-wide choice per product depth between them
+// and the threshold scan (and the blocked form's waves per workgroup), the
+// autotuner that times them on the device, and its on-disk cache.
 //
 // Cache file (path in the HP_TUNE_CACHE environment variable, optional): one
 // line per depth, "gfx950 <K_pad> <T> <NW> <mode>", written by hp_autotune and
@@ -25,16 +25,15 @@ namespace {
 
 struct Registry {
     std::vector<GemmVariant> by_kb[kMaxKB + 1];
-    std::atomic<int> selected[kMaxKB + 1];
-    std::atomic<bool> chosen[kMaxKB + 1];   // not the default shape: runs instead of the scan
+    // 2 shape + 1 while the threshold scan runs where it covers the handle, the
+    // shape serving the other handles; 2 shape where the shape serves them all
+    std::atomic<int> choice[kMaxKB + 1];
     std::once_flag cache_once;
 
     Registry()
     {
-        for (auto &s : selected)
-            s.store(0);
-        for (auto &c : chosen)
-            c.store(false);
+        for (auto &c : choice)
+            c.store(1);
         int (*groups[])(const GemmVariant **) = {gemm_variants_kb1_4, gemm_variants_kb5,
                                                  gemm_variants_kb6_10, gemm_variants_kb11_12};
         for (auto g : groups) {
@@ -80,7 +79,7 @@ void load_cache()
             continue;
         const int idx = find_shape(KB, T, NW, mode);
         if (idx >= 0)   // the best of the shapes; the scan still runs where it applies
-            registry().selected[KB].store(idx);
+            registry().choice[KB].store(2 * idx + 1);
     }
     std::fclose(f);
 }
@@ -123,19 +122,16 @@ const GemmVariant *gemm_selected_variant(int KB)
     const auto &v = r.by_kb[KB];
     if (v.empty())
         return nullptr;
-    int idx = r.selected[KB].load();
-    if (idx < 0 || idx >= int(v.size()))
-        idx = 0;
-    return &v[idx];
+    return &v[r.choice[KB].load() >> 1];
 }
 
-bool gemm_shape_chosen(int KB)
+bool gemm_scans(int KB)
 {
     if (KB < 1 || KB > kMaxKB)
         return false;
     Registry &r = registry();
     std::call_once(r.cache_once, load_cache);
-    return r.chosen[KB].load();
+    return r.choice[KB].load() & 1;
 }
 
 namespace {
@@ -177,7 +173,8 @@ int hp_gemm_shape_count(uint32_t K_pad)
 {
     if (K_pad % 32 != 0 || K_pad / 32 < 1 || K_pad / 32 > uint32_t(kMaxKB))
         return 0;
-    return int(registry().by_kb[K_pad / 32].size());
+    const int n = int(registry().by_kb[K_pad / 32].size());
+    return n ? n + 1 : 0;   // the compiled shapes, then the scan
 }
 
 hp_status hp_gemm_shape_info(uint32_t K_pad, int idx, int *T, int *NW, int *mode)
@@ -185,7 +182,8 @@ hp_status hp_gemm_shape_info(uint32_t K_pad, int idx, int *T, int *NW, int *mode
     const int n = hp_gemm_shape_count(K_pad);
     if (idx < 0 || idx >= n)
         return fail(HP_EINVAL, "no such tile shape for this K_pad");
-    const GemmVariant &v = registry().by_kb[K_pad / 32][idx];
+    const GemmVariant scan{int(K_pad / 32), 0, 0, kGemmModeScan, launch_scan};
+    const GemmVariant &v = idx == n - 1 ? scan : registry().by_kb[K_pad / 32][idx];
     if (T)
         *T = v.T;
     if (NW)
@@ -202,18 +200,19 @@ hp_status hp_gemm_select(uint32_t K_pad, int idx)
         return fail(HP_EINVAL, "no such tile shape for this K_pad");
     Registry &r = registry();
     std::call_once(r.cache_once, load_cache);
-    r.selected[K_pad / 32].store(idx);
-    r.chosen[K_pad / 32].store(idx != 0);
+    r.choice[K_pad / 32].store(idx == n - 1 ? 1 : 2 * idx);
     return HP_OK;
 }
 
 int hp_gemm_selected(uint32_t K_pad)
 {
-    if (hp_gemm_shape_count(K_pad) == 0)
+    const int n = hp_gemm_shape_count(K_pad);
+    if (n == 0)
         return -1;
     Registry &r = registry();
     std::call_once(r.cache_once, load_cache);
-    return r.selected[K_pad / 32].load();
+    const int c = r.choice[K_pad / 32].load();
+    return c & 1 ? n - 1 : c >> 1;
 }
 
 hp_status hp_autotune(const hp_structs *s, const void *d_ws, uint64_t seq_lo, uint64_t n_seq,
@@ -234,10 +233,9 @@ hp_status hp_autotune(const hp_structs *s, const void *d_ws, uint64_t seq_lo, ui
     hipError_t err = hipEventCreate(&e0);
     if (err == hipSuccess)
         err = hipEventCreate(&e1);
+    // best_idx: of the compiled shapes; the threshold scan is timed last
     int best_idx = -1;
-    float best_ms = 0.f, scan_ms = 0.f;
-    // the shapes, and last the threshold scan, which no shape replaces where
-    // it is faster
+    float best_ms = 0.f, scan_ms = -1.f;
     const size_t n_run = vars.size() + (s->scan_kb > 0 ? 1 : 0);
     for (size_t i = 0; i < n_run && err == hipSuccess; ++i) {
         EnumJob j = make_enum_job(s, d_ws, seq_lo, seq_lo + n_seq, nullptr, nullptr, nullptr,
@@ -276,11 +274,13 @@ hp_status hp_autotune(const hp_structs *s, const void *d_ws, uint64_t seq_lo, ui
         return fail(HP_EDEVICE, std::string("hp_autotune: ") + hipGetErrorString(err));
     Registry &r = registry();
     std::call_once(r.cache_once, load_cache);
-    r.selected[KB].store(best_idx);
-    r.chosen[KB].store(best_idx != 0 && !(s->scan_kb > 0 && scan_ms <= best_ms));
+    const bool scan = s->scan_kb > 0 && scan_ms < best_ms;
+    r.choice[KB].store(2 * best_idx + (scan ? 1 : 0));
     store_cache(KB, vars[best_idx]);
+    if (ms)
+        ms[vars.size()] = scan_ms;
     if (best)
-        *best = best_idx;
+        *best = scan ? int(vars.size()) : best_idx;
     return HP_OK;
 }
 
