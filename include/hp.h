@@ -428,7 +428,10 @@ hp_status hp_autotune_blocked(const hp_structs *s, const void *d_ws, uint64_t se
  *                        index to *best (may be NULL).  Synchronises `stream`.
  *                        If the environment variable HP_TUNE_CACHE names a
  *                        file, the choice is recorded there and read back by
- *                        later processes on first use of that K_pad.
+ *                        later processes on first use of that K_pad: the
+ *                        fastest compiled shape, and whether the scan was
+ *                        faster (a record of a library without the scan does
+ *                        not say, and leaves it on).
  * Errors: HP_EINVAL for an unknown shape, NULL handle/workspace or a range
  * outside [0, 2^N); HP_EDEVICE for a failed launch.
  */

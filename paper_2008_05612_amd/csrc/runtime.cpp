@@ -4,8 +4,11 @@
 // autotuner that times them on the device, and its on-disk cache.
 //
 // Cache file (path in the HP_TUNE_CACHE environment variable, optional): one
-// line per depth, "gfx950 <K_pad> <T> <NW> <mode>", written by hp_autotune and
-// read the first time a depth is launched.
+// line per depth, "gfx950 <K_pad> <T> <NW> <mode> <scan>", the fastest compiled
+// shape and whether the scan was faster (1) or that shape serves every handle
+// (0), written by hp_autotune and read the first time a depth is launched.  A
+// line without the last field comes from shapes timed without the scan, and
+// leaves the scan on.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -69,22 +72,24 @@ void load_cache()
     FILE *f = std::fopen(path, "r");
     if (!f)
         return;
-    char arch[32];
-    int kpad, T, NW, mode;
-    while (std::fscanf(f, "%31s %d %d %d %d", arch, &kpad, &T, &NW, &mode) == 5) {
-        if (std::strcmp(arch, "gfx950") != 0 || kpad % 32 != 0)
+    char line[256];
+    while (std::fgets(line, sizeof line, f)) {
+        char arch[32];
+        int kpad, T, NW, mode, scan = 1;
+        if (std::sscanf(line, "%31s %d %d %d %d %d", arch, &kpad, &T, &NW, &mode, &scan) < 5 ||
+            std::strcmp(arch, "gfx950") != 0 || kpad % 32 != 0)
             continue;
         const int KB = kpad / 32;
         if (KB < 1 || KB > kMaxKB)
             continue;
         const int idx = find_shape(KB, T, NW, mode);
-        if (idx >= 0)   // the best of the shapes; the scan still runs where it applies
-            registry().choice[KB].store(2 * idx + 1);
+        if (idx >= 0)
+            registry().choice[KB].store(2 * idx + (scan != 0 ? 1 : 0));
     }
     std::fclose(f);
 }
 
-void store_cache(int KB, const GemmVariant &v)
+void store_cache(int KB, const GemmVariant &v, bool scan)
 {
     const char *path = std::getenv("HP_TUNE_CACHE");
     if (!path || !*path)
@@ -106,7 +111,7 @@ void store_cache(int KB, const GemmVariant &v)
     if (FILE *f = std::fopen(path, "w")) {
         for (const auto &l : keep)
             std::fputs(l.c_str(), f);
-        std::fprintf(f, "gfx950 %d %d %d %d\n", KB * 32, v.T, v.NW, v.mode);
+        std::fprintf(f, "gfx950 %d %d %d %d %d\n", KB * 32, v.T, v.NW, v.mode, int(scan));
         std::fclose(f);
     }
 }
@@ -276,7 +281,7 @@ hp_status hp_autotune(const hp_structs *s, const void *d_ws, uint64_t seq_lo, ui
     std::call_once(r.cache_once, load_cache);
     const bool scan = s->scan_kb > 0 && scan_ms < best_ms;
     r.choice[KB].store(2 * best_idx + (scan ? 1 : 0));
-    store_cache(KB, vars[best_idx]);
+    store_cache(KB, vars[best_idx], scan);
     if (ms)
         ms[vars.size()] = scan_ms;
     if (best)

@@ -1,0 +1,35 @@
+"""Autotuning and the choices that it leaves: what it recorded is what a later
+process reads."""
+import pytest
+
+import paper_2008_05612_amd as hp
+from tests.conftest import gpu_available
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not gpu_available():
+        pytest.skip("no GPU")
+
+
+def test_autotune_records_its_choice(tmp_path, monkeypatch):
+    import torch
+    s = hp.Structures(5, 5, 1)
+    shapes = hp.hp_gemm_shapes(s.K_pad)
+    keep = hp.hp_gemm_selected(s.K_pad)
+    cache = tmp_path / "tuned"
+    cache.write_text("gfx950 %d 1 1 1\ngfx950 32 4 4 0\n" % s.K_pad)   # its depth, and another
+    monkeypatch.setenv("HP_TUNE_CACHE", str(cache))
+    try:
+        print("autotune", s.K_pad, flush=True)
+        best, ms = hp.hp_autotune(s, s.workspace(), 0, 1 << 16, repeats=1)
+        torch.cuda.synchronize()
+    finally:
+        hp.hp_gemm_select(s.K_pad, keep)
+    compiled = ms[:-1].index(min(ms[:-1]))
+    assert best == (len(shapes) - 1 if ms[-1] < ms[compiled] else compiled)
+    assert cache.read_text().splitlines() == [
+        "gfx950 32 4 4 0",
+        "gfx950 %d %d %d %d %d" % ((s.K_pad,) + shapes[compiled] + (best == len(shapes) - 1,))]

@@ -4,6 +4,8 @@ compiled shape, the first among them, can be selected in its place.
 """
 import ctypes
 import os
+import subprocess
+import sys
 
 import pytest
 
@@ -37,3 +39,27 @@ def test_every_listed_shape_can_be_selected(scans, K_pad):
     for bad in (-1, len(shapes)):
         with pytest.raises(hp.HPError):
             hp.hp_gemm_select(K_pad, bad)
+
+
+_READ_BACK = """
+import ctypes, paper_2008_05612_amd as hp
+fn = getattr(hp.library(), "_ZN5hpmap10gemm_scansEi")
+fn.restype = ctypes.c_bool
+print(hp.hp_gemm_selected(160), fn(5), hp.hp_gemm_selected(192), fn(6))
+"""
+
+
+# A record of hp_autotune says whether its shape was faster than the scan; one
+# without that field was timed without the scan.  A line of another kind is passed
+# over.
+@pytest.mark.parametrize("field,scan", [(" 0", False), (" 1", True), ("", True)])
+def test_recorded_choice_is_read_back(tmp_path, field, scan):
+    shapes = hp.hp_gemm_shapes(160)
+    cache = tmp_path / "tuned"
+    cache.write_text("# shapes\ngfx950 160 %d %d %d%s\n" % (shapes[2] + (field,)))
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", _READ_BACK], capture_output=True, text=True,
+                         cwd=root, env=dict(os.environ, HP_TUNE_CACHE=str(cache)))
+    assert out.returncode == 0, out.stderr
+    other = len(hp.hp_gemm_shapes(192)) - 1
+    assert out.stdout.split() == [str(len(shapes) - 1 if scan else 2), str(scan), str(other), "True"]
