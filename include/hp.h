@@ -431,7 +431,9 @@ hp_status hp_autotune_blocked(const hp_structs *s, const void *d_ws, uint64_t se
  *                        later processes on first use of that K_pad: the
  *                        fastest compiled shape, and whether the scan was
  *                        faster (a record of a library without the scan does
- *                        not say, and leaves it on).
+ *                        not say, and leaves it on).  A handle that the scan does
+ *                        not cover is given the fastest compiled shape beside
+ *                        it; the scan stays the choice of the others.
  * Errors: HP_EINVAL for an unknown shape, NULL handle/workspace or a range
  * outside [0, 2^N); HP_EDEVICE for a failed launch.
  */

@@ -31,12 +31,15 @@ struct Registry {
     // 2 shape + 1 while the threshold scan runs where it covers the handle, the
     // shape serving the other handles; 2 shape where the shape serves them all
     std::atomic<int> choice[kMaxKB + 1];
+    std::atomic<int> tuned[kMaxKB + 1];   // the shape beside the scan: timed fastest, or the first
     std::once_flag cache_once;
 
     Registry()
     {
         for (auto &c : choice)
             c.store(1);
+        for (auto &t : tuned)
+            t.store(0);
         int (*groups[])(const GemmVariant **) = {gemm_variants_kb1_4, gemm_variants_kb5,
                                                  gemm_variants_kb6_10, gemm_variants_kb11_12};
         for (auto g : groups) {
@@ -83,8 +86,10 @@ void load_cache()
         if (KB < 1 || KB > kMaxKB)
             continue;
         const int idx = find_shape(KB, T, NW, mode);
-        if (idx >= 0)
+        if (idx >= 0) {
+            registry().tuned[KB].store(idx);
             registry().choice[KB].store(2 * idx + (scan != 0 ? 1 : 0));
+        }
     }
     std::fclose(f);
 }
@@ -205,7 +210,7 @@ hp_status hp_gemm_select(uint32_t K_pad, int idx)
         return fail(HP_EINVAL, "no such tile shape for this K_pad");
     Registry &r = registry();
     std::call_once(r.cache_once, load_cache);
-    r.choice[K_pad / 32].store(idx == n - 1 ? 1 : 2 * idx);
+    r.choice[K_pad / 32].store(idx == n - 1 ? 2 * r.tuned[K_pad / 32].load() + 1 : 2 * idx);
     return HP_OK;
 }
 
@@ -279,13 +284,17 @@ hp_status hp_autotune(const hp_structs *s, const void *d_ws, uint64_t seq_lo, ui
         return fail(HP_EDEVICE, std::string("hp_autotune: ") + hipGetErrorString(err));
     Registry &r = registry();
     std::call_once(r.cache_once, load_cache);
-    const bool scan = s->scan_kb > 0 && scan_ms < best_ms;
+    // a handle that the scan does not cover says nothing about the scan, which
+    // other handles of this depth run
+    const bool covered = s->scan_kb > 0;
+    const bool scan = covered ? scan_ms < best_ms : (r.choice[KB].load() & 1) != 0;
+    r.tuned[KB].store(best_idx);
     r.choice[KB].store(2 * best_idx + (scan ? 1 : 0));
     store_cache(KB, vars[best_idx], scan);
     if (ms)
         ms[vars.size()] = scan_ms;
     if (best)
-        *best = scan ? int(vars.size()) : best_idx;
+        *best = covered && scan ? int(vars.size()) : best_idx;
     return HP_OK;
 }
 

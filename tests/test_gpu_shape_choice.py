@@ -1,5 +1,8 @@
 """Autotuning and the choices that it leaves: what it recorded is what a later
-process reads."""
+process reads, and a handle that the scan does not cover leaves the scan to the
+others."""
+import ctypes
+
 import pytest
 
 import paper_2008_05612_amd as hp
@@ -33,3 +36,30 @@ def test_autotune_records_its_choice(tmp_path, monkeypatch):
     assert cache.read_text().splitlines() == [
         "gfx950 32 4 4 0",
         "gfx950 %d %d %d %d %d" % ((s.K_pad,) + shapes[compiled] + (best == len(shapes) - 1,))]
+
+
+class _Variant(ctypes.Structure):
+    _fields_ = [("KB", ctypes.c_int), ("T", ctypes.c_int), ("NW", ctypes.c_int),
+                ("mode", ctypes.c_int)]
+
+
+def test_autotune_of_an_uncovered_table_leaves_the_scan_on():
+    import torch
+    scans = getattr(hp.library(), "_ZN5hpmap10gemm_scansEi")
+    scans.restype = ctypes.c_bool
+    variant = getattr(hp.library(), "_ZN5hpmap21gemm_selected_variantEi")
+    variant.restype = ctypes.POINTER(_Variant)
+    s = hp.Structures(5, 5, 1, table=(0, -32, -32, -72))     # B > 15
+    assert s.K_pad == hp.Structures(3, 3, 3).K_pad           # which the scan covers
+    shapes = hp.hp_gemm_shapes(s.K_pad)
+    keep = hp.hp_gemm_selected(s.K_pad)
+    assert keep == len(shapes) - 1
+    print("autotune", s.K_pad, flush=True)
+    best, ms = hp.hp_autotune(s, s.workspace(), 0, 1 << 16, repeats=1)
+    torch.cuda.synchronize()
+    assert ms[-1] == -1 and ms[best] == min(ms[:-1])
+    hp.hp_gemm_select(s.K_pad, 0)
+    hp.hp_gemm_select(s.K_pad, keep)      # as a caller that keeps and restores the choice
+    v = variant(s.K_pad // 32).contents
+    assert (v.T, v.NW, v.mode) == shapes[best]
+    assert hp.hp_gemm_selected(s.K_pad) == keep and scans(s.K_pad // 32)
