@@ -376,8 +376,9 @@ hp_status hp_enumerate_batch_static(const hp_job *jobs, int njobs, int form, voi
  * 4 and 6, 8, .., 16) in the other whole chunks of 2^17 where N >= 17; blocks
  * of 1024 throughout with two-letter tables.  Plain ranges only, elsewhere
  * mode 3 acts as -1; -1, default: 3 with 8 waves where wide blocks apply, else
- * 2 for K_pad <= 192, else 0).  With mode -1 few sequences run as columns of
- * the dense scan instead: up to 3.4e5 / ceil(K_pad / 32), with two-letter tables
+ * 2 for K_pad <= 192, else 0).  With mode -1, or the
+ * shape that hp_autotune_blocked found, few sequences run as columns of the
+ * dense scan instead: up to 3.4e5 / ceil(K_pad / 32), with two-letter tables
  * 2.7e5 / ceil(K_pad / 64).  hp_blocked_selected
  * reports them (either pointer may be NULL).  Results never depend on the
  * shape.

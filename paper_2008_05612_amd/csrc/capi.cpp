@@ -396,10 +396,11 @@ struct RunOpts {
 // ms, 80000 0.51 against 0.49; 6x6, 10: 20000 0.24 against 0.31 ms, 40000 0.36
 // against 0.31).  Products of two-letter tables take longer (3x3x3, chains of 3:
 // 50000 sequences 0.50 against 0.83 ms, 100000 0.87 against 0.83; 5x5, 50000
-// 46 against 69 us, 100000 70 against 57).  Only without a selected launch shape.
+// 46 against 69 us, 100000 70 against 57).  Not where a caller selected the launch
+// shape; the one that hp_autotune_blocked found is the fastest among blocks.
 bool blocked_small(const hp_structs *s, uint64_t n)
 {
-    return blocked_selected_mode() < 0 && n * uint64_t(s->scan_kb) <= (s->B ? 270000u : 340000u);
+    return !blocked_shape_chosen() && n * uint64_t(s->scan_kb) <= (s->B ? 270000u : 340000u);
 }
 
 // Launches [lo, hi) in blocks of kBlockSeqs indices.  Per-index outputs are

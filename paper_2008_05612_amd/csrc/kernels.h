@@ -139,6 +139,9 @@ hipError_t launch_gemm_blk_batch(void *d_batch_ws, int kb, bool unary, int wide,
 // Process-wide launch shape of the blocked form (runtime.cpp).
 int blocked_selected_nw();
 int blocked_selected_mode();
+// Whether a caller selected that mode, for every range; one that
+// hp_autotune_blocked found leaves few sequences to the dense scan.
+bool blocked_shape_chosen();
 // Sequences per work item of the dense persistent batched kernel.
 uint64_t gemm_batch_seqs_per_item();
 // Persistent launch over items [item_lo, item_hi) of the work list at

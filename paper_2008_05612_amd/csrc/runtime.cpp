@@ -147,10 +147,12 @@ bool gemm_scans(int KB)
 namespace {
 std::atomic<int> g_blocked_nw{4};     // waves per workgroup of the blocked form
 std::atomic<int> g_blocked_mode{-1};  // its staging mode; -1: by product depth
+std::atomic<bool> g_blocked_chosen{false};   // that mode was selected, not timed
 }
 
 int blocked_selected_nw() { return g_blocked_nw.load(); }
 int blocked_selected_mode() { return g_blocked_mode.load(); }
+bool blocked_shape_chosen() { return g_blocked_chosen.load(); }
 
 }  // namespace hpmap
 
@@ -168,6 +170,7 @@ hp_status hp_blocked_select(int nw, int mode)
         return fail(HP_EINVAL, "blocked form: wide blocks (mode 3) run 4 or 8 waves per workgroup");
     g_blocked_nw.store(nw);
     g_blocked_mode.store(mode);
+    g_blocked_chosen.store(mode >= 0);
     return HP_OK;
 }
 
@@ -357,6 +360,7 @@ hp_status hp_autotune_blocked(const hp_structs *s, const void *d_ws, uint64_t se
     const int bnw = bi < 9 ? kNW[bi / 3] : 8, bmode = bi < 9 ? bi % 3 : 3;
     g_blocked_nw.store(bnw);
     g_blocked_mode.store(bmode);
+    g_blocked_chosen.store(false);
     if (best_nw)
         *best_nw = bnw;
     if (best_mode)

@@ -1,6 +1,6 @@
 """Autotuning and the choices that it leaves: what it recorded is what a later
-process reads, and a handle that the scan does not cover leaves the scan to the
-others."""
+process reads, a handle that the scan does not cover leaves the scan to the
+others, and a tuned blocked form still hands few sequences to the scan."""
 import ctypes
 
 import pytest
@@ -63,3 +63,23 @@ def test_autotune_of_an_uncovered_table_leaves_the_scan_on():
     v = variant(s.K_pad // 32).contents
     assert (v.T, v.NW, v.mode) == shapes[best]
     assert hp.hp_gemm_selected(s.K_pad) == keep and scans(s.K_pad // 32)
+
+
+def test_tuned_blocks_leave_few_sequences_to_the_scan():
+    import torch
+    chosen = getattr(hp.library(), "_ZN5hpmap20blocked_shape_chosenEv")
+    chosen.restype = ctypes.c_bool
+    keep = hp.hp_blocked_selected()
+    assert keep == (4, -1) and not chosen()
+    try:
+        hp.hp_blocked_select(4, 3)
+        assert chosen()
+        s = hp.Structures(5, 5, 1)
+        print("autotune blocked", s.K_pad, flush=True)
+        (nw, mode), _ = hp.hp_autotune_blocked(s, s.workspace(), 0, 1 << 18, repeats=1)
+        torch.cuda.synchronize()
+        assert mode >= 0 and hp.hp_blocked_selected() == (nw, mode)
+        assert not chosen()
+    finally:
+        hp.hp_blocked_select(*keep)
+    assert not chosen()
