@@ -11,7 +11,7 @@
 namespace emu {
 
 unsigned lane_id;
-dim3 block_dim, block_idx;
+dim3 block_dim, block_idx, grid_dim;
 
 namespace {
 
@@ -27,6 +27,8 @@ struct Fiber {
     unsigned from;
     v8i a, b;
     v16f c;
+    v4i ai, bi;
+    v16i ci;
     int fmt_a, fmt_b, scale_a, scale_b;
 };
 
@@ -90,6 +92,24 @@ void product(Fiber *w)
         }
 }
 
+void product_i8(Fiber *w)
+{
+    static int A[32][32], B[32][32];
+    for (int l = 0; l < 64; ++l)
+        for (int n = 0; n < 16; ++n) {
+            A[l % 32][16 * (l / 32) + n] = int8_t(uint32_t(w[l].ai[n / 4]) >> (8 * (n % 4)));
+            B[16 * (l / 32) + n][l % 32] = int8_t(uint32_t(w[l].bi[n / 4]) >> (8 * (n % 4)));
+        }
+    for (int l = 0; l < 64; ++l)
+        for (int q = 0; q < 16; ++q) {
+            const int row = 8 * (q / 4) + 4 * (l / 32) + q % 4;
+            int sum = w[l].ci[q];
+            for (int k = 0; k < 32; ++k)
+                sum += A[row][k] * B[k][l % 32];
+            w[l].ci[q] = sum;
+        }
+}
+
 void finish(Fiber *w)
 {
     if (w[0].op == 0) {
@@ -101,8 +121,10 @@ void finish(Fiber *w)
     } else if (w[0].op == 1) {
         for (int l = 0; l < 64; ++l)
             w[l].result = w[w[l].from].word;
-    } else {
+    } else if (w[0].op == 2) {
         product(w);
+    } else {
+        product_i8(w);
     }
 }
 
@@ -130,6 +152,42 @@ v16f mfma_scale(const v8i &a, const v8i &b, const v16f &c, int fmt_a, int fmt_b,
     f.a = a, f.b = b, f.c = c;
     f.fmt_a = fmt_a, f.fmt_b = fmt_b, f.scale_a = scale_a, f.scale_b = scale_b;
     return wait(kAtWave, 2).c;
+}
+
+v16i mfma_i8(const v4i &a, const v4i &b, const v16i &c)
+{
+    Fiber &f = fibers[lane_id];
+    f.ai = a, f.bi = b, f.ci = c;
+    return wait(kAtWave, 3).ci;
+}
+
+unsigned byte_permute(unsigned upper, unsigned lower, unsigned select)
+{
+    const uint64_t bytes = uint64_t(upper) << 32 | lower;
+    unsigned r = 0;
+    for (int i = 0; i < 4; ++i) {
+        const unsigned s = (select >> (8 * i)) & 255u;
+        r |= (s < 8 ? unsigned(bytes >> (8 * s)) & 255u : 0u) << (8 * i);
+    }
+    return r;
+}
+
+v6u to_fp6(const v16f &even, const v16f &odd, float scale)
+{
+    v6u r = {};
+    for (int n = 0; n < 32; ++n) {
+        const float x = (n % 2 ? odd : even)[n / 2] / scale;
+        const float m = std::fabs(x);
+        unsigned code = m < 2.f   ? unsigned(std::nearbyint(m * 8.f))
+                        : m < 4.f ? 16u + unsigned(std::nearbyint((m - 2.f) * 4.f))
+                                  : 24u + unsigned(std::nearbyint((m - 4.f) * 2.f));
+        code = std::min(code, 31u) | (x < 0 ? 32u : 0u);
+        const int bit = 6 * n;
+        r[bit / 32] |= code << (bit % 32);
+        if (bit % 32 > 26)
+            r[bit / 32 + 1] |= code >> (32 - bit % 32);
+    }
+    return r;
 }
 
 void run(unsigned threads, uint64_t seed, const std::function<void()> &body)

@@ -24,7 +24,7 @@
 
 typedef int hipError_t;
 typedef void *hipStream_t;
-constexpr hipError_t hipSuccess = 0;
+constexpr hipError_t hipSuccess = 0, hipErrorInvalidValue = 1;
 inline hipError_t hipGetLastError() { return hipSuccess; }
 struct dim3 {
     unsigned x, y, z;
@@ -34,10 +34,13 @@ struct dim3 {
 namespace emu {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef unsigned v6u __attribute__((ext_vector_type(6)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 extern unsigned lane_id;          // thread index of the running lane
-extern dim3 block_dim, block_idx;
+extern dim3 block_dim, block_idx, grid_dim;
 struct Lane {
     unsigned x;
 };
@@ -48,6 +51,9 @@ uint64_t ballot(bool on);
 uint64_t exchange(uint64_t own, unsigned from);   // `own` of the wave's lane `from`
 v16f mfma_scale(const v8i &a, const v8i &b, const v16f &c, int fmt_a, int fmt_b, int scale_a,
                 int scale_b);
+v16i mfma_i8(const v4i &a, const v4i &b, const v16i &c);
+v6u to_fp6(const v16f &even, const v16f &odd, float scale);   // values in turn, divided by scale
+unsigned byte_permute(unsigned upper, unsigned lower, unsigned select);
 
 // Runs `body` on every lane of a workgroup of `threads`, in the order of `seed`.
 void run(unsigned threads, uint64_t seed, const std::function<void()> &body);
@@ -57,6 +63,7 @@ void run(unsigned threads, uint64_t seed, const std::function<void()> &body);
 #define threadIdx emu::lane()
 #define blockDim emu::block_dim
 #define blockIdx emu::block_idx
+#define gridDim emu::grid_dim
 
 inline void __syncthreads() { emu::workgroup_barrier(); }
 inline uint64_t __ballot(bool on) { return emu::ballot(on); }
@@ -69,6 +76,16 @@ inline int __shfl_xor(int v, int mask)
     return int(emu::exchange(uint32_t(v), ((emu::lane_id & 63u) ^ unsigned(mask)) & 63u));
 }
 inline float __uint_as_float(unsigned x) { return __builtin_bit_cast(float, x); }
+
+struct int2 {
+    int x, y;
+};
+struct uint2 {
+    unsigned x, y;
+};
+struct uint4 {
+    unsigned x, y, z, w;
+};
 
 inline int min(int a, int b) { return a < b ? a : b; }
 inline int max(int a, int b) { return a > b ? a : b; }
@@ -96,5 +113,14 @@ inline std::array<unsigned, 2> __builtin_amdgcn_permlane32_swap(unsigned a, unsi
     const unsigned lower = unsigned(emu::exchange(a, col));
     return {lower, unsigned(emu::exchange(a, col + 32))};
 }
+inline int __builtin_amdgcn_readfirstlane(int v) { return int(emu::exchange(uint32_t(v), 0)); }
+inline void __builtin_amdgcn_s_waitcnt(int) {}
+inline void __builtin_amdgcn_s_setprio(int) {}
+inline void __builtin_amdgcn_sched_group_barrier(int, int, int) {}
+inline void __builtin_amdgcn_sched_barrier(int) {}
+inline void __builtin_amdgcn_wave_barrier() {}
+#define __builtin_amdgcn_perm emu::byte_permute
+#define __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32 emu::to_fp6
+#define __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, x, y, z) emu::mfma_i8(a, b, c)
 #define __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, fa, fb, oa, sa, ob, sb) \
     emu::mfma_scale(a, b, c, fa, fb, sa, sb)
