@@ -60,18 +60,24 @@ typedef enum {
 
 /* Energy-kernel forms (all give bit-identical results). */
 #define HP_FORM_POPCOUNT 0  /* contact bitmasks, AND + popcount per pair        */
-#define HP_FORM_GEMM_I8 1   /* E = -P.C as an int8 matrix product on MFMA cores */
-/* Block-factorised int8 form: each block of 256 consecutive sequences shares
- * every monomer above the low 8, so per conformation the energy is a block
- * term plus weights of the 8 low monomers and their mutual contacts; one
- * int8 product per 256 sequences forms those (as bytes), a second product of
- * depth 32 applies them to the sequences.  Two-letter tables (E_HP !=
- * E_PP) add the unary terms of the outer monomers as a few more per-block
- * rows.  Needs N >= 8 and weights whose per-block bytes fit int8 within 32
- * rows, and with unary rows a first product at most 256 deep (pure HP on
- * every box up to 6x6 and 3x3x3 qualifies, Table 1 up to 3x3x3 but not 6x6;
- * hp_canonical_block_count is 0 when a handle does not); only plain ranges
- * (hp_enumerate, hp_enumerate_gap).  Otherwise HP_EUNSUPPORTED.           */
+#define HP_FORM_GEMM_I8 1   /* E = -P.C as a matrix product on MFMA cores       */
+/* The dense form runs as a threshold scan in FP4 / FP6 where it applies, else
+ * in int8 (hp_gemm_select).  Products and sums are whole numbers that the
+ * types used hold exactly, so "I8" is the name of the form, not a precision.
+ *
+ * Block-factorised form: each block of sequences shares every monomer but a
+ * few, so per conformation the energy is a block term plus weights of the
+ * varying monomers and their mutual contacts; one product per block forms
+ * those, a second product of depth 32 applies them to the sequences.  Wide
+ * blocks of 1024 to 4096 sequences run as a threshold scan (pure pair
+ * energies in FP4 / FP6, two-letter tables in int8), blocks of 256 in int8
+ * (hp_blocked_select).  Two-letter tables (E_HP != E_PP) add the unary terms
+ * of the outer monomers, in blocks of 256 as a few more per-block rows.
+ * Needs N >= 8 and weights whose per-block bytes, in blocks of 256, fit int8
+ * within 32 rows, and with unary rows a first product at most 256 deep (pure
+ * HP on every box up to 6x6 and 3x3x3 qualifies, Table 1 up to 3x3x3 but not
+ * 6x6; hp_canonical_block_count is 0 when a handle does not); only plain
+ * ranges (hp_enumerate, hp_enumerate_gap).  Otherwise HP_EUNSUPPORTED.    */
 #define HP_FORM_BLOCKED_I8 2
 
 typedef struct hp_structs hp_structs;
@@ -133,8 +139,8 @@ hp_status hp_structs_export(const hp_structs *s, uint8_t *walks, uint16_t *conf_
 /*
  * Device workspace holding the packed structure tables the kernel forms
  * read (contact bitmasks, the int8 contact matrix in MFMA operand order, the
- * blocked form's 0/1 contact matrix where it applies, the pair table and the
- * conformation-to-class map).  hp_workspace_bytes gives
+ * blocked form's 0/1 contact matrix and the scans' FP4 one where they apply,
+ * the pair table and the conformation-to-class map).  hp_workspace_bytes gives
  * its size; hp_upload fills caller memory d_ws (>= that many bytes, 256-byte
  * aligned) asynchronously on `stream`.  The host source stays owned by the
  * handle, so the handle must outlive the copy (synchronise before freeing).

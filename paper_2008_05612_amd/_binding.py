@@ -332,14 +332,14 @@ def hp_sample(s: Structures, ws, form: int, seed: int, idx_lo: int, idx_hi: int,
 
 
 def hp_blocked_select(nw: int, mode: int = -1):
-    """Launch shape of the blocked int8 form: waves per workgroup (2, 4 or 8)
+    """Launch shape of the blocked form: waves per workgroup (2, 4 or 8)
     and staging mode (0 double-buffered, 1 pipelined, 2 operand in LDS, 3 wide
     blocks of 1024 sequences (nw 4), -1 by product depth)."""
     _check(library().hp_blocked_select(nw, mode), "hp_blocked_select")
 
 
 def hp_blocked_selected():
-    """(nw, mode) of the blocked int8 form."""
+    """(nw, mode) of the blocked form."""
     nw, mode = ctypes.c_int(), ctypes.c_int()
     library().hp_blocked_selected(ctypes.byref(nw), ctypes.byref(mode))
     return nw.value, mode.value

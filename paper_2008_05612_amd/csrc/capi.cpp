@@ -591,7 +591,7 @@ hp_status hp_enumerate_symmetric_wide(const hp_structs *s, const void *d_ws, uin
         return fail(HP_EINVAL, "workspace pointer is NULL");
     if (!s->wide_ok)
         return fail(HP_EUNSUPPORTED, "wide blocks need pure pair energies, N >= 10 and "
-                                     "per-block bytes within int8");
+                                     "weights within the blocked form's bounds");
     if (b_lo >= b_hi)
         return fail(HP_EINVAL, "empty block range (b_lo >= b_hi)");
     if (b_hi > hp_wide_block_count(s))

@@ -30,8 +30,9 @@
 //
 // Per 32 x 32 (conformation x sequence) tile this issues one MFMA of depth
 // 32 instead of K_pad/32 of them; stage one adds K_pad/32 MFMAs per
-// conformation tile per 256 sequences.  The epilogue is the same top-2 key
-// update as the dense form, which now bounds the kernel.
+// conformation tile per 256 sequences.  Blocks of 256 reduce each product's 16
+// keys to their largest and update the top-2 where it counts (stage_two); the
+// wide blocks below, which run wherever they apply, scan for thresholds.
 #pragma once
 
 #include <algorithm>

@@ -1,6 +1,7 @@
 // int8-MFMA ground-state kernels for product depths K_pad = 352 .. 384 (N up
 // to 36 with a two-letter contact table, e.g. the 6x6 square).  The first
-// entry per depth is the default shape; the autotuner may pick any other.
+// entry per depth is the default shape beside the scan; the autotuner may pick
+// any other.
 #include "gemm_body.h"
 
 namespace hpmap {

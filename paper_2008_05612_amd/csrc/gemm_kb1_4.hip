@@ -1,6 +1,6 @@
 // int8-MFMA ground-state kernels for product depths K_pad = 32 .. 128
 // (boxes up to N = 24, e.g. 4x4 and 2x3x4).  The first entry per depth is the
-// default shape; the autotuner may pick any other.
+// default shape beside the scan; the autotuner may pick any other.
 #include "gemm_body.h"
 
 namespace hpmap {

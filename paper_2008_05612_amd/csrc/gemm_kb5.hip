@@ -1,6 +1,6 @@
 // int8-MFMA ground-state kernels for product depth K_pad = 160 (5x5 and the
-// 3x3x3 cube).  The first entry is the default shape; the autotuner may pick
-// any other.
+// 3x3x3 cube).  The first entry is the default shape beside the scan; the
+// autotuner may pick any other.
 #include "gemm_body.h"
 
 namespace hpmap {

@@ -1,7 +1,7 @@
 // int8-MFMA ground-state kernels for product depths K_pad = 192 .. 320
 // (N = 28 .. 36, e.g. the 6x6 square; the 3x3x3 cube with a two-letter
 // contact table).  The first entry per depth is the
-// default shape; the autotuner may pick any other.
+// default shape beside the scan; the autotuner may pick any other.
 #include "gemm_body.h"
 
 namespace hpmap {

@@ -110,8 +110,8 @@ constexpr int kLow8NumPairs = 9;
 // kLow10Pairs1 (shared by the host tables and the kernel).
 constexpr int kWideBits = 10;
 constexpr int kWideWaveBits = 9;
-// The second product packs the contact counts of two sequences in one
-// accumulator, 6 bits each (no accepted box has more than 28 contacts).
+// The scans hold a contact count in fields of 6 bits, several to an accumulator
+// (no box of up to 36 monomers has more than 28 contacts).
 constexpr uint32_t kScanMaxContacts = 31;
 // Dense scan with unary rows: thresholds are formed from digits up to this.
 constexpr int64_t kScanMaxUnF = 742;

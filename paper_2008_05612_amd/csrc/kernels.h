@@ -71,7 +71,7 @@ struct BatchHeader {
     int32_t kb_max;
 };
 
-// One compiled tile shape of the int8 form: KB = K_pad/32 product depth, T
+// One compiled tile shape of the dense form in int8: KB = K_pad/32 product depth, T
 // sequence tiles of 32 per wave, NW waves per workgroup, A staged through
 // LDS (mode 0) or loaded per wave from global memory (mode 1).
 struct GemmVariant {
@@ -85,7 +85,8 @@ int gemm_variants_kb5(const GemmVariant **out);
 int gemm_variants_kb6_10(const GemmVariant **out);
 int gemm_variants_kb11_12(const GemmVariant **out);
 
-// Shape used for product depth KB (process-wide choice; default: first listed).
+// Shape used for product depth KB where the scan is not (process-wide choice;
+// default: first listed).
 const GemmVariant *gemm_selected_variant(int KB);
 
 hipError_t launch_popcount(const EnumJob &j, hipStream_t st);
@@ -96,7 +97,7 @@ hipError_t launch_scan(const EnumJob &j, hipStream_t st);
 // (hp_gemm_select, hp_autotune).
 bool gemm_scans(int KB);
 constexpr int kGemmModeScan = 3;   // the scan's entry in the list of shapes
-// Block-factorised int8 form over a plain range (pure pair energies); nw
+// Block-factorised form over a plain range, or canonical blocks; nw
 // waves per workgroup (2, 4 or 8), one 256-sequence block per wave; mode 0
 // stages contact tiles through double-buffered LDS, mode 1 through triple-
 // buffered LDS with the next tile's first product overlapping this tile's

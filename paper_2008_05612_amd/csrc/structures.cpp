@@ -840,7 +840,9 @@ hp_status build_structures(int X, int Y, int Z, const int32_t table[4], hp_struc
         }
         s->wide_un = B > 0 && maxw <= 127 && A + 2 * B <= 127 && fmax < (1 << 13) &&
                      n_tiles <= kScanMaxTiles;
-        // (weights are counts of contacts, at most 5: FP6 holds 15 exactly)
+        // The kernel scores counts of contacts (weights at most 5; FP6 holds 15
+        // exactly) and multiplies by A at the end.  blk_coef maxw <= 128 is the
+        // bound of int8 rows; it stays as the line of what callers are given.
         s->wide_ok = B == 0 && maxw <= 15 * A && int64_t(s->blk_coef) * maxw <= 128 && s->nbp <= kScanMaxContacts &&
                      s->scan_kb > 0 &&
                      (s->K + 3 + 63) / 64 == (s->blk_KB + 1) / 2;
