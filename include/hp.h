@@ -354,7 +354,7 @@ void hp_graph_free(hp_graph *g);
  * allocate device memory (code under hipGraph capture, tight serving loops,
  * harnesses that forbid allocation).  It takes no workspace: the work list
  * lives in a device array of the library, one per GPU, sized for
- * HP_STATIC_BATCH_MAX_JOBS jobs (about 10 KiB) and held until the process
+ * HP_STATIC_BATCH_MAX_JOBS jobs (about 11 KiB) and held until the process
  * ends; every call on that GPU rewrites it.  The call allocates nothing: the
  * list reaches the array through kernel launches on `stream`, in stream
  * order after the work already queued there, and the call does not wait.

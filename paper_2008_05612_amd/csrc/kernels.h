@@ -129,7 +129,9 @@ uint64_t wide_blocks(int kind, uint64_t lo, uint64_t hi);
 // A plain range cut into blocks of 4096 in its whole chunks of 2^19, of 2048
 // in the whole chunks of 2^17 on both sides of those, and of 1024 in the
 // rest.  n3, n2, n1: blocks of each size; those of 2048 and 1024 start at block
-// lo2 / lo1 (n2_lo / n1_lo of them) and go on after the gap at hi2 / hi1.
+// lo2 / lo1 (n2_lo / n1_lo of them) and go on after the gap at hi2 / hi1.  Only
+// for ranges that hold a whole chunk, as those of more than 256 blocks of 1024
+// do: the blocks that a last workgroup of four has beyond n1 then lie past hi.
 struct WideCut {
     uint64_t lo3, lo2, hi2, lo1, hi1;
     uint32_t n3, n2, n2_lo, n1, n1_lo;
