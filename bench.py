@@ -18,7 +18,7 @@ wide blocks, int8 otherwise; "extra" has the int8 fraction too).  What the
 kernel issues instead (depth-32 products, the first product per block, the
 vector-ALU scan of each product) is reported under "extra".
 
-Prints ONE JSON line.  Extra measurements (dense int8 and popcount forms, the
+Prints ONE JSON line.  Extra measurements (dense and popcount forms, the
 full 6x6 map, the mixed-lattice batch, the sampling mode, per-kernel times) go
 in the same line under "extra".
 """
@@ -267,8 +267,8 @@ def main():
     if not args.no_extra:
         extra.update(extra_measurements(hp, s, ws, dev, out))
     if args.profile:
-        # the dense int8 form over the same full map, once, so that profiles of
-        # this run cover both int8 kernels
+        # the dense form over the same full map, once, so that profiles of
+        # this run cover both kernels
         hp.hp_enumerate(s, ws, hp.FORM_GEMM_I8, 0, total, out)
         torch.cuda.synchronize()
         # a plain copy of known size, for scaling the FETCH_SIZE / WRITE_SIZE counters
@@ -336,7 +336,7 @@ def recorded_issue(kname, src_hash):
 def extra_measurements(hp, s, ws, dev, blocked_map):
     """The whole phi_pq matrix of the full 3x3x3 map (dense counts and
     compressed rows), the paper's own timed workload (Table 1 energies,
-    sampled sequences) on 3x3x3 and 6x6, the dense int8 form over the same
+    sampled sequences) on 3x3x3 and 6x6, the dense form over the same
     full 3x3x3 map (its fractions of the int8 MFMA peak, and a bit-exact
     comparison with the blocked form's map), the popcount form on a 2^24
     slice, the sampling mode on both lattices, one 2^28 block of the 6x6 map
